@@ -57,7 +57,8 @@ typedef enum gs_status {
  *   GS_STATE_WORKER_MAJOR  [P][d]: element (q, i) at q*d + i (the default, 0).
  *   GS_STATE_INTERLEAVED   [d][GS_STATE_STRIDE(P)]: element (q, i) at i*GS_STATE_STRIDE(P) + q,
  *                          rows padded to a multiple of 4 floats (16 bytes). The padding
- *                          entries (q >= P) are never written and never affect a result.
+ *                          entries (q >= P) keep their contents (a call may store the value
+ *                          it read back) and never affect a result.
  * The interleaved form keeps the P values of a coordinate in one 16-byte-aligned row, which
  * is what the sketch gathers, so the step needs no interleaved copy of v. */
 #define GS_STATE_WORKER_MAJOR 0

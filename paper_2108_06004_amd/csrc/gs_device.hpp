@@ -95,6 +95,18 @@ __device__ __forceinline__ float tree_sum(float (&x)[P]) {
   return x[0];
 }
 
+// The same tree over the first P <= PX elements, in registers (P uniform at run time).
+template <int PX>
+__device__ __forceinline__ float tree_sum_upto(float (&x)[PX], int P) {
+#pragma unroll
+  for (int s = 1; s < PX; s <<= 1) {
+#pragma unroll
+    for (int m = 0; m + s < PX; m += 2 * s)
+      if (m + s < P) x[m] = x[m] + x[m + s];
+  }
+  return x[0];
+}
+
 // Runtime-P variant over a private array (used only when P is not one of the unrolled
 // template instances).
 __device__ __forceinline__ float tree_sum_dyn(float* x, int P) {

@@ -77,7 +77,7 @@ struct PullPlan {
   // Packed lists: each tile's list starts at a multiple of kListGroup entries; an entry is
   // one word, the coordinate's offset from its group's base (the group's first coordinate)
   // in the low off_bits bits, the position in the tile above it, the sign in bit 31. When a
-  // group's coordinates span too much for off_bits (or P > 16) the lists stay unpacked:
+  // group's coordinates span too much for off_bits the lists stay unpacked:
   // coordinates in `list`, position | sign << 15 in `codes`.
   int32_t packed;
   int32_t off_bits;
@@ -214,7 +214,7 @@ hipError_t launch_accumulate_vi(const gs_ctx* x, hipStream_t s, const float* g, 
 hipError_t launch_interleave(const gs_ctx* x, hipStream_t s, const float* v);
 // The pull gathers rows of PP floats (16-byte aligned) from `rows`: the context's interleaved
 // copy x->vI, or the caller's v itself when the state is interleaved. When pull_merges(x)
-// (P <= 16 and one list segment per tile) it also writes the per-worker tables and/or the
+// (one list segment per tile) it also writes the per-worker tables and/or the
 // merged sketch (non-null outputs) and launch_merge_partials has nothing left to do; pass
 // the same outputs to both.
 hipError_t launch_pull(const gs_ctx* x, hipStream_t s, const float* rows, float* merged, float* tables);

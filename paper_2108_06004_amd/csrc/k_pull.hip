@@ -32,10 +32,15 @@ constexpr int kBlock = 256;
 // measured best at 512 threads and about 1,500 entries per CU (4 per group when one lane
 // takes an entry, P <= 4; 6 otherwise).
 constexpr int kPullBlock = 512;
-constexpr int pull_unroll(int P) { return P <= 4 ? 4 : 6; }
+constexpr int pull_unroll(int PP) { return PP <= 4 ? 4 : 6; }
 // Whether a pass fetches the next pass's list words while its own rows are in flight (see
-// k_pull): the one-worker plain-vector gather and four lanes per entry (P >= 13).
-constexpr bool pull_pipelined(int P, bool flat) { return flat || P >= 13; }
+// k_pull): the one-worker plain-vector gather and four or more lanes per entry (P >= 13).
+constexpr bool pull_pipelined(int PP, bool flat) { return flat || PP >= 16; }
+// Padding of a worker's column of LDS cells (see k_pull). The L = PP / 4 lanes of an entry add
+// into columns four apart, so their banks (32 pairs) are 4 (W32 + pad) doubles apart: with pad 6
+// two lanes are 24 apart and four lanes hit distinct pairs; beyond four lanes pad 1 spaces eight
+// lanes by four pairs, all distinct, where pad 6 would pair them up.
+__host__ __device__ constexpr int tile_pad(int PP) { return PP > 16 ? 1 : 6; }
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 int grid_for(int64_t work_items, int per_block, int cap) {
@@ -337,28 +342,57 @@ __global__ void __launch_bounds__(kBlock) k_vi_il(const float* __restrict__ g, f
     if (ch * CW + sub < d) pass(ch, std::integral_constant<int, 1>());
 }
 
-// Generic (any P, any d, any alignment): one lane per (coordinate, worker).
-// Coordinates from i_lo on.
-__global__ void __launch_bounds__(kBlock) k_accumulate_vi_any(const float* __restrict__ g, float* __restrict__ u,
-                                                              float* __restrict__ v, float* __restrict__ vI,
-                                                              int64_t d, int P, int PP, float rho, int do_acc,
-                                                              int64_t i_lo) {
-  const int64_t dt = d - i_lo;
-  const int64_t n = (int64_t)P * dt;
+// The same for P > 16, where a wave's chunk would be 12 coordinates or fewer (48-byte pieces of
+// each worker row or less). Here a wave covers 64 consecutive coordinates, a lane each, and walks the workers
+// eight at a time (24 loads in flight), so every access of the worker rows is 256 contiguous
+// bytes; the values of v pass through an LDS tile (rows of PP + 4 floats: 16-byte aligned, and
+// consecutive rows start four banks apart) from which the vI rows leave in 16-byte pieces, 1 KB
+// contiguous per instruction.
+template <bool ACC>
+__global__ void __launch_bounds__(kBlock) k_vi_wide(const float* __restrict__ g, float* __restrict__ u,
+                                                    float* __restrict__ v, float* __restrict__ vI, int64_t d,
+                                                    float rho, int P, int PP) {
+  extern __shared__ __align__(16) float tile[];  // [kBlock / 64][64][PP + 4]
+  constexpr int UW = 8;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ld = PP + 4;
+  float* const mine = tile + (int64_t)wave * 64 * ld;
   const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < n; t += stride) {
-    const int64_t q = t / dt, i = i_lo + (t - q * dt);
-    const int64_t e = q * d + i;
-    float w;
-    if (do_acc) {
-      const float un = rho * u[e] + g[e];
-      u[e] = un;
-      w = v[e] + un;
-      v[e] = w;
-    } else {
-      w = v[e];
+  for (int64_t b0 = (int64_t)blockIdx.x * kBlock; b0 < d; b0 += stride) {  // block-uniform
+    const int64_t i0 = b0 + 64 * wave, i = i0 + lane;
+    const bool in = i < d;
+    for (int q0 = 0; q0 < PP; q0 += UW) {
+      float x[UW], uu[UW], gg[UW];
+#pragma unroll
+      for (int m = 0; m < UW; ++m) {
+        const bool ok = in && q0 + m < P;
+        const int64_t o = (int64_t)(q0 + m) * d + i;
+        if constexpr (ACC) {
+          gg[m] = ok ? __builtin_nontemporal_load(g + o) : 0.f;
+          uu[m] = ok ? __builtin_nontemporal_load(u + o) : 0.f;
+        }
+        x[m] = ok ? __builtin_nontemporal_load(v + o) : 0.f;
+      }
+#pragma unroll
+      for (int m = 0; m < UW; ++m) {
+        const int64_t o = (int64_t)(q0 + m) * d + i;
+        if (ACC && in && q0 + m < P) {
+          uu[m] = rho * uu[m] + gg[m];
+          x[m] = x[m] + uu[m];
+          __builtin_nontemporal_store(uu[m], u + o);
+          __builtin_nontemporal_store(x[m], v + o);
+        }
+        if (q0 + m < PP) mine[lane * ld + q0 + m] = x[m];
+      }
     }
-    vI[i * PP + q] = w;
+    __syncthreads();
+    const int G = PP / 4;
+    const int64_t n = d - i0 < 64 ? d - i0 : 64;  // coordinates of this wave's chunk (may be <= 0)
+    for (int t = lane; t < n * G; t += 64) {
+      const int row = t / G, h = t - row * G;
+      reinterpret_cast<f4*>(vI + (i0 + row) * PP)[h] = *reinterpret_cast<const f4*>(mine + row * ld + 4 * h);
+    }
+    __syncthreads();
   }
 }
 
@@ -372,19 +406,6 @@ __global__ void __launch_bounds__(kBlock) k_copy_rows(const float* __restrict__ 
 
 // ------------------------------------------------------------------------------------
 // The pull: one workgroup per (tile, segment).
-
-template <int PP>
-__device__ __forceinline__ void load_row(const float* __restrict__ vI, uint32_t i, float (&x)[PP]) {
-  const f4* p = reinterpret_cast<const f4*>(vI + (int64_t)i * PP);
-#pragma unroll
-  for (int m = 0; m < PP / 4; ++m) {
-    const f4 y = p[m];
-    x[4 * m + 0] = y.x;
-    x[4 * m + 1] = y.y;
-    x[4 * m + 2] = y.z;
-    x[4 * m + 3] = y.w;
-  }
-}
 
 // L = PP/4 adjacent lanes share one list entry; lane `sub` of the group gathers workers
 // [4 sub, 4 sub + 4) of the row (16 B) and adds them into the tile.
@@ -421,21 +442,23 @@ __device__ __forceinline__ void segment_bounds(int64_t lo, int64_t n, int64_t s,
 // Workers 4 sub .. 4 sub + 3 of coordinate i: one 16-byte load of an interleaved row (rows of
 // PP floats, 16-byte aligned), or, with FLAT (one worker: the state [1][d] is a plain vector),
 // the coordinate's one value.
-template <int P, bool FLAT>
+// Rows of more than 16 workers need no 16-byte alignment (dword-aligned vector loads).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int PP, bool FLAT>
 __device__ __forceinline__ f4 load_quad(const float* __restrict__ v, uint32_t i, int sub) {
-  constexpr int PP = (P + 3) & ~3;
   if constexpr (FLAT) {
-    static_assert(P == 1, "a flat state holds one worker");
     f4 x;
     x.x = v[i];
     x.y = x.z = x.w = 0.f;
     return x;
   } else {
-    return reinterpret_cast<const f4*>(v + (int64_t)i * PP)[sub];
+    using F4 = typename std::conditional<(PP > 16), f4u, f4>::type;
+    return reinterpret_cast<const F4*>(v + (int64_t)i * PP)[sub];
   }
 }
 
-template <int P, int U, bool PK, bool FLAT>
+// NP > 0: P = NP workers, fixed at compile time; NP = 0 (P > 16): P = pl.P <= PP at run time.
+template <int NP, int U, bool PK, bool FLAT, int PP = (NP + 3) / 4 * 4>
 __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, const uint32_t* __restrict__ list,
                                                      const uint16_t* __restrict__ codes,
                                                      const uint32_t* __restrict__ bases,
@@ -443,7 +466,8 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
                                                      const float* __restrict__ vI, double* __restrict__ partial,
                                                      float* __restrict__ merged, float* __restrict__ tables) {
   extern __shared__ double acc[];  // [P][ws] (below): worker-major, so lanes adding for one worker hit spread banks
-  constexpr int PP = (P + 3) & ~3;
+  static_assert(!FLAT || NP == 1, "a flat state holds one worker");
+  const int P = NP > 0 ? NP : pl.P;
   constexpr int L = PP / 4;
   constexpr int64_t B = kPullBlock / L;  // entries per block pass
   const int sub = threadIdx.x % L;
@@ -460,9 +484,9 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
   const int j = (int)(t / pl.tiles_per_row);
   const int64_t kt = t - (int64_t)j * pl.tiles_per_row;
   const int64_t wt = min((int64_t)pl.W, (int64_t)hs.c - kt * pl.W);
-  // column stride: whole blocks of 32 cells (for the swizzle) plus 6, so that the two or four
-  // workers' columns one wave instruction adds into start in different banks
-  const int64_t ws = ((wt + 31) & ~31ll) + 6;
+  // column stride: whole blocks of 32 cells (for the swizzle) plus a pad, so that the workers'
+  // columns one wave instruction adds into start in different banks (tile_pad)
+  const int64_t ws = ((wt + 31) & ~31ll) + tile_pad(PP);
   const int swz = pl.swz[j];
   for (int64_t e = threadIdx.x; e < ws * P; e += kPullBlock) acc[e] = 0.0;
   __syncthreads();
@@ -477,16 +501,16 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
   // round trip (the rows), not two (words, then rows): measured faster where a pass moves
   // little (one worker's 4-byte values: 0.39 -> 0.30 ms at d = 25.6M) or where the miss
   // latency is long (66M x 16: 6.10 -> 5.71 ms), slower at 25.6M x 8 (0.66 -> 0.73 ms).
-  constexpr bool PIPE = pull_pipelined(P, FLAT);
+  constexpr bool PIPE = pull_pipelined(PP, FLAT);
   uint32_t wn[U], an[U];
   auto fetch = [&](int64_t ebx) {
 #pragma unroll
     for (int m = 0; m < U; ++m) {
       const int64_t e = ebx + m * B;
       wn[m] = list[e];
-      if constexpr (PK && (L == 1 || L == 2 || L == 4)) {
-        static_assert(B % kListGroup == 0 && kListGroup % (64 / L) == 0, "a wave's entries must share a group");
-        // e0 is group-aligned, B is a multiple of kListGroup and a wave's lanes take 64 / L
+      if constexpr (PK && (L & (L - 1)) == 0) {
+        static_assert(B % (64 / L) == 0 && kListGroup % (64 / L) == 0, "a wave's entries must share a group");
+        // e0 is group-aligned, B is a multiple of 64 / L and a wave's lanes take 64 / L
         // consecutive entries of an aligned run (permuted within it): every lane active in
         // this pass needs the same group base, so the wave loads it once, as a scalar. The
         // tail loop below cannot do this (its lanes may be one pass apart).
@@ -504,7 +528,7 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
       for (int m = 0; m < U; ++m) decode_entry<PK>(wn[m], an[m], pl.off_bits, i[m], pos[m], sg[m]);
       f4 x[U];
 #pragma unroll
-      for (int m = 0; m < U; ++m) x[m] = load_quad<P, FLAT>(vI, i[m], sub);
+      for (int m = 0; m < U; ++m) x[m] = load_quad<PP, FLAT>(vI, i[m], sub);
       const int64_t ebn = eb + U * B;
       const bool more = ebn + (U - 1) * B < e1;
       if (more) fetch(ebn);
@@ -515,7 +539,7 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
         const float xs[4] = {x[m].x, x[m].y, x[m].z, x[m].w};
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          if (P % 4 == 0 || 4 * sub + q < P) atomicAdd(cell + q * ws, (double)apply_sign(xs[q], sflip));
+          if ((NP > 0 && NP % 4 == 0) || 4 * sub + q < P) atomicAdd(cell + q * ws, (double)apply_sign(xs[q], sflip));
       }
       eb = ebn;
       if (!more) break;
@@ -528,7 +552,7 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
     for (int m = 0; m < U; ++m) decode_entry<PK>(wn[m], an[m], pl.off_bits, i[m], pos[m], sg[m]);
     f4 x[U];
 #pragma unroll
-    for (int m = 0; m < U; ++m) x[m] = load_quad<P, FLAT>(vI, i[m], sub);
+    for (int m = 0; m < U; ++m) x[m] = load_quad<PP, FLAT>(vI, i[m], sub);
 #pragma unroll
     for (int m = 0; m < U; ++m) {
       double* cell = mycol + tile_cell(pos[m], swz);
@@ -536,18 +560,18 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
       const float xs[4] = {x[m].x, x[m].y, x[m].z, x[m].w};
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (P % 4 == 0 || 4 * sub + q < P) atomicAdd(cell + q * ws, (double)apply_sign(xs[q], sflip));
+        if ((NP > 0 && NP % 4 == 0) || 4 * sub + q < P) atomicAdd(cell + q * ws, (double)apply_sign(xs[q], sflip));
     }
   }
   for (; eb < e1; eb += B) {
     uint32_t i, pos, sflip;
     decode_entry<PK>(list[eb], PK ? bases[eb / kListGroup] : (uint32_t)codes[eb], pl.off_bits, i, pos, sflip);
-    const f4 x = load_quad<P, FLAT>(vI, i, sub);
+    const f4 x = load_quad<PP, FLAT>(vI, i, sub);
     double* cell = mycol + tile_cell(pos, swz);
     const float xs[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (P % 4 == 0 || 4 * sub + q < P) atomicAdd(cell + q * ws, (double)apply_sign(xs[q], sflip));
+      if ((NP > 0 && NP % 4 == 0) || 4 * sub + q < P) atomicAdd(cell + q * ws, (double)apply_sign(xs[q], sflip));
   }
   __syncthreads();
   // write out: tile position o holds column theta_inv_j * (kt W + o) mod c; along the
@@ -559,15 +583,17 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
   const int64_t row0 = (int64_t)j * c;
   if (pl.S == 1 && (merged || tables)) {
     for (int64_t o = threadIdx.x; o < wt; o += kPullBlock) {
-      float x[P];
+      constexpr int PX = NP > 0 ? NP : PP;
+      float x[PX];
       const uint32_t oc = tile_cell((uint32_t)o, swz);
 #pragma unroll
-      for (int q = 0; q < P; ++q) x[q] = (float)acc[q * ws + oc];
+      for (int q = 0; q < PX; ++q) x[q] = q < P ? (float)acc[q * ws + oc] : 0.f;
       if (tables) {
 #pragma unroll
-        for (int q = 0; q < P; ++q) tables[q * rc + row0 + col] = x[q];
+        for (int q = 0; q < PX; ++q)
+          if (q < P) tables[q * rc + row0 + col] = x[q];
       }
-      if (merged) merged[row0 + col] = tree_sum<P>(x);
+      if (merged) merged[row0 + col] = NP > 0 ? tree_sum<PX>(x) : tree_sum_upto<PX>(x, P);
       col = col + cstep >= c ? col + cstep - c : col + cstep;
     }
     return;
@@ -576,41 +602,8 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
   for (int64_t o = threadIdx.x; o < wt; o += kPullBlock) {
     const uint32_t oc = tile_cell((uint32_t)o, swz);
 #pragma unroll
-    for (int q = 0; q < P; ++q) dst[q * rc + col] = acc[q * ws + oc];
-    col = col + cstep >= c ? col + cstep - c : col + cstep;
-  }
-}
-
-// Runtime-P variant (P > 16): rows of PP floats read element by element.
-__global__ void __launch_bounds__(kBlock) k_pull_any(HashSet hs, PullPlan pl, const uint32_t* __restrict__ list,
-                                                     const uint16_t* __restrict__ codes,
-                                                     const int64_t* __restrict__ off, const uint32_t* __restrict__ tn,
-                                                     const float* __restrict__ vI, double* __restrict__ partial) {
-  extern __shared__ double acc[];
-  const int P = pl.P, PP = pl.PP;
-  const int64_t item = grouped_item(blockIdx.x, gridDim.x, pl.slots);
-  const int64_t t = item / pl.S, s = item - t * pl.S;
-  const int j = (int)(t / pl.tiles_per_row);
-  const int64_t kt = t - (int64_t)j * pl.tiles_per_row;
-  const int64_t wt = min((int64_t)pl.W, (int64_t)hs.c - kt * pl.W);
-  for (int64_t e = threadIdx.x; e < wt * P; e += kBlock) acc[e] = 0.0;
-  __syncthreads();
-  int64_t e0, e1;
-  segment_bounds(off[t], tn[t], s, pl.S, e0, e1);
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock) {
-    const uint32_t i = list[e], code = codes[e];
-    double* cell = acc + (code & 0x7fffu);
-    const uint32_t sflip = (code & 0x8000u) << 16;
-    for (int q = 0; q < P; ++q) atomicAdd(cell + q * wt, (double)apply_sign(vI[(int64_t)i * PP + q], sflip));
-  }
-  __syncthreads();
-  const int64_t rc = (int64_t)hs.r * hs.c;
-  const uint32_t c = hs.c;
-  const uint32_t cstep = (uint32_t)(((uint64_t)pl.theta_inv[j] * kBlock) % c);
-  uint32_t col = threadIdx.x < wt ? column_at(hs, pl, j, kt, threadIdx.x) : 0u;
-  double* dst = partial + s * P * rc + (int64_t)j * c;
-  for (int64_t o = threadIdx.x; o < wt; o += kBlock) {
-    for (int q = 0; q < P; ++q) dst[q * rc + col] = acc[q * wt + o];
+    for (int q = 0; q < (NP > 0 ? NP : PP); ++q)
+      if (q < P) dst[q * rc + col] = acc[q * ws + oc];
     col = col + cstep >= c ? col + cstep - c : col + cstep;
   }
 }
@@ -681,25 +674,52 @@ hipError_t launch_vi_il_p(const gs_ctx* x, hipStream_t s, const float* g, float*
   return hipGetLastError();
 }
 
-template <int P, bool FLAT = false>
+// The kernels are instantiated for each P up to 16 and beyond it for each row length PP.
+#define GS_FOR_P16(M) \
+  M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) M(16)
+#define GS_FOR_WIDE(M) M(20) M(24) M(28) M(32) M(36) M(40) M(44) M(48) M(52) M(56) M(60) M(64)
+
+size_t vi_wide_lds(int PP) { return (size_t)kBlock * (PP + 4) * sizeof(float); }  // 69,632 bytes at PP = 64
+
+template <bool ACC>
+hipError_t launch_vi_il(const gs_ctx* x, hipStream_t s, const float* g, float* u, float* v) {
+  switch (x->P) {
+#define GS_VI_CASE(P) case P: return launch_vi_il_p<P, ACC>(x, s, g, u, v);
+    GS_FOR_P16(GS_VI_CASE)
+#undef GS_VI_CASE
+    default: {
+      const int PP = x->plan.PP;
+      hipLaunchKernelGGL(k_vi_wide<ACC>, dim3(grid_for(x->d, kBlock, 64 * x->num_cus)), dim3(kBlock),
+                         vi_wide_lds(PP), s, g, u, v, x->vI, x->d, x->rho, x->P, PP);
+      return hipGetLastError();
+    }
+  }
+}
+
+size_t tile_lds_bytes(const PullPlan& pl) {
+  return (size_t)(((pl.W + 31) & ~31) + tile_pad(pl.PP)) * pl.P * sizeof(double);
+}
+
+template <int NP, bool FLAT = false, int PP = (NP + 3) / 4 * 4>
 void launch_pull_p(const gs_ctx* x, hipStream_t s, const float* rows, float* merged, float* tables) {
   const PullPlan& pl = x->plan;
   const dim3 grid((unsigned)((int64_t)pl.T * pl.S)), block(kPullBlock);
-  const size_t lds = (size_t)(((pl.W + 31) & ~31) + 6) * pl.P * sizeof(double);
+  const size_t lds = tile_lds_bytes(pl);
   if (pl.packed)
-    hipLaunchKernelGGL((k_pull<P, pull_unroll(P), true, FLAT>), grid, block, lds, s, x->hs, pl, x->list, x->codes,
+    hipLaunchKernelGGL((k_pull<NP, pull_unroll(PP), true, FLAT, PP>), grid, block, lds, s, x->hs, pl, x->list, x->codes,
                        x->bases, x->tile_off, x->tile_n, rows, x->partial, merged, tables);
   else
-    hipLaunchKernelGGL((k_pull<P, pull_unroll(P), false, FLAT>), grid, block, lds, s, x->hs, pl, x->list, x->codes,
-                       x->bases, x->tile_off, x->tile_n, rows, x->partial, merged, tables);
+    hipLaunchKernelGGL((k_pull<NP, pull_unroll(PP), false, FLAT, PP>), grid, block, lds, s, x->hs, pl, x->list,
+                       x->codes, x->bases, x->tile_off, x->tile_n, rows, x->partial, merged, tables);
 }
 
-template <int P, bool FLAT = false>
+template <int NP, bool FLAT = false, int PP = (NP + 3) / 4 * 4>
 hipError_t allow_pull_lds(size_t bytes) {
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pull<P, pull_unroll(P), true, FLAT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  const hipError_t e =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pull<NP, pull_unroll(PP), true, FLAT, PP>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pull<P, pull_unroll(P), false, FLAT>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pull<NP, pull_unroll(PP), false, FLAT, PP>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
@@ -886,22 +906,27 @@ PullPlan make_pull_plan(const HashSet& hs, int64_t d, int32_t P, int32_t r, int6
 }
 
 hipError_t prepare_pull_kernels(const gs_ctx* x) {
-  const size_t bytes = (size_t)(((x->plan.W + 31) & ~31) + 6) * x->plan.P * sizeof(double);
-  switch (x->P) {
-#define GS_ALLOW_CASE(PP) \
-  case PP: return allow_pull_lds<PP>(bytes);
-    case 1: {
-      const hipError_t e = allow_pull_lds<1, true>(bytes);
-      if (e != hipSuccess) return e;
-      return allow_pull_lds<1>(bytes);
-    }
-    GS_ALLOW_CASE(2) GS_ALLOW_CASE(3) GS_ALLOW_CASE(4) GS_ALLOW_CASE(5) GS_ALLOW_CASE(6)
-    GS_ALLOW_CASE(7) GS_ALLOW_CASE(8) GS_ALLOW_CASE(9) GS_ALLOW_CASE(10) GS_ALLOW_CASE(11) GS_ALLOW_CASE(12)
-    GS_ALLOW_CASE(13) GS_ALLOW_CASE(14) GS_ALLOW_CASE(15) GS_ALLOW_CASE(16)
+  const size_t bytes = tile_lds_bytes(x->plan);
+  if (x->P == 1) {
+    const hipError_t e = allow_pull_lds<1, true>(bytes);
+    if (e != hipSuccess) return e;
+  }
+  if (x->P > 16) {
+    const int wide = (int)vi_wide_lds(x->plan.PP);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vi_wide<true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, wide);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vi_wide<false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, wide);
+    if (e != hipSuccess) return e;
+  }
+  switch (x->P <= 16 ? x->P : x->plan.PP) {
+#define GS_ALLOW_CASE(P) case P: return allow_pull_lds<P>(bytes);
+#define GS_ALLOW_WIDE(PP) case PP: return allow_pull_lds<0, false, PP>(bytes);
+    GS_FOR_P16(GS_ALLOW_CASE) GS_FOR_WIDE(GS_ALLOW_WIDE)
 #undef GS_ALLOW_CASE
-    default:
-      return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pull_any),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+#undef GS_ALLOW_WIDE
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -938,9 +963,8 @@ hipError_t build_pull_lists(gs_ctx* x) {
   }
   uint32_t overflow = 1;
   if (e == hipSuccess) e = hipMemcpy(&overflow, flag, sizeof(uint32_t), hipMemcpyDeviceToHost);
-  // pack when every group's span fits (and the unrolled pulls run: P <= 16); off_bits = 0
-  // keeps the lists unpacked
-  if (e == hipSuccess && overflow == 0 && x->P <= 16 && pl.off_bits > 0) {
+  // pack when every group's span fits; off_bits = 0 keeps the lists unpacked
+  if (e == hipSuccess && overflow == 0 && pl.off_bits > 0) {
     hipLaunchKernelGGL(k_build_pack, dim3(pl.T), dim3(kBlock), 0, 0, x->list, x->codes, x->bases, x->tile_off,
                        x->tile_n, pl.off_bits, 1, flag);
     e = hipGetLastError();
@@ -959,36 +983,12 @@ hipError_t build_pull_lists(gs_ctx* x) {
 }
 
 hipError_t launch_accumulate_vi(const gs_ctx* x, hipStream_t s, const float* g, float* u, float* v) {
-  switch (x->P) {
-#define GS_ACCVI_CASE(PP) \
-  case PP: return launch_vi_il_p<PP, true>(x, s, g, u, v);
-    GS_ACCVI_CASE(1) GS_ACCVI_CASE(2) GS_ACCVI_CASE(3) GS_ACCVI_CASE(4) GS_ACCVI_CASE(5) GS_ACCVI_CASE(6)
-    GS_ACCVI_CASE(7) GS_ACCVI_CASE(8) GS_ACCVI_CASE(9) GS_ACCVI_CASE(10) GS_ACCVI_CASE(11) GS_ACCVI_CASE(12)
-    GS_ACCVI_CASE(13) GS_ACCVI_CASE(14) GS_ACCVI_CASE(15) GS_ACCVI_CASE(16)
-#undef GS_ACCVI_CASE
-    default: break;
-  }
-  const int64_t n = (int64_t)x->P * x->d;
-  hipLaunchKernelGGL(k_accumulate_vi_any, dim3(grid_for(n, kBlock, 8 * x->num_cus)), dim3(kBlock), 0, s, g, u, v,
-                     x->vI, x->d, x->P, x->plan.PP, x->rho, 1, (int64_t)0);
-  return hipGetLastError();
+  return launch_vi_il<true>(x, s, g, u, v);
 }
 
 hipError_t launch_interleave(const gs_ctx* x, hipStream_t s, const float* v) {
-  float* src = const_cast<float*>(v);  // read only (no accumulation)
-  switch (x->P) {
-#define GS_IL_CASE(PP) \
-  case PP: return launch_vi_il_p<PP, false>(x, s, nullptr, nullptr, src);
-    GS_IL_CASE(1) GS_IL_CASE(2) GS_IL_CASE(3) GS_IL_CASE(4) GS_IL_CASE(5) GS_IL_CASE(6) GS_IL_CASE(7) GS_IL_CASE(8)
-    GS_IL_CASE(9) GS_IL_CASE(10) GS_IL_CASE(11) GS_IL_CASE(12) GS_IL_CASE(13) GS_IL_CASE(14) GS_IL_CASE(15)
-    GS_IL_CASE(16)
-#undef GS_IL_CASE
-    default: break;
-  }
-  const int64_t n = (int64_t)x->P * x->d;
-  hipLaunchKernelGGL(k_accumulate_vi_any, dim3(grid_for(n, kBlock, 8 * x->num_cus)), dim3(kBlock), 0, s, nullptr,
-                     nullptr, src, x->vI, x->d, x->P, x->plan.PP, x->rho, 0, (int64_t)0);
-  return hipGetLastError();
+  // the source is read only (no accumulation)
+  return launch_vi_il<false>(x, s, nullptr, nullptr, const_cast<float*>(v));
 }
 
 hipError_t launch_pull_flat(const gs_ctx* x, hipStream_t s, const float* v, float* merged, float* tables) {
@@ -998,25 +998,21 @@ hipError_t launch_pull_flat(const gs_ctx* x, hipStream_t s, const float* v, floa
 }
 
 hipError_t launch_pull(const gs_ctx* x, hipStream_t s, const float* rows, float* merged, float* tables) {
-  switch (x->P) {
-#define GS_PULL_CASE(PP) \
-  case PP: launch_pull_p<PP>(x, s, rows, merged, tables); break;
-    GS_PULL_CASE(1) GS_PULL_CASE(2) GS_PULL_CASE(3) GS_PULL_CASE(4) GS_PULL_CASE(5) GS_PULL_CASE(6) GS_PULL_CASE(7)
-    GS_PULL_CASE(8) GS_PULL_CASE(9) GS_PULL_CASE(10) GS_PULL_CASE(11) GS_PULL_CASE(12) GS_PULL_CASE(13)
-    GS_PULL_CASE(14) GS_PULL_CASE(15) GS_PULL_CASE(16)
+  switch (x->P <= 16 ? x->P : x->plan.PP) {
+#define GS_PULL_CASE(P) \
+  case P: launch_pull_p<P>(x, s, rows, merged, tables); break;
+#define GS_PULL_WIDE(PP) \
+  case PP: launch_pull_p<0, false, PP>(x, s, rows, merged, tables); break;
+    GS_FOR_P16(GS_PULL_CASE) GS_FOR_WIDE(GS_PULL_WIDE)
 #undef GS_PULL_CASE
-    default: {
-      const PullPlan& pl = x->plan;
-      hipLaunchKernelGGL(k_pull_any, dim3((unsigned)((int64_t)pl.T * pl.S)), dim3(kBlock),
-                         (size_t)pl.W * pl.P * sizeof(double), s, x->hs, pl, x->list, x->codes, x->tile_off,
-                         x->tile_n, rows, x->partial);
-    }
+#undef GS_PULL_WIDE
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 const float* pull_rows_of_state(const gs_ctx* x, hipStream_t s, const float* v, hipError_t* e) {
-  // the unrolled pulls (P <= 16) load 16-byte pieces of a row; the generic one loads floats
+  // the pulls of up to 16 workers load 16-byte aligned pieces of a row, the wider ones any floats
   if (x->P > 16 || ((uintptr_t)v & 15u) == 0) {
     *e = hipSuccess;
     return v;
@@ -1027,7 +1023,7 @@ const float* pull_rows_of_state(const gs_ctx* x, hipStream_t s, const float* v, 
   return x->vI;
 }
 
-bool pull_merges(const gs_ctx* x) { return x->P <= 16 && x->plan.S == 1; }
+bool pull_merges(const gs_ctx* x) { return x->plan.S == 1; }
 
 hipError_t launch_merge_partials(const gs_ctx* x, hipStream_t s, float* merged, float* tables) {
   if (pull_merges(x)) return hipSuccess;  // the pull wrote merged / tables itself

@@ -79,9 +79,11 @@ __global__ void __launch_bounds__(kBlock) k_accumulate1(const float* __restrict_
 // the 16-byte group h = l%G of its row (workers 4h..4h+3), so consecutive lanes read and
 // write consecutive 16-byte pieces of u and v; the four gradient values come from four
 // worker rows of g (4-byte loads, 4*CW bytes contiguous per row and wave). Each pass a wave
-// takes U consecutive chunks (four, eight for G = 4), all in flight together, so when CW*4
-// bytes is less than a 128-byte line (G = 3, 4) the rest of the line is read by the wave's
-// next instruction.
+// takes U consecutive chunks (four, eight for G >= 4), all in flight together, so when CW*4
+// bytes is less than a 128-byte line (G >= 3) the rest of the line is read by the wave's
+// next instructions. Beyond G = 4 those pieces are 32 bytes or less, and the gradients are then
+// loaded with ordinary loads: non-temporal ones fetched each line several times (2M x 32: 232
+// against 194 us; one lane per (coordinate, worker), as before, 422 us).
 // The chunks past the last group run one at a time, and with RAGGED (d not a multiple
 // of CW) the first wave then takes the partial last chunk, whose lanes past d take no
 // coordinate. The non-ragged form is kept free of that code: the compiler schedules this loop
@@ -95,9 +97,9 @@ __global__ void __launch_bounds__(kBlock) k_accumulate_il(const float* __restric
                                                           float* __restrict__ v, int64_t d, float rho) {
   constexpr int CW = 64 / G;
   constexpr int PP = 4 * G;
-  constexpr int U = G == 4 ? 8 : 4;
+  constexpr int U = G >= 4 ? 8 : 4;
   const int lane = threadIdx.x & 63;
-  if (lane >= CW * G) return;  // G = 3: one idle lane per wave (no barrier below)
+  if (lane >= CW * G) return;  // G no power of two: idle lanes (no barrier below)
   const int h = lane % G;
   const int64_t sub = lane / G;
   const int64_t nch = d / CW;  // full chunks
@@ -110,14 +112,21 @@ __global__ void __launch_bounds__(kBlock) k_accumulate_il(const float* __restric
     for (int m = 0; m < U; ++m) {
       const int64_t i = (gr * U + m) * CW + sub;
       const float* gq = g + (int64_t)(4 * h) * d + i;
-      gg[m].x = __builtin_nontemporal_load(gq);
-      gg[m].y = __builtin_nontemporal_load(gq + d);
-      gg[m].z = __builtin_nontemporal_load(gq + 2 * d);
-      gg[m].w = __builtin_nontemporal_load(gq + 3 * d);
+      if constexpr (G > 4) {
+        gg[m].x = gq[0];
+        gg[m].y = gq[d];
+        gg[m].z = gq[2 * d];
+        gg[m].w = gq[3 * d];
+      } else {
+        gg[m].x = __builtin_nontemporal_load(gq);
+        gg[m].y = __builtin_nontemporal_load(gq + d);
+        gg[m].z = __builtin_nontemporal_load(gq + 2 * d);
+        gg[m].w = __builtin_nontemporal_load(gq + 3 * d);
+      }
       uu[m] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(u + i * PP) + h);
       ww[m] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(v + i * PP) + h);
     }
-    if constexpr (G == 4) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (G >= 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < U; ++m) {
       const int64_t i = (gr * U + m) * CW + sub;
@@ -160,6 +169,72 @@ __global__ void __launch_bounds__(kBlock) k_accumulate_il(const float* __restric
       *up = uu;
       *vp = ww;
     }
+  }
+}
+
+// P not a multiple of four: the row's last group holds rem = P mod 4 workers. Its lanes load and
+// store the whole 16-byte piece, the padding with the value it holds: rows stored without their
+// padding reach memory as partial lines (7M x 3: 108 us, against 78 us with whole pieces and
+// 113 us one lane per (coordinate, worker); 1.2M x 6: 45.8, 33.7 and 41.3 us).
+template <int G>
+__global__ void __launch_bounds__(kBlock) k_accumulate_il_part(const float* __restrict__ g, float* __restrict__ u,
+                                                               float* __restrict__ v, int64_t d, float rho, int rem) {
+  constexpr int CW = 64 / G;
+  constexpr int PP = 4 * G;
+  constexpr int U = G >= 4 ? 8 : 4;
+  const int lane = threadIdx.x & 63;
+  if (lane >= CW * G) return;  // G no power of two: idle lanes (no barrier below)
+  const int h = lane % G;
+  const int64_t sub = lane / G;
+  const int nw = h == G - 1 ? rem : 4;  // workers of this lane's group
+  const int64_t nch = d / CW;
+  const int64_t wstride = (int64_t)gridDim.x * (kBlock / 64);
+  const int64_t ngr = nch / U;
+  const int64_t w0 = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  auto load1 = [](const float* q) { return G > 4 ? *q : __builtin_nontemporal_load(q); };
+  auto load_g = [&](int64_t i) {
+    const float* gq = g + (int64_t)(4 * h) * d + i;
+    f4 x;
+    x.x = load1(gq);
+    x.y = nw > 1 ? load1(gq + d) : 0.f;
+    x.z = nw > 2 ? load1(gq + 2 * d) : 0.f;
+    x.w = nw > 3 ? load1(gq + 3 * d) : 0.f;
+    return x;
+  };
+  auto update = [&](f4 gg, f4& uu, f4& ww) {  // the group's workers; the padding keeps its bits
+    const f4 un = rho * uu + gg;
+    const f4 wn = ww + un;
+    uu.x = un.x;
+    ww.x = wn.x;
+    if (nw > 1) uu.y = un.y, ww.y = wn.y;
+    if (nw > 2) uu.z = un.z, ww.z = wn.z;
+    if (nw > 3) uu.w = un.w, ww.w = wn.w;
+  };
+  for (int64_t gr = w0; gr < ngr; gr += wstride) {
+    f4 gg[U], uu[U], ww[U];
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      const int64_t i = (gr * U + m) * CW + sub;
+      gg[m] = load_g(i);
+      uu[m] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(u + i * PP) + h);
+      ww[m] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(v + i * PP) + h);
+    }
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      const int64_t i = (gr * U + m) * CW + sub;
+      update(gg[m], uu[m], ww[m]);
+      __builtin_nontemporal_store(uu[m], reinterpret_cast<f4*>(u + i * PP) + h);
+      __builtin_nontemporal_store(ww[m], reinterpret_cast<f4*>(v + i * PP) + h);
+    }
+  }
+  // the chunks past the last group, the ragged last one included (lanes past d take nothing)
+  for (int64_t i = (ngr * U + w0) * CW + sub; i < d; i += wstride * CW) {
+    f4* up = reinterpret_cast<f4*>(u + i * PP) + h;
+    f4* vp = reinterpret_cast<f4*>(v + i * PP) + h;
+    f4 uu = *up, ww = *vp;
+    update(load_g(i), uu, ww);
+    *up = uu;
+    *vp = ww;
   }
 }
 
@@ -279,6 +354,46 @@ __global__ void __launch_bounds__(kBlock) k_merge64_dyn(const double* __restrict
 // ------------------------------------------------------------------------------------
 // Exact values of the selected coordinates and their reset (Alg. 2, second round).
 
+// Interleaved state: GL lanes (a power of two, at least PP/4) share a coordinate, lane sub
+// holding the row's 16-byte piece of workers 4 sub .. 4 sub + 3. A row is then one coalesced
+// access of v and one of each cleared array; one lane per coordinate walked its row 4 bytes at a
+// time (2M x 32, k = 20,000: 25.8 us, 66M x 16, k = 66,000: 21.9 us). The tree runs in the
+// lane's own four (strides 1, 2), then across lanes (strides 4, 8, ... workers); an element
+// absorbs its partner only if that worker exists, so the sums are those of tree_sum.
+template <int GL>
+__global__ void __launch_bounds__(kBlock) k_gather_reset_il(const int32_t* __restrict__ idx, int64_t k,
+                                                            float* __restrict__ u, float* __restrict__ v,
+                                                            float* __restrict__ values, int P, int PP, int reset_u) {
+  const int sub = threadIdx.x % GL;
+  const int nw = P - 4 * sub;  // workers from this lane's first one on
+  const int64_t stride = (int64_t)gridDim.x * (kBlock / GL);
+  // the shuffles below read lanes of the same coordinate, which leave the loop together
+  for (int64_t t = (int64_t)blockIdx.x * (kBlock / GL) + threadIdx.x / GL; t < k; t += stride) {
+    const int64_t o = (int64_t)idx[t] * PP + 4 * sub;
+    f4 x = {0.f, 0.f, 0.f, 0.f};
+    if (nw > 0) x = *reinterpret_cast<const f4*>(v + o);
+    if (nw > 1) x.x = x.x + x.y;
+    if (nw > 3) x.z = x.z + x.w;
+    float y = nw > 2 ? x.x + x.z : x.x;
+#pragma unroll
+    for (int s = 1; s < GL; s <<= 1) {
+      const float z = __shfl_down(y, s, GL);
+      if (nw > 4 * s) y = y + z;
+    }
+    if (sub == 0) values[t] = y;
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    if (nw >= 4) {
+      *reinterpret_cast<f4*>(v + o) = zero;
+      if (reset_u) *reinterpret_cast<f4*>(u + o) = zero;
+    } else {
+      for (int q = 0; q < nw; ++q) {  // the row's padding is not written
+        v[o + q] = 0.f;
+        if (reset_u) u[o + q] = 0.f;
+      }
+    }
+  }
+}
+
 template <int P>
 __global__ void __launch_bounds__(kBlock) k_gather_reset(const int32_t* __restrict__ idx, int64_t k,
                                                          float* __restrict__ u, float* __restrict__ v,
@@ -337,25 +452,29 @@ namespace {
 hipError_t launch_accumulate_il(const gs_ctx* x, hipStream_t s, const float* g, float* u, float* v) {
   const int P = x->P, PP = x->state_stride;
   int64_t done = 0;
-  if (P % 4 == 0 && P <= 16 && aligned16(u) && aligned16(v)) {
-    const int G = P / 4;
+  if (aligned16(u) && aligned16(v)) {
+    const int G = PP / 4;
     const int64_t cw = 64 / G;
     const int64_t nch = (x->d + cw - 1) / cw;  // the last one may be ragged
     // about four chunks per wave (the most loads in flight measured best on the 25.6M x 8 stream)
     const dim3 grid(grid_for(nch, 4 * (kBlock / 64), 64 * x->num_cus)), block(kBlock);
     const bool ragged = x->d % cw != 0;
-#define GS_ACC_IL(GG)                                                                               \
-  if (ragged)                                                                                       \
-    hipLaunchKernelGGL((k_accumulate_il<GG, true>), grid, block, 0, s, g, u, v, x->d, x->rho);      \
-  else                                                                                              \
-    hipLaunchKernelGGL((k_accumulate_il<GG, false>), grid, block, 0, s, g, u, v, x->d, x->rho)
+    const int rem = P % 4;
     switch (G) {
-      case 1: GS_ACC_IL(1); break;
-      case 2: GS_ACC_IL(2); break;
-      case 3: GS_ACC_IL(3); break;
-      default: GS_ACC_IL(4); break;
-    }
+#define GS_ACC_IL(GG)                                                                                          \
+  case GG:                                                                                                     \
+    if (rem)                                                                                                   \
+      hipLaunchKernelGGL(k_accumulate_il_part<GG>, grid, block, 0, s, g, u, v, x->d, x->rho, rem);             \
+    else if (ragged)                                                                                           \
+      hipLaunchKernelGGL((k_accumulate_il<GG, true>), grid, block, 0, s, g, u, v, x->d, x->rho);               \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_accumulate_il<GG, false>), grid, block, 0, s, g, u, v, x->d, x->rho);              \
+    break;
+      GS_ACC_IL(1) GS_ACC_IL(2) GS_ACC_IL(3) GS_ACC_IL(4) GS_ACC_IL(5) GS_ACC_IL(6) GS_ACC_IL(7) GS_ACC_IL(8)
+      GS_ACC_IL(9) GS_ACC_IL(10) GS_ACC_IL(11) GS_ACC_IL(12) GS_ACC_IL(13) GS_ACC_IL(14) GS_ACC_IL(15)
+      GS_ACC_IL(16)
 #undef GS_ACC_IL
+    }
     done = x->d;
   }
   if (done < x->d) {
@@ -447,6 +566,20 @@ hipError_t launch_gather_reset(const gs_ctx* x, hipStream_t s, const int32_t* id
   const dim3 grid(grid_for(k, kBlock, 4 * x->num_cus)), block(kBlock);
   const int ru = x->reset_momentum ? 1 : 0;
   const StateView sv = state_view(x);
+  if (x->state_layout == GS_STATE_INTERLEAVED && aligned16(u) && aligned16(v)) {
+    const int G = x->state_stride / 4;
+    const int gl = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : G <= 8 ? 8 : 16;
+    const dim3 gi(grid_for(k, kBlock / gl, 8 * x->num_cus));
+    switch (gl) {
+#define GS_GATHER_IL(GL)                                                                                      \
+  case GL:                                                                                                    \
+    hipLaunchKernelGGL(k_gather_reset_il<GL>, gi, block, 0, s, idx, k, u, v, values, x->P, x->state_stride, ru); \
+    break;
+      GS_GATHER_IL(1) GS_GATHER_IL(2) GS_GATHER_IL(4) GS_GATHER_IL(8) GS_GATHER_IL(16)
+#undef GS_GATHER_IL
+    }
+    return hipGetLastError();
+  }
   switch (x->P) {
 #define GS_GATHER_CASE(PP) \
   case PP: hipLaunchKernelGGL(k_gather_reset<PP>, grid, block, 0, s, idx, k, u, v, values, sv, ru); break;
