@@ -103,7 +103,7 @@ def log(msg):
 
 CSRC = os.path.join(ROOT, "paper_2108_06004_amd", "csrc")
 # launch configuration and shared device helpers: a change there can change any kernel
-SHARED_SOURCES = ("gs_api.hip", "gs_internal.hpp", "gs_device.hpp")
+SHARED_SOURCES = ("gs_api.hip", "gs_internal.hpp", "gs_device.hpp", "gs_select.hpp")
 
 
 def file_sha256(path: str) -> str:
@@ -118,6 +118,11 @@ def kernel_source_file(name: str):
         if re.search(r"__global__[^;{]*\b" + re.escape(base) + r"\s*\(", open(p).read()):
             return os.path.basename(p)
     return None
+
+
+def state_stride(P: int) -> int:
+    """Row length of the interleaved state."""
+    return (P + 3) // 4 * 4
 
 
 def num_cus() -> int:
@@ -143,26 +148,28 @@ def stage_kernels(w, layout: str = "interleaved", plan: dict = None) -> dict:
         acc = ["k_accumulate4"]
     else:
         acc = [f"k_vi_il<{w.P}, true>"]
-    tail = ["k_digit2", "k_select2", "k_mark", "k_emit"]
+    tail = ["k_digit2", "k_emit"]  # the emit also gathers the exact values and resets
     # the full estimate's form: two coordinates per thread per pass up to 8 * 256 * (CUs)
     unsketch = f"k_unsketch<{w.r}, {2 if w.d <= 8 * 256 * num_cus() else 1}>"
     if w.d * w.r > 2_000_000:  # pruned selection (the library's choice above 2,000,000 cells of d*r)
-        select = [f"k_sample<{w.r}, false>", "k_heavy", f"k_pruned<{w.r}, false, 0>", f"k_survivors<{w.r}, false>",
-                  unsketch] + tail
+        rows = w.r * -(-w.c // 64) * 64  # bits of the heavy-cell map
+        fine = 160 * 1024 - 256 - rows // 8 >= 4 * 512
+        select = [f"k_sample<{w.r}, false>", "k_heavy"] + ([] if fine else ["k_coarse"]) + \
+            [f"k_pruned<{w.r}, false, {0 if fine else 1}>"] + tail
     else:  # every coordinate estimated
         select = [unsketch] + tail
     segmented = plan["segments"] > 1 if plan is not None else w.d <= 1_000_000
     return {
         "accumulate": acc,
         # packed lists (the library's choice here); one worker in the worker-major layout: its
-        # plain state vector gathered directly (the last template argument)
+        # plain state vector gathered directly (the fourth template argument)
         "sketch": [f"k_pull<{w.P}, {4 if w.P <= 4 else 6}, true, "
-                   f"{'true' if w.P == 1 and layout == 'worker_major' else 'false'}>"],
+                   f"{'true' if w.P == 1 and layout == 'worker_major' else 'false'}, {state_stride(w.P)}>"],
         # the tiles merge their own cells; small sketches' tiles, split into list segments,
         # are summed here
         "merge": [f"k_merge_partials<{w.P}>"] if segmented else [],
         "select": select,
-        "gather_reset": [f"k_gather_reset<{w.P}>"],
+        "gather_reset": [],  # in the selection's k_emit
     }
 
 

@@ -37,7 +37,7 @@ hipError_t alloc(T** p, int64_t count) {
 
 void free_scratch(gs_ctx* x) {
   void* ptrs[] = {x->keys,     x->hist,     x->hist2,       x->hist_s, x->hist_c, x->ctl,     x->stage_idx,
-                  x->cand_key, x->cand_idx, x->bitmap,      x->emit_flags, x->acc64, x->list,  x->codes,
+                  x->cand_key, x->cand_idx, x->bitmap,      x->counts, x->stage2, x->acc64, x->list,  x->codes,
                   x->bases,    x->tile_off, x->tile_n,      x->vI,     x->partial, x->sample_keys,
                   x->heavy,    x->l2buf,    x->coarse};
   for (void* p : ptrs)
@@ -52,7 +52,8 @@ void free_scratch(gs_ctx* x) {
   x->cand_key = nullptr;
   x->cand_idx = nullptr;
   x->bitmap = nullptr;
-  x->emit_flags = nullptr;
+  x->counts = nullptr;
+  x->stage2 = nullptr;
   x->acc64 = nullptr;
   x->list = nullptr;
   x->codes = nullptr;
@@ -181,7 +182,7 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
   }
 
   x->cand_cap = x->d;
-  x->emit_blocks = gs::emit_blocks_for(x->d);
+  const int64_t range = gs::emit_range(x->d, x->num_cus), ranges = (x->d + range - 1) / range;
   const int64_t words = (x->d + 31) / 32;
   hipError_t ea = hipSuccess;
   auto chk = [&](hipError_t r) {
@@ -197,7 +198,8 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
   chk(alloc(&x->cand_key, x->cand_cap));
   chk(alloc(&x->cand_idx, x->cand_cap));
   chk(alloc(&x->bitmap, words));
-  chk(alloc(&x->emit_flags, x->emit_blocks));
+  chk(alloc(&x->counts, ranges));
+  chk(alloc(&x->stage2, 2 * gs::kStage2Cap));
   chk(alloc(&x->sample_keys, gs::kSampleMax));
   x->heavy_row = (x->c + 63) / 64 * 64;
   chk(alloc(&x->heavy, (int64_t)x->r * x->heavy_row / 32));
@@ -219,10 +221,6 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
     const char* sel = std::getenv("GS_SELECT_PATH");
     if (sel && std::strcmp(sel, "pruned") == 0) x->prune_min_cells = 0;
     if (sel && std::strcmp(sel, "full") == 0) x->prune_min_cells = INT64_MAX;
-    // GS_EMIT_SPIN=n bounds the emit's look-back polls (0: count directly as soon as a
-    // predecessor has not published; negative: always count directly), for tests
-    const char* spin = std::getenv("GS_EMIT_SPIN");
-    if (spin) x->emit_spin = std::atoi(spin);
   }
   if (x->use_pull) {
     x->list_cap = (int64_t)x->r * x->d + (int64_t)gs::kListGroup * x->plan.T;
@@ -244,10 +242,12 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
   if (ea == hipSuccess) ea = hipMemset(x->hist2, 0, gs::kDigitBins * sizeof(uint32_t));
   if (ea == hipSuccess) ea = hipMemset(x->hist_s, 0, gs::kDigit1Bins * sizeof(uint32_t));
   if (ea == hipSuccess) ea = hipMemset(x->hist_c, 0, gs::kDigit1Bins * sizeof(uint32_t));
+  if (ea == hipSuccess) ea = hipMemset(x->counts, 0, ranges * sizeof(uint32_t));
   if (ea == hipSuccess) ea = hipMemset(x->ctl, 0, sizeof(gs::SelectCtl));
   if (ea == hipSuccess) ea = hipDeviceSynchronize();
   if (ea == hipSuccess && x->use_pull) ea = gs::build_pull_lists(x);
   if (ea == hipSuccess) ea = gs::prepare_prune(x);
+  if (ea == hipSuccess) ea = gs::prepare_emit();
   if (ea != hipSuccess) {
     const bool oom = ea == hipErrorOutOfMemory || ea == hipErrorMemoryAllocation;
     gs::set_free_error((std::string("device scratch allocation failed: ") + hipGetErrorString(ea)).c_str());
@@ -330,7 +330,8 @@ gs_status gs_unsketch_topk(gs_ctx* x, void* stream, const float* merged, int64_t
   x->last_error.clear();
   if (!merged || !idx) return fail(x, GS_ERR_INVALID_ARG, "gs_unsketch_topk: NULL array");
   if (k < 1 || k > x->k_max) return fail(x, GS_ERR_INVALID_ARG, "gs_unsketch_topk: k must satisfy 1 <= k <= k_max");
-  return device_status(x, gs::launch_unsketch_topk(x, as_stream(stream), merged, k, est, idx), "gs_unsketch_topk");
+  return device_status(x, gs::launch_unsketch_topk(x, as_stream(stream), merged, k, est, idx, nullptr),
+                       "gs_unsketch_topk");
 }
 
 gs_status gs_gather_reset(gs_ctx* x, void* stream, const int32_t* idx, int64_t k, float* u, float* v,
@@ -339,7 +340,9 @@ gs_status gs_gather_reset(gs_ctx* x, void* stream, const int32_t* idx, int64_t k
   x->last_error.clear();
   if (!idx || !u || !v || !values) return fail(x, GS_ERR_INVALID_ARG, "gs_gather_reset: NULL array");
   if (k < 1 || k > x->k_max) return fail(x, GS_ERR_INVALID_ARG, "gs_gather_reset: k must satisfy 1 <= k <= k_max");
-  return device_status(x, gs::launch_gather_reset(x, as_stream(stream), idx, k, u, v, values), "gs_gather_reset");
+  return device_status(x, gs::launch_gather(x->num_cus, as_stream(stream), x->hs, nullptr, idx, k,
+                                            gs::gather_args(x, u, v, values)),
+                       "gs_gather_reset");
 }
 
 }  // extern "C"
@@ -394,9 +397,9 @@ gs_status gs_step(gs_ctx* x, void* stream, const float* g, float* u, float* v, i
   if (unaligned_without_copy(x, v)) return fail(x, GS_ERR_INVALID_ARG, std::string("gs_step") + kUnalignedMsg);
   hipStream_t s = as_stream(stream);
   hipError_t e = launch_sketch_phase(x, s, g, u, v, merged);
-  if (e == hipSuccess) e = gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx);
+  const gs::GatherArgs ga = gs::gather_args(x, u, v, values);
+  if (e == hipSuccess) e = gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx, &ga);
   gs::stage_mark(x, s, 4);
-  if (e == hipSuccess) e = gs::launch_gather_reset(x, s, idx, k, u, v, values);
   gs::stage_mark(x, s, 5);
   return device_status(x, e, "gs_step");
 }
@@ -407,7 +410,7 @@ gs_status gs_heavymix_topk(gs_ctx* x, void* stream, const float* merged, int64_t
   x->last_error.clear();
   if (!merged || !rnd || !idx) return fail(x, GS_ERR_INVALID_ARG, "gs_heavymix_topk: NULL array");
   if (k < 1 || k > x->k_max) return fail(x, GS_ERR_INVALID_ARG, "gs_heavymix_topk: k must satisfy 1 <= k <= k_max");
-  return device_status(x, gs::launch_heavymix_topk(x, as_stream(stream), merged, k, rnd, est, idx, n_heavy, l2sq),
+  return device_status(x, gs::launch_heavymix_topk(x, as_stream(stream), merged, k, rnd, est, idx, n_heavy, l2sq, nullptr),
                        "gs_heavymix_topk");
 }
 
@@ -422,9 +425,9 @@ gs_status gs_step_heavymix(gs_ctx* x, void* stream, const float* g, float* u, fl
     return fail(x, GS_ERR_INVALID_ARG, std::string("gs_step_heavymix") + kUnalignedMsg);
   hipStream_t s = as_stream(stream);
   hipError_t e = launch_sketch_phase(x, s, g, u, v, merged);
-  if (e == hipSuccess) e = gs::launch_heavymix_topk(x, s, merged, k, rnd, nullptr, idx, n_heavy, nullptr);
+  const gs::GatherArgs ga = gs::gather_args(x, u, v, values);
+  if (e == hipSuccess) e = gs::launch_heavymix_topk(x, s, merged, k, rnd, nullptr, idx, n_heavy, nullptr, &ga);
   gs::stage_mark(x, s, 4);
-  if (e == hipSuccess) e = gs::launch_gather_reset(x, s, idx, k, u, v, values);
   gs::stage_mark(x, s, 5);
   return device_status(x, e, "gs_step_heavymix");
 }
@@ -545,9 +548,9 @@ gs_status gs_step_profiled(gs_ctx* x, void* stream, const float* g, float* u, fl
     if (erec == hipSuccess) erec = hipEventRecord(ev[t], s);
   };
   if (e == hipSuccess) e = launch_sketch_phase(x, s, g, u, v, merged, mark);
-  if (e == hipSuccess) e = gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx);
+  const gs::GatherArgs ga = gs::gather_args(x, u, v, values);
+  if (e == hipSuccess) e = gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx, &ga);
   mark(4);
-  if (e == hipSuccess) e = gs::launch_gather_reset(x, s, idx, k, u, v, values);
   mark(5);
   if (e == hipSuccess) e = erec;
   if (e == hipSuccess) e = hipEventSynchronize(ev[5]);

@@ -9,49 +9,69 @@
 #include "../../include/gs.h"
 #include "gs_device.hpp"
 
-// Top-k selection works on 32-bit keys (the bits of |estimate|) in three radix digits.
 namespace gs {
+// Where element (worker q, coordinate i) of a per-worker array lives: q*qs + i*is.
+// [P][d] (worker-major) is {d, 1}; the interleaved state [d][PP] is {1, PP}.
+struct StateView {
+  int64_t qs, is;
+  __host__ __device__ int64_t at(int q, int64_t i) const { return (int64_t)q * qs + i * is; }
+};
+
+// Top-k selection works on 32-bit keys (the bits of |estimate|) in three radix digits.
 constexpr int kDigit1Shift = 20;  // digit 1: key bits 31..20 (12 bits; |est| keys leave bit 31 clear,
 constexpr int kDigit1Bins = 4096; // HEAVYMIX keys use it to rank the heavy set above the fill)
 constexpr int kDigitBins = 1024;  // digits 2 and 3: key bits 19..10 and 9..0
 
 // Device-resident control block of the selection (one per context).
 struct SelectCtl {
-  uint32_t k;           // number to select
-  uint32_t b1;          // digit-1 bucket holding the k-th key
-  uint32_t above1;      // keys in digit-1 buckets above b1
   uint32_t n_cand;      // candidates appended by the pruned pass (dense candidates: d)
-  uint32_t tau;         // the k-th largest key
-  uint32_t iota;        // largest index taken among keys equal to tau
-  uint32_t tau0;        // pruning bound: a key no larger than the k-th key (when no fallback)
-  uint32_t fallback;    // 1: fewer than k coordinates reach tau0, run the unpruned selection
-  uint32_t n_surv;      // coordinates queued by the pruned pass for an exact estimate
+  uint32_t tau0;        // pruning bound: a key no larger than the k-th key (else fewer than k candidates)
+  // the bin of the k-th key at each digit pass: keys taken from it, its first and last key, and the
+  // keys staged from it (zero between calls)
+  uint32_t need[2], lo[2], hi[2], n_stage[2];
+  uint32_t emit_ticket; // order in which the emit's workgroups end; zero between calls
   double l2sq;          // HEAVYMIX: l2-norm-squared estimate (median of the pairwise row sums)
   double theta;         // HEAVYMIX: heavy threshold l2sq / k
   unsigned long long n_heavy;  // HEAVYMIX: |H|
-  uint32_t n_stage2;    // keys of the digit-1 bucket b1 staged for the digit-3 pass
-  uint32_t n_staged;    // n_stage2 as k_select2 found it, for the emit (n_stage2 is reset there)
-  uint32_t emit_ticket; // order in which the emit's workgroups start (their look-back order)
 };
-// Buffers of the dense selection (every coordinate a candidate) and of its radix tail: the
-// context's scratch for gs_unsketch_topk and friends, or the static scratch of
-// gs_unsketch_topk_static. hist, hist2, hist_c and ctl->n_stage2 are zero between calls.
+// What to do with the coordinates a selection has chosen (gather_entry in gs_select.hpp).
+struct GatherArgs {
+  int op;  // kGatherNone, ...
+  int gl, P, PP, reset_u;
+  float* u;
+  float* v;
+  float* values;
+  StateView sv;
+  // sketch-space state: values are estimates of E, and the touched cells' accumulators are cleared
+  double* acc;
+  uint32_t* claim;
+};
+constexpr int kGatherNone = 0, kGatherRows = 1, kGatherWorkers = 2, kGatherSketch = 3;
+
+// Buffers of the selection's tail: the context's scratch for gs_unsketch_topk and friends, or the
+// static scratch of gs_unsketch_topk_static. hist, hist2, hist_c, counts, ctl->n_stage and
+// ctl->emit_ticket are zero between calls.
 struct SelectBufs {
-  uint32_t* cand_key;   // [cand_cap] candidate keys (dense: key of coordinate t at t)
-  int32_t* cand_idx;    // [cand_cap] candidate coordinates (read only for pruned candidates)
-  int64_t cand_cap;
-  uint32_t* keys;       // [d] staged keys of the digit-1 bucket of the k-th key
+  uint32_t* cand_key;   // [d] candidate keys (dense: key of coordinate t at t)
+  int32_t* cand_idx;    // [d] candidate coordinates (not used for dense candidates)
+  uint32_t* keys;       // [d] staged keys of the k-th key's bin (every key, when the pruned pass fell short)
   int32_t* stage_idx;   // [d] their coordinates
+  uint32_t* stage2;     // [2 kStage2Cap] keys, then coordinates, staged by a second digit pass
   uint32_t* hist;       // [kDigit1Bins] digit-1 histogram of the dense keys
-  uint32_t* hist2;      // [kDigitBins]
-  uint32_t* hist_c;     // [kDigit1Bins] digit-1 histogram of pruned candidates
+  uint32_t* hist2;      // [kDigitBins] digit-2 histogram of the bin's keys
+  uint32_t* hist_c;     // [kDigit1Bins] histogram of pruned candidates
   SelectCtl* ctl;
-  uint32_t* bitmap;     // [ceil(d/32)] output bitmap
-  unsigned long long* emit_flags;  // [emit_blocks] look-back words of the emit (zero before it)
-  int64_t emit_blocks;
-  int emit_spin;        // polls of the emit's look-back before counting directly (< 0: never look back)
+  uint32_t* bitmap;     // [ceil(d/32)] pruned candidates above the k-th key's bin
+  uint32_t* counts;     // [ranges] keys above the k-th key's bin in each emit workgroup's range
 };
-constexpr int kEmitSpinDefault = 1 << 20;
+constexpr int64_t kStage2Cap = 1 << 16;
+// The emit's workgroups own `range` coordinates each (a multiple of 64): one per CU, at least 4,096
+// coordinates and at most what fits the workgroup's LDS bitmap.
+constexpr int64_t kRangeMax = 1 << 19;
+inline int64_t emit_range(int64_t d, int num_cus) {
+  const int64_t r = ((d + num_cus - 1) / num_cus + 63) / 64 * 64;
+  return r < 4096 ? 4096 : r > kRangeMax ? kRangeMax : r;
+}
 constexpr int kSampleMax = 16384;  // sampled estimates for the pruning bound
 constexpr int64_t kPruneMinCells = 2000000;  // d*r below which the full estimate is faster (measured)
 
@@ -92,12 +112,6 @@ struct PullPlan {
 constexpr int kListGroup = 64;
 constexpr int64_t kMaxFillLds = 160 * 1024;  // LDS of the list-fill kernel holds T cursors
 
-// Where element (worker q, coordinate i) of a per-worker array lives: q*qs + i*is.
-// [P][d] (worker-major) is {d, 1}; the interleaved state [d][PP] is {1, PP}.
-struct StateView {
-  int64_t qs, is;
-  __host__ __device__ int64_t at(int q, int64_t i) const { return (int64_t)q * qs + i * is; }
-};
 constexpr int kTilesPerCu = 1;               // resident pull workgroups per CU (LDS-limited)
 }  // namespace gs
 
@@ -124,7 +138,8 @@ struct gs_ctx {
   int32_t* cand_idx = nullptr;    // [cand_cap]
   int64_t cand_cap = 0;
   uint32_t* bitmap = nullptr;     // [ceil(d/32)]
-  unsigned long long* emit_flags = nullptr;  // [emit blocks] look-back words of the emit
+  uint32_t* stage2 = nullptr;     // [2 kStage2Cap]
+  uint32_t* counts = nullptr;     // [emit ranges] taken keys of each range, zero between calls
   uint32_t* sample_keys = nullptr;  // [kSampleMax]
   uint32_t* heavy = nullptr;        // [r * heavy_row / 32] heavy-cell bitmap, rows padded to heavy_row bits
   int64_t heavy_row = 0;            // c rounded up to a multiple of 64: bit j * heavy_row + col is cell (j, col)
@@ -134,8 +149,6 @@ struct gs_ctx {
   uint32_t* coarse = nullptr;       // coarse heavy-cell map (bit = OR of its cells' heavy bits)
   int64_t prune_coarse_words = 0;
   int prune_buf_cap = 0;            // LDS candidate buffer entries of the pruned pass
-  int64_t emit_blocks = 0;
-  int emit_spin = gs::kEmitSpinDefault;  // diagnostic override: GS_EMIT_SPIN
   // selections without an estimate vector prune when d*r exceeds this (0: always); below it
   // the full estimate takes fewer launches than the pruned pass's chain
   int64_t prune_min_cells = 0;
@@ -171,9 +184,8 @@ inline StateView state_view(const gs_ctx* x) {
 }
 inline StateView worker_major_view(const gs_ctx* x) { return StateView{x->d, 1}; }
 inline SelectBufs select_bufs(const gs_ctx* x) {
-  return SelectBufs{x->cand_key, x->cand_idx, x->cand_cap, x->keys,   x->stage_idx, x->hist,
-                    x->hist2,    x->hist_c,   x->ctl,      x->bitmap, x->emit_flags, x->emit_blocks,
-                    x->emit_spin};
+  return SelectBufs{x->cand_key, x->cand_idx, x->keys, x->stage_idx, x->stage2, x->hist,
+                    x->hist2,    x->hist_c,   x->ctl,  x->bitmap,    x->counts};
 }
 
 constexpr int kStageMarks = 6;  // events per timed step: before stage 0, after stages 0..4
@@ -187,21 +199,32 @@ hipError_t launch_sketch_acc(const gs_ctx* x, hipStream_t s, const float* v, Sta
 hipError_t launch_sketch(const gs_ctx* x, hipStream_t s, const float* v, StateView sv, float* tables);
 hipError_t launch_merge_acc(const gs_ctx* x, hipStream_t s, float* merged);
 hipError_t launch_merge(const gs_ctx* x, hipStream_t s, const float* tables, float* merged);
-hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, float* est, int32_t* idx);
+// With ga (may be null) the selected coordinates are gathered too, in the selection's last
+// kernel or in one of its own.
+hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, float* est, int32_t* idx,
+                                const GatherArgs* ga);
 hipError_t launch_heavymix_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, const uint32_t* rnd,
-                                float* est, int32_t* idx, int64_t* n_heavy, double* l2sq);
+                                float* est, int32_t* idx, int64_t* n_heavy, double* l2sq, const GatherArgs* ga);
+// From the last digit pass's staged keys to the ascending index list (and the gather); `level` is
+// that pass (0 or 1), pruned and hm say what the candidates are.
+hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
+                       const float* merged, int64_t k, int pruned, int level, int32_t* idx, int64_t* n_heavy,
+                       double* l2sq, const GatherArgs* ga);
+hipError_t prepare_emit();
+// The gather alone, over idx[0, k).
+hipError_t launch_gather(int num_cus, hipStream_t s, const HashSet& hs, const float* merged, const int32_t* idx,
+                         int64_t k, const GatherArgs& ga);
+GatherArgs gather_args(const gs_ctx* x, float* u, float* v, float* values);
 int64_t l2_pad(int64_t c);
 hipError_t launch_apply_update(const gs_ctx* x, hipStream_t s, const int32_t* idx, const float* values, int64_t k,
                                float lr, float* w);
 hipError_t launch_sketch_state(gs_ctx* x, hipStream_t s, const float* merged, float* U, float* E, int64_t k,
                                int32_t* idx, float* values);
-hipError_t launch_gather_reset(const gs_ctx* x, hipStream_t s, const int32_t* idx, int64_t k, float* u, float* v,
-                               float* values);
-int64_t emit_blocks_for(int64_t d);
 // The estimate of every coordinate and the top-k over them (the full path of
 // launch_unsketch_topk) on explicit buffers; r = hs.r, 1 <= k <= d.
 hipError_t launch_unsketch_topk_dense(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
-                                      const float* merged, int64_t k, float* est, int32_t* idx);
+                                      const float* merged, int64_t k, float* est, int32_t* idx,
+                                      const GatherArgs* ga);
 // Granlund-Montgomery reciprocal of the bucket modulus c (sets hs.c, hs.magic, hs.shift).
 void set_divisor(HashSet& hs, uint32_t c);
 // Message of the last failing context-free call on this thread (gs_create,

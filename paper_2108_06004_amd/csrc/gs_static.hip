@@ -17,21 +17,23 @@ constexpr int64_t kMaxD = GS_STATIC_MAX_D;
 constexpr int64_t kAlignWords = 64;  // 256-byte alignment of every region
 constexpr int64_t up(int64_t n) { return (n + kAlignWords - 1) / kAlignWords * kAlignWords; }
 constexpr int64_t kCtlWords = up((int64_t)((sizeof(gs::SelectCtl) + 3) / 4));
-constexpr int64_t kFlagWords = 64;  // look-back words of the emit, 2 per emit block: 32 at kMaxD (checked per call)
+constexpr int64_t kCountWords = 1024;  // counts of the emit's ranges: at least 4,096 coordinates each
+static_assert(kMaxD / 4096 <= kCountWords, "emit ranges");
 
 // Layout of the array in 32-bit words.
 constexpr int64_t kCandKey = 0;                            // [kMaxD] key of coordinate t
 constexpr int64_t kStageKey = kCandKey + up(kMaxD);        // [kMaxD] staged keys
 constexpr int64_t kStageIdx = kStageKey + up(kMaxD);       // [kMaxD] their coordinates
-constexpr int64_t kBitmap = kStageIdx + up(kMaxD);         // [kMaxD / 32] output bitmap
-constexpr int64_t kFlags = kBitmap + up((kMaxD + 31) / 32);
+constexpr int64_t kStage2 = kStageIdx + up(kMaxD);         // [2 gs::kStage2Cap]
+constexpr int64_t kBitmap = kStage2 + 2 * gs::kStage2Cap;         // [kMaxD / 32] output bitmap
 // Cleared at the start of every call (the selection needs them zero and leaves them zero,
 // but a call that was never completed, or one overlapping on another stream, may not have).
-constexpr int64_t kZero = kFlags + kFlagWords;
+constexpr int64_t kZero = kBitmap + up((kMaxD + 31) / 32);
 constexpr int64_t kHist = kZero;                           // [kDigit1Bins]
 constexpr int64_t kHist2 = kHist + gs::kDigit1Bins;        // [kDigitBins]
 constexpr int64_t kHistC = kHist2 + gs::kDigitBins;        // [kDigit1Bins] (not read: dense candidates)
-constexpr int64_t kCtl = kHistC + gs::kDigit1Bins;         // SelectCtl
+constexpr int64_t kCounts = kHistC + gs::kDigit1Bins;      // [ranges]
+constexpr int64_t kCtl = kCounts + kCountWords;            // SelectCtl
 constexpr int64_t kZeroWords = kCtl + kCtlWords - kZero;
 constexpr int64_t kWords = kZero + kZeroWords;
 static_assert(kCtl % kAlignWords == 0, "control block alignment");
@@ -67,6 +69,8 @@ hipError_t scratch_of_current_device(uint32_t** ptr, int* num_cus) {
     e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     g_num_cus[dev] = n > 0 ? n : 256;
+    e = gs::prepare_emit();
+    if (e != hipSuccess) return e;
     g_scratch_ptr[dev] = static_cast<uint32_t*>(p);
   }
   *ptr = g_scratch_ptr[dev];
@@ -116,23 +120,20 @@ extern "C" gs_status gs_unsketch_topk_static(const gs_config* cfg, void* stream,
   hipError_t e = scratch_of_current_device(&base, &num_cus);
   if (e != hipSuccess) return device_error("scratch set-up", e);
   const int64_t d = cfg->d;
-  if (2 * gs::emit_blocks_for(d) > kFlagWords) return device_error("scratch layout", hipErrorInvalidValue);
   const gs::SelectBufs bufs{base + kCandKey,
-                            reinterpret_cast<int32_t*>(base + kStageIdx),  // candidates are dense: never read
-                            d,
+                            nullptr,  // candidates are dense: no coordinates
                             base + kStageKey,
                             reinterpret_cast<int32_t*>(base + kStageIdx),
+                            base + kStage2,
                             base + kHist,
                             base + kHist2,
                             base + kHistC,
                             reinterpret_cast<gs::SelectCtl*>(base + kCtl),
                             base + kBitmap,
-                            reinterpret_cast<unsigned long long*>(base + kFlags),
-                            gs::emit_blocks_for(d),
-                            gs::kEmitSpinDefault};
+                            base + kCounts};
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   e = gs::launch_fill_zero(s, reinterpret_cast<float*>(base + kZero), kZeroWords);  // a kernel, not a memset
-  if (e == hipSuccess) e = gs::launch_unsketch_topk_dense(hs, d, num_cus, bufs, s, merged, k, est, idx);
+  if (e == hipSuccess) e = gs::launch_unsketch_topk_dense(hs, d, num_cus, bufs, s, merged, k, est, idx, nullptr);
   if (e != hipSuccess) return device_error("launch", e);
   return GS_OK;
 }

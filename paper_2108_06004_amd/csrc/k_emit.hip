@@ -1,0 +1,352 @@
+// k_emit.hip -- the end of a selection: from the staged keys of the k-th key's bin to the ascending
+// index list and, in the fused steps, the exact values and the reset, in one kernel.
+//
+// Each workgroup owns a range of coordinates and needs nothing from another one: the keys above the
+// bin are known from the digit pass (a bit in the output bitmap and
+// a count per range, whose sum over the ranges before its own is the workgroup's output offset), and
+// every workgroup finds the cut inside the bin by itself, since the bin holds about a hundred keys:
+//   1. A key and its coordinate make one 64-bit word, key first and the lower coordinate larger,
+//      so the words are distinct and the selection is the k largest of them. The bin's words (in
+//      LDS) are cut down by 10-bit histograms until at most 256 are left, and ranked against each
+//      other: the need-th largest is the cut.
+//   2. The range's bitmap words; the bin's words at or above the cut set their bit if they are in the
+//      range and are counted if before it.
+//   3. Bits become indices; the workgroup's own indices are gathered and reset.
+// One kernel instead of four (digit 3 in one workgroup, marking, emission with a look-back,
+// gather), at about 4.6 us each however little they do.
+// When the pruned pass fell short of k candidates, or the bin is crowded (ties: an all-zero
+// sketch), the first workgroup selects alone over the whole candidate list: slow (milliseconds at
+// d in the tens of millions), and right for every input. No workgroup ever waits for another.
+#include "gs_internal.hpp"
+#include "gs_select.hpp"
+
+namespace gs {
+namespace {
+
+constexpr int kBlock = 1024;
+constexpr int kBucketCap = 8192;   // words of the k-th key's bin kept in LDS
+constexpr int kRankCap = 256;      // words ranked against each other
+// Staged keys that every workgroup reads for itself; beyond, the first workgroup selects alone.
+constexpr uint32_t kListMax = (uint32_t)kStage2Cap;
+
+struct EmitArgs {
+  const uint32_t* key;        // [n] candidate keys; dense: key of coordinate t at t
+  const int32_t* idx;         // [n] their coordinates; dense: null
+  const uint32_t* list_key;   // staged keys of the bin
+  const int32_t* list_idx;    // and their coordinates
+  uint32_t* bitmap;
+  uint32_t* counts;
+  SelectCtl* ctl;
+  uint32_t* hist;             // histograms cleared here for the next call
+  uint32_t* hist2;
+  const float* merged;
+  int32_t* out;
+  int64_t* n_heavy;
+  double* l2sq;
+  int64_t d, range;
+  uint32_t k;
+  int pruned, level;
+};
+
+__device__ __forceinline__ uint64_t word_of(uint32_t key, uint32_t ix) {
+  return ((uint64_t)key << 32) | (0xffffffffu - ix);
+}
+
+struct Shared {
+  union {
+    uint64_t bucket[kBucketCap];
+    float rows[kBlock * kMaxRows];  // estimate_any's, where no bucket is held
+  };
+  uint64_t fin[kRankCap];
+  uint32_t h[1024];
+  uint32_t shw[kBlock / 64];
+  uint32_t res[2];
+  uint64_t cut;
+  uint32_t n, before, last;
+};
+
+// The `need`-th largest of the n_in words in [lo, hi] that `each` enumerates: each(f) calls
+// f(in the source?, word) the same number of times in every thread of the block.
+template <class Each>
+__device__ __forceinline__ uint64_t nth_largest(Shared& sh, Each each, uint64_t lo, uint64_t hi, uint32_t need, uint32_t n_in) {
+  while (n_in > (uint32_t)kRankCap) {  // the words are distinct, so the interval is wider than 2^8
+    const int bits = 64 - __clzll((long long)(hi - lo));
+    const int shift = bits > 10 ? bits - 10 : 0;
+    for (int b = threadIdx.x; b < 1024; b += kBlock) sh.h[b] = 0u;
+    __syncthreads();
+    each([&](bool ok, uint64_t w) {
+      const bool in = ok && w >= lo && w <= hi;
+      hist_add(sh.h, in, in ? (uint32_t)((w - lo) >> shift) : 0u);
+    });
+    __syncthreads();
+    find_bucket<kBlock, 1024>(sh.h, true, need, sh.shw, sh.res);
+    const uint64_t b = sh.res[0];
+    n_in = sh.h[b];
+    need -= sh.res[1];
+    lo += b << shift;
+    const uint64_t top = lo + ((1ull << shift) - 1ull);
+    hi = top < hi ? top : hi;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) sh.n = 0u;
+  __syncthreads();
+  each([&](bool ok, uint64_t w) {
+    if (ok && w >= lo && w <= hi) {
+      const uint32_t pos = atomicAdd(&sh.n, 1u);
+      if (pos < (uint32_t)kRankCap) sh.fin[pos] = w;
+    }
+  });
+  __syncthreads();
+  const uint32_t n = min(sh.n, (uint32_t)kRankCap);  // == n_in
+  if (threadIdx.x < n) {
+    const uint64_t w = sh.fin[threadIdx.x];
+    uint32_t rank = 0;
+    for (uint32_t b = 0; b < n; ++b) rank += sh.fin[b] > w ? 1u : 0u;
+    if (rank == need - 1) sh.cut = w;
+  }
+  __syncthreads();
+  return sh.cut;
+}
+
+// f(valid, word) for every entry of a list (idx null: entry t is coordinate t) by one block, in the
+// same number of rounds for every thread.
+template <class F>
+__device__ __forceinline__ void for_list(const uint32_t* __restrict__ key, const int32_t* __restrict__ idx, int64_t n,
+                                         F f) {
+  constexpr int U = 4;
+  for (int64_t t0 = 0; t0 < n; t0 += (int64_t)U * kBlock) {
+    uint32_t kk[U], ii[U];
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      const int64_t t = t0 + (int64_t)m * kBlock + threadIdx.x;
+      kk[m] = t < n ? key[t] : 0u;
+      ii[m] = t < n && idx ? (uint32_t)idx[t] : (uint32_t)t;
+    }
+#pragma unroll
+    for (int m = 0; m < U; ++m) f(t0 + (int64_t)m * kBlock + threadIdx.x < n, word_of(kk[m], ii[m]));
+  }
+}
+
+// Entries idx[t0], idx[t0 + step], ... below n, a lane group of ga.gl threads each.
+__device__ __forceinline__ void gather_range(const GatherArgs& ga, const HashSet& hs, const float* __restrict__ merged,
+                                             const int32_t* __restrict__ idx, int64_t t0, int64_t step, int64_t n,
+                                             float* rows) {
+  const int sub = (int)(threadIdx.x & (unsigned)(ga.gl - 1));
+  for (int64_t t = t0; t < n; t += step) {
+    const int32_t i = idx[t];
+    if (ga.op != kGatherSketch) {
+      gather_entry(ga, i, t, sub);
+      continue;
+    }
+    ga.values[t] = estimate_any(hs, merged, (uint32_t)i, rows + threadIdx.x * kMaxRows);
+#pragma nounroll
+    for (int j = 0; j < hs.r; ++j) {
+      uint32_t col, sflip;
+      hash_ij(hs, j, (uint32_t)i, col, sflip);
+      const int64_t cell = (int64_t)j * hs.c + col;
+      ga.acc[cell] = 0.0;
+      atomicAnd(&ga.claim[cell >> 5], ~(1u << (cell & 31)));
+    }
+  }
+}
+
+// Entries [p0, p0 + n) of the index list, written by this block.
+__device__ __forceinline__ void gather_own(const EmitArgs& a, const HashSet& hs, const GatherArgs& ga, Shared& sh,
+                                           int64_t p0, uint32_t n) {
+  if (ga.op == kGatherNone) return;
+  __syncthreads();
+  gather_range(ga, hs, a.merged, a.out, p0 + threadIdx.x / (unsigned)ga.gl, kBlock / (unsigned)ga.gl, p0 + n,
+               sh.rows);
+}
+
+constexpr int kGatherBlock = 256;
+__global__ void __launch_bounds__(kGatherBlock) k_gather_reset(const int32_t* __restrict__ idx, int64_t k, HashSet hs,
+                                                               const float* __restrict__ merged, GatherArgs ga) {
+  __shared__ float rows[kGatherBlock * kMaxRows];  // sketch-space values only
+  const int64_t per = kGatherBlock / (unsigned)ga.gl;
+  gather_range(ga, hs, merged, idx, (int64_t)blockIdx.x * per + threadIdx.x / (unsigned)ga.gl,
+               (int64_t)gridDim.x * per, k, rows);
+}
+
+// The whole selection by one block over a list of n entries (idx null: dense).
+__device__ __forceinline__ void select_alone(const EmitArgs& a, const HashSet& hs, const GatherArgs& ga, Shared& sh,
+                                             const uint32_t* key, const int32_t* idx, int64_t n) {
+  const int64_t words = (a.d + 31) / 32;
+  for (int64_t w = threadIdx.x; w < words; w += kBlock) a.bitmap[w] = 0u;
+  const uint64_t cut =
+      nth_largest(sh, [&](auto f) { for_list(key, idx, n, f); }, 0ull, ~0ull, a.k, (uint32_t)n);  // n <= d < 2^31
+  __threadfence();
+  __syncthreads();
+  for_list(key, idx, n, [&](bool ok, uint64_t w) {
+    const uint32_t ix = 0xffffffffu - (uint32_t)w;
+    if (ok && w >= cut) atomicOr(&a.bitmap[ix >> 5], 1u << (ix & 31u));
+  });
+  __threadfence();
+  __syncthreads();
+  uint32_t base = 0;
+  for (int64_t w0 = 0; w0 < words; w0 += kBlock) {  // block-uniform
+    const int64_t w = w0 + threadIdx.x;
+    uint32_t x = w < words ? __hip_atomic_load(&a.bitmap[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    uint32_t total;
+    uint32_t pos = base + block_scan_incl<kBlock>((uint32_t)__popc(x), sh.shw, total) - (uint32_t)__popc(x);
+    while (x) {
+      const int bit = __ffs(x) - 1;
+      if (pos < a.k) a.out[pos] = (int32_t)(32 * w + bit);
+      ++pos;
+      x &= x - 1u;
+    }
+    base += total;
+  }
+  gather_own(a, hs, ga, sh, 0, a.k);
+}
+
+__global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherArgs ga) {
+  extern __shared__ uint32_t bits[];  // [range / 32]
+  __shared__ Shared sh;
+  const int64_t lo = (int64_t)blockIdx.x * a.range, hi = min(a.d, lo + a.range);
+  const uint32_t n_cand = a.pruned ? a.ctl->n_cand : (uint32_t)a.d;
+  const uint32_t nb = a.ctl->n_stage[a.level];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (a.n_heavy) *a.n_heavy = (int64_t)a.ctl->n_heavy;
+    if (a.l2sq) *a.l2sq = a.ctl->l2sq;
+  }
+  const bool few = n_cand < a.k;  // the bound admitted too little: the digit pass left every key in list_key
+  if (few || nb > kListMax) {
+    if (blockIdx.x == 0) {
+      if (few)
+        select_alone(a, hs, ga, sh, a.list_key, nullptr, a.d);
+      else
+        select_alone(a, hs, ga, sh, a.key, a.idx, n_cand);
+    }
+  } else {
+    const uint32_t need = a.ctl->need[a.level];
+    const uint64_t wlo = (uint64_t)a.ctl->lo[a.level] << 32, whi = ((uint64_t)a.ctl->hi[a.level] << 32) | 0xffffffffull;
+    const uint32_t l32 = (uint32_t)lo, width = (uint32_t)(hi - lo);
+    const int nw = (int)(a.range / 32);
+    uint32_t before = 0;
+    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kBlock) before += a.counts[t];
+    const int64_t words = (a.d + 31) / 32, word0 = lo / 32;
+    for (int w = threadIdx.x; w < nw; w += kBlock) bits[w] = word0 + w < words ? a.bitmap[word0 + w] : 0u;
+    if (threadIdx.x == 0) sh.before = 0u;
+    const bool kept = nb <= (uint32_t)kBucketCap;
+    if (kept)
+      for (uint32_t t = threadIdx.x; t < nb; t += kBlock) sh.bucket[t] = word_of(a.list_key[t], (uint32_t)a.list_idx[t]);
+    __syncthreads();
+    auto each = [&](auto f) {
+      if (kept) {
+        for (uint32_t t0 = 0; t0 < nb; t0 += kBlock) {
+          const uint32_t t = t0 + threadIdx.x;
+          f(t < nb, t < nb ? sh.bucket[t] : 0ull);
+        }
+      } else {
+        for_list(a.list_key, a.list_idx, nb, f);
+      }
+    };
+    const uint64_t cut = nth_largest(sh, each, wlo, whi, need, nb);
+    each([&](bool ok, uint64_t w) {
+      const uint32_t ix = 0xffffffffu - (uint32_t)w;
+      if (ok && w >= cut) {
+        if (ix < l32)
+          ++before;
+        else if (ix - l32 < width)
+          atomicOr(&bits[(ix - l32) >> 5], 1u << ((ix - l32) & 31u));
+      }
+    });
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    if ((threadIdx.x & 63) == 0 && before) atomicAdd(&sh.before, before);
+    __syncthreads();
+    const int per = (nw + kBlock - 1) / kBlock, w0 = threadIdx.x * per;
+    uint32_t cnt = 0;
+    for (int m = 0; m < per; ++m)
+      if (w0 + m < nw) cnt += (uint32_t)__popc(bits[w0 + m]);
+    uint32_t total;
+    const uint32_t p0 = sh.before;
+    uint32_t pos = p0 + block_scan_incl<kBlock>(cnt, sh.shw, total) - cnt;
+    for (int m = 0; m < per; ++m) {
+      uint32_t x = w0 + m < nw ? bits[w0 + m] : 0u;
+      while (x) {
+        const int bit = __ffs(x) - 1;
+        if (pos < a.k) a.out[pos] = (int32_t)(lo + 32 * (w0 + m) + bit);
+        ++pos;
+        x &= x - 1u;
+      }
+    }
+    gather_own(a, hs, ga, sh, p0, total);
+  }
+  // the last workgroup to get here clears what the next call needs zero
+  __syncthreads();
+  if (threadIdx.x == 0) sh.last = atomicAdd(&a.ctl->emit_ticket, 1u) == gridDim.x - 1 ? 1u : 0u;
+  __syncthreads();
+  if (!sh.last) return;
+  for (int b = threadIdx.x; b < kDigit1Bins; b += kBlock) a.hist[b] = 0u;
+  for (int b = threadIdx.x; b < kDigitBins; b += kBlock) a.hist2[b] = 0u;
+  for (unsigned b = threadIdx.x; b < gridDim.x; b += kBlock) a.counts[b] = 0u;
+  if (threadIdx.x == 0) {
+    a.ctl->n_stage[0] = a.ctl->n_stage[1] = 0u;
+    a.ctl->emit_ticket = 0u;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
+                       const float* merged, int64_t k, int pruned, int level, int32_t* idx, int64_t* n_heavy,
+                       double* l2sq, const GatherArgs* ga) {
+  EmitArgs a{};
+  a.range = emit_range(d, num_cus);
+  a.key = b.cand_key;
+  a.idx = pruned ? b.cand_idx : nullptr;
+  a.list_key = level ? b.stage2 : b.keys;
+  a.list_idx = level ? reinterpret_cast<const int32_t*>(b.stage2 + kStage2Cap) : b.stage_idx;
+  a.bitmap = b.bitmap;
+  a.counts = b.counts;
+  a.ctl = b.ctl;
+  a.hist = pruned ? b.hist_c : b.hist;
+  a.hist2 = b.hist2;
+  a.merged = merged;
+  a.out = idx;
+  a.n_heavy = n_heavy;
+  a.l2sq = l2sq;
+  a.d = d;
+  a.k = (uint32_t)k;
+  a.pruned = pruned;
+  a.level = level;
+  const unsigned blocks = (unsigned)((d + a.range - 1) / a.range);
+  hipLaunchKernelGGL(k_emit, dim3(blocks), dim3(kBlock), (size_t)(a.range / 32) * sizeof(uint32_t), s, a, hs,
+                     ga ? *ga : GatherArgs{});
+  return hipGetLastError();
+}
+
+hipError_t prepare_emit() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_emit), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kRangeMax / 8);
+}
+
+hipError_t launch_gather(int num_cus, hipStream_t s, const HashSet& hs, const float* merged, const int32_t* idx,
+                         int64_t k, const GatherArgs& ga) {
+  const int64_t per = kGatherBlock / ga.gl;
+  int64_t blocks = (k + per - 1) / per;
+  if (blocks > 8 * num_cus) blocks = 8 * num_cus;
+  hipLaunchKernelGGL(k_gather_reset, dim3((unsigned)blocks), dim3(kGatherBlock), 0, s, idx, k, hs, merged, ga);
+  return hipGetLastError();
+}
+
+GatherArgs gather_args(const gs_ctx* x, float* u, float* v, float* values) {
+  GatherArgs a{};
+  const bool rows = x->state_layout == GS_STATE_INTERLEAVED && ((((uintptr_t)u | (uintptr_t)v) & 15u) == 0);
+  a.op = rows ? kGatherRows : kGatherWorkers;
+  const int lanes = rows ? x->state_stride / 4 : x->P;  // at most 16 or 64
+  a.gl = 1;
+  while (a.gl < lanes) a.gl *= 2;
+  a.P = x->P;
+  a.PP = x->state_stride;
+  a.reset_u = x->reset_momentum ? 1 : 0;
+  a.u = u;
+  a.v = v;
+  a.values = values;
+  a.sv = state_view(x);
+  return a;
+}
+
+}  // namespace gs

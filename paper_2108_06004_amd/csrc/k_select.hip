@@ -26,14 +26,13 @@
 #include <type_traits>
 
 #include "gs_internal.hpp"
+#include "gs_select.hpp"
 
 namespace gs {
 namespace {
 
 constexpr int kBlock = 256;
 constexpr int kSelBlock = 1024;
-constexpr int kEmitWordsPerThread = 4;
-constexpr int kEmitWordsPerBlock = kSelBlock * kEmitWordsPerThread;
 
 int grid_for(int64_t work_items, int per_block, int cap) {
   int64_t b = (work_items + per_block - 1) / per_block;
@@ -42,95 +41,10 @@ int grid_for(int64_t work_items, int per_block, int cap) {
   return (int)b;
 }
 
-// Inclusive prefix sum of x over the threads of a block of BS threads (BS a multiple of 64,
-// at most 64 waves). sh must hold BS/64 words. All threads must call it.
-template <int BS>
-__device__ uint32_t block_scan_incl(uint32_t x, uint32_t* sh, uint32_t& total) {
-  constexpr int kWaves = BS / 64;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) sh[wid] = x;
-  __syncthreads();
-  if (wid == 0) {
-    uint32_t w = lane < kWaves ? sh[lane] : 0u;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(w, o, 64);
-      if (lane >= o) w += y;
-    }
-    if (lane < kWaves) sh[lane] = w;
-  }
-  __syncthreads();
-  total = sh[kWaves - 1];
-  const uint32_t add = wid ? sh[wid - 1] : 0u;
-  __syncthreads();
-  return x + add;
-}
-
-// Scan the histogram h[NB] (LDS or global; NB a multiple of BS, at most 16 bins per
-// thread) in descending or ascending bin order and find the first bin at which the running
-// count reaches `need` (1 <= need <= total). res[0] = that bin, res[1] = count in the bins
-// before it (in scan order). Each thread reads its bins once. All threads must call it.
-template <int BS, int NB>
-__device__ void find_bucket(const uint32_t* h, bool descending, uint32_t need, uint32_t* shw, uint32_t* res) {
-  constexpr int kPer = NB / BS;
-  static_assert(kPer >= 1 && kPer * BS == NB && kPer <= 16, "bins per thread");
-  uint32_t cnt[kPer];
-  uint32_t sum = 0;
-#pragma unroll
-  for (int m = 0; m < kPer; ++m) {
-    const int pos = threadIdx.x * kPer + m;
-    cnt[m] = h[descending ? NB - 1 - pos : pos];
-    sum += cnt[m];
-  }
-  uint32_t total;
-  const uint32_t incl = block_scan_incl<BS>(sum, shw, total);
-  const uint32_t excl = incl - sum;
-  if (excl < need && need <= incl) {
-    uint32_t run = excl;
-    for (int m = 0; m < kPer; ++m) {
-      if (run + cnt[m] >= need) {
-        const int pos = threadIdx.x * kPer + m;
-        res[0] = (uint32_t)(descending ? NB - 1 - pos : pos);
-        res[1] = run;
-        break;
-      }
-      run += cnt[m];
-    }
-  }
-  __syncthreads();
-}
-
-// Adds 1 to the LDS histogram bin `bin` of every lane with `take` set; every lane of the
-// wave must call it. The lanes whose bin equals that of the first taking lane add with one
-// atomic, so runs of equal keys (all-zero estimates, say) do not serialise on one address.
-__device__ __forceinline__ void hist_add(uint32_t* h, bool take, uint32_t bin) {
-  const uint64_t act = __ballot(take);
-  if (act == 0ull) return;
-  const int first = __builtin_ctzll(act);
-  const uint32_t b0 = __shfl(bin, first, 64);
-  const uint64_t same = __ballot(take && bin == b0);
-  if (take && bin != b0) atomicAdd(&h[bin], 1u);
-  if ((int)(threadIdx.x & 63) == first) atomicAdd(&h[b0], (uint32_t)__popcll(same));
-}
-
 // ------------------------------------------------------------------------------------
 // Step 1, full path: every coordinate is a candidate ("dense" candidates: candidate t is
 // coordinate t, so no index array). The estimate, its key in cand_key[i], the digit-1
 // histogram in hist, and the output bitmap cleared.
-
-// After a pruned pass: true when fewer than k coordinates reached its bound, so the full
-// estimate has to run. The first kernel of the full path calls it (every block sees the
-// same counts) and raises ctl->fallback, which gates the kernels after it.
-__device__ __forceinline__ bool fallback_needed(SelectCtl* ctl) {
-  const bool fb = ctl->n_cand < ctl->k;
-  if (fb && blockIdx.x == 0 && threadIdx.x == 0) ctl->fallback = 1u;
-  return fb;
-}
 
 // k_unsketch's grid. Each block adds its LDS histogram into the global one with an atomic
 // per non-empty bin, and the atomics of many blocks on the few well-filled bins queue at one
@@ -143,9 +57,7 @@ constexpr int kUnsketchSmall = 8;
 template <int R, int U>
 __global__ void __launch_bounds__(kBlock) k_unsketch(HashSet hs, const float* __restrict__ merged, int64_t d,
                                                      float* __restrict__ est, uint32_t* __restrict__ keys,
-                                                     uint32_t* __restrict__ hist, uint32_t* __restrict__ bitmap,
-                                                     SelectCtl* __restrict__ gate) {
-  if (gate && !fallback_needed(gate)) return;  // the pruned selection sufficed
+                                                     uint32_t* __restrict__ hist) {
   __shared__ uint32_t h[kDigit1Bins];
   for (int b = threadIdx.x; b < kDigit1Bins; b += kBlock) h[b] = 0u;
   RowConst kr[R];
@@ -185,8 +97,7 @@ __global__ void __launch_bounds__(kBlock) k_unsketch(HashSet hs, const float* __
       if (est) est[i] = e;
       const uint32_t key = abs_key(e);
       keys[i] = key;
-      atomicAdd(&h[key >> kDigit1Shift], 1u);
-      if ((i & 31) == 0) bitmap[i >> 5] = 0u;
+      atomicAdd(&h[key >> 19], 1u);  // cand_bin's coarse bins
     }
   }
   __syncthreads();
@@ -197,256 +108,175 @@ __global__ void __launch_bounds__(kBlock) k_unsketch(HashSet hs, const float* __
 }
 
 // ------------------------------------------------------------------------------------
-// Steps 2 and 3: digits 2 and 3 of the k-th key, then the index cut among equal keys.
-// Candidates are either the pruned pass's (keys in cand_key, coordinates in cand_idx,
-// digit-1 histogram in hist_c) or dense (after the full estimate: every coordinate, key
-// in cand_key, histogram in hist). dense_cands() tells which.
+// Step 2: the digit pass. Candidates are either the pruned pass's (keys in cand_key, coordinates in
+// cand_idx, fine bins in hist_c) or dense (after the full estimate: every coordinate, key in
+// cand_key, coarse bins in hist).
 
-constexpr int kSelUnroll = 8;    // candidate loads in flight per thread
-constexpr int kTieMax = 1024;    // ties at the k-th key resolved by ranking in LDS (else radix digits)
-constexpr int kDigit2Block = 1024;              // threads per k_digit2 block
+constexpr int kDigit2Block = 1024;           // threads per k_digit2 block
 constexpr int kStageBuf = 8 * kDigit2Block;  // per-block LDS buffer of k_digit2 (keys and coordinates)
+constexpr int kCountMax = 1024;              // emit ranges counted in LDS: all of them up to d = 2^29
 
-__device__ __forceinline__ bool dense_cands(const SelectCtl* ctl, int pruned) {
-  return !pruned || ctl->fallback != 0u;
-}
+struct DigitArgs {
+  const uint32_t* key;   // [n] candidate keys; dense: key of coordinate t at t
+  const int32_t* idx;    // [n] their coordinates; dense: null
+  SelectCtl* ctl;
+  const uint32_t* hist;  // [kDigit1Bins] level 0, [kDigitBins] level 1
+  uint32_t* hist_next;   // [kDigitBins] next digit of the staged keys, or null
+  uint32_t* out_key;     // staged keys of the bin
+  int32_t* out_idx;
+  int64_t cap;           // room in out_key and out_idx
+  uint32_t* bitmap;      // keys above the bin set their bit (dense: every word is written)
+  uint32_t* counts;      // and are counted per emit range
+  const float* merged;   // the estimates, when the pruned pass fell short
+  const uint32_t* rnd;
+  int64_t d, range;
+  int64_t slice;         // dense: keys per block (a multiple of 64)
+  uint32_t slices;       // and blocks per emit range
+  uint32_t k;
+  int pruned, hm, level;
+};
 
-// Step 2 (many blocks): every block finds the digit-1 bucket b1 of the k-th key in the
-// candidates' histogram (block 0 records it); then the digit-2 histogram of the bucket's
-// keys (LDS per block, added into hist2) and the bucket compacted, key and coordinate, into
-// stage_key / stage_idx (an LDS buffer per block, one global atomic per flush).
-__global__ void __launch_bounds__(kDigit2Block) k_digit2(const uint32_t* __restrict__ cand_key,
-                                                   const int32_t* __restrict__ cand_idx,
-                                                   SelectCtl* __restrict__ ctl, int64_t cap, int64_t d,
-                                                   const uint32_t* __restrict__ hist_c,
-                                                   const uint32_t* __restrict__ hist, int pruned, uint32_t k,
-                                                   uint32_t* __restrict__ hist2, uint32_t* __restrict__ stage_key,
-                                                   int32_t* __restrict__ stage_idx, uint32_t* __restrict__ bitmap) {
+// Many blocks: every block finds the bin of the k-th key in the histogram (block 0 records it);
+// keys above it are taken (their bit in the output bitmap: an atomic each, or for dense candidates a
+// ballot per 64 coordinates; and the count of their emit range); the bin is compacted, key and coordinate, through an LDS buffer per
+// block and one global atomic per flush, with a histogram of the next ten bits on request. Level 1
+// runs the same over the keys staged by level 0, by that next digit: a dense bin holds percents
+// of d, too many for the emit's workgroups to read one by one.
+// When the pruned pass left fewer than k candidates, the blocks instead store every coordinate's
+// key in out_key for the emit.
+__global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs) {
+  union Buf {
+    struct {
+      uint32_t key[kStageBuf];
+      int32_t idx[kStageBuf];
+    } s;
+    float rows[kDigit2Block * kMaxRows];
+  };
+  __shared__ Buf buf;
   __shared__ uint32_t h[kDigitBins];
-  __shared__ uint32_t bkey[kStageBuf];
-  __shared__ int32_t bidx[kStageBuf];
+  __shared__ uint32_t cnt[kCountMax];
   __shared__ uint32_t shw[kDigit2Block / 64];
   __shared__ uint32_t res[2];
   __shared__ uint32_t bn, gbase;
-  const bool dense = dense_cands(ctl, pruned);
-  const int64_t n = dense ? d : (ctl->n_cand < (uint64_t)cap ? (int64_t)ctl->n_cand : cap);
-  find_bucket<kDigit2Block, kDigit1Bins>(dense ? hist : hist_c, true, k, shw, res);
-  const uint32_t b1 = res[0];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctl->b1 = res[0];
-    ctl->above1 = res[1];
+  SelectCtl* const ctl = a.ctl;
+  const int64_t grid = gridDim.x;
+  if (a.pruned && ctl->n_cand < a.k) {
+    const double theta = ctl->theta;
+    for (int64_t i = (int64_t)blockIdx.x * kDigit2Block + threadIdx.x; i < a.d; i += grid * kDigit2Block) {
+      const float e = estimate_any(hs, a.merged, (uint32_t)i, buf.rows + threadIdx.x * kMaxRows);
+      uint32_t key = abs_key(e);
+      if (a.hm) key = (double)e * (double)e >= theta ? 0x80000000u | key : a.rnd[i] >> 1;
+      a.out_key[i] = key;
+    }
+    return;
   }
+  int64_t n;
+  uint32_t need = a.k, klo, khi;
+  if (a.level == 0) {
+    n = a.pruned ? (int64_t)ctl->n_cand : a.d;
+    find_bucket<kDigit2Block, kDigit1Bins>(a.hist, true, need, shw, res);
+    const CandBins bins = cand_bins(a.pruned ? ctl->tau0 : 0u, a.hm != 0, a.hm ? ctl->theta : 0.0, a.pruned != 0);
+    klo = (uint32_t)cand_bin_lo(bins, res[0]);
+    khi = (uint32_t)(cand_bin_lo(bins, res[0] + 1u) - 1ull);
+  } else {
+    n = (int64_t)ctl->n_stage[0];
+    need = ctl->need[0];
+    const uint32_t lo0 = ctl->lo[0], w = ctl->hi[0] - lo0;  // level 0's bin is 2^19 or 2^20 keys wide
+    const int sh = 32 - __clz(w) - 10;
+    find_bucket<kDigit2Block, kDigitBins>(a.hist, true, need, shw, res);
+    klo = lo0 + (res[0] << sh);
+    khi = klo + ((1u << sh) - 1u);
+  }
+  need -= res[1];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctl->need[a.level] = need;
+    ctl->lo[a.level] = klo;
+    ctl->hi[a.level] = khi;
+  }
+  const uint32_t kw = khi - klo;
+  const int nsh = 32 - __clz(kw | 1u) - 10;  // shift of the next digit (with hist_next: kw is 2^19 - 1 or 2^20 - 1)
   const int lane = threadIdx.x & 63;
+  const int nr = (int)((a.d + a.range - 1) / a.range);
   for (int b = threadIdx.x; b < kDigitBins; b += kDigit2Block) h[b] = 0u;
+  for (int b = threadIdx.x; b < kCountMax; b += kDigit2Block) cnt[b] = 0u;
   if (threadIdx.x == 0) bn = 0u;
   __syncthreads();
-  const int64_t per = (n + gridDim.x - 1) / gridDim.x;
-  const int64_t lo = (int64_t)blockIdx.x * per, hi = min(n, lo + per);
+  const uint32_t range = (uint32_t)a.range;
+  const bool dense = a.idx == nullptr;
+  // a dense slice lies in one emit range, and its words of the bitmap are its own
+  const int64_t per = dense ? a.slice : (n + grid - 1) / grid;
+  const int64_t r0 = dense ? blockIdx.x / a.slices * a.range : 0;
+  const int64_t lo = dense ? r0 + blockIdx.x % a.slices * per : blockIdx.x * per;
+  const int64_t hi = min(dense ? min(n, r0 + a.range) : n, lo + per);
+  uint32_t mine = 0;  // dense: this wave's keys above the bin
   constexpr int V = 4;
   for (int64_t c0 = lo; c0 < hi; c0 += (int64_t)V * kDigit2Block) {  // block-uniform
-    uint32_t key[V];
+    uint32_t key[V], ix[V];
 #pragma unroll
     for (int m = 0; m < V; ++m) {
       const int64_t t = c0 + (int64_t)m * kDigit2Block + threadIdx.x;
-      key[m] = t < hi ? cand_key[t] : 0u;
+      key[m] = t < hi ? a.key[t] : 0u;
+      ix[m] = !dense && t < hi ? (uint32_t)a.idx[t] : (uint32_t)t;
     }
 #pragma unroll
     for (int m = 0; m < V; ++m) {
       const int64_t t = c0 + (int64_t)m * kDigit2Block + threadIdx.x;
-      const uint32_t d1 = key[m] >> kDigit1Shift;
-      if (t < hi && d1 > b1) {  // above the k-th key's bucket: taken
-        const uint32_t ix = dense ? (uint32_t)t : (uint32_t)cand_idx[t];
-        atomicOr(&bitmap[ix >> 5], 1u << (ix & 31u));
+      const bool above = t < hi && key[m] > khi;
+      if (dense) {
+        const uint64_t bal = __ballot(above);
+        mine += (uint32_t)__popcll(bal);
+        const int64_t w = (t - lane) / 32 + lane;  // slices are multiples of 64 coordinates
+        if (lane < 2 && t - lane + 32 * lane < hi) a.bitmap[w] = (uint32_t)(lane ? bal >> 32 : bal);
+      } else {
+        if (above) atomicOr(&a.bitmap[ix[m] >> 5], 1u << (ix[m] & 31u));
+        if (nr <= kCountMax)
+          hist_add(cnt, above, above ? ix[m] / range : 0u);
+        else if (above)
+          atomicAdd(&a.counts[ix[m] / range], 1u);
       }
-      const bool take = t < hi && d1 == b1;
-      hist_add(h, take, (key[m] >> 10) & 1023u);
+      const bool take = t < hi && key[m] - klo <= kw;
+      if (a.hist_next) hist_add(h, take, take ? (key[m] - klo) >> nsh : 0u);
       const uint64_t bal = __ballot(take);
       uint32_t wbase = 0u;
       if (lane == 0 && bal) wbase = atomicAdd(&bn, (uint32_t)__popcll(bal));
       wbase = __shfl(wbase, 0);
       if (take) {
         const uint32_t pos = wbase + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-        bkey[pos] = key[m];
-        bidx[pos] = dense ? (int32_t)t : cand_idx[t];
+        buf.s.key[pos] = key[m];
+        buf.s.idx[pos] = (int32_t)ix[m];
       }
     }
     __syncthreads();
     const uint32_t nb = bn;  // < kStageBuf / 2 + V * kDigit2Block <= kStageBuf
     if (nb >= (uint32_t)(kStageBuf / 2) || (c0 + (int64_t)V * kDigit2Block >= hi && nb > 0)) {
-      if (threadIdx.x == 0) gbase = atomicAdd(&ctl->n_stage2, nb);
+      if (threadIdx.x == 0) gbase = atomicAdd(&ctl->n_stage[a.level], nb);
       __syncthreads();
-      const uint32_t g0 = gbase;
+      const int64_t g0 = gbase;
       for (uint32_t t = threadIdx.x; t < nb; t += kDigit2Block) {
-        stage_key[g0 + t] = bkey[t];
-        stage_idx[g0 + t] = bidx[t];
+        if (g0 + t < a.cap) {
+          a.out_key[g0 + t] = buf.s.key[t];
+          a.out_idx[g0 + t] = buf.s.idx[t];
+        }
       }
       __syncthreads();
       if (threadIdx.x == 0) bn = 0u;
     }
     __syncthreads();
   }
-  for (int b = threadIdx.x; b < kDigitBins; b += kDigit2Block) {
-    const uint32_t c = h[b];
-    if (c) atomicAdd(&hist2[b], c);
+  if (a.hist_next)
+    for (int b = threadIdx.x; b < kDigitBins; b += kDigit2Block) {
+      const uint32_t c = h[b];
+      if (c) atomicAdd(&a.hist_next[b], c);
+    }
+  if (dense) {
+    if (lane == 0 && mine) atomicAdd(&cnt[0], mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && cnt[0]) atomicAdd(&a.counts[lo / a.range], cnt[0]);
+    return;
   }
-}
-
-// Step 3 (one block): the digit-2 bucket from the histogram, digit 3 over the staged keys,
-// and the index cut among the staged keys equal to tau. Clears the histograms it and
-// k_digit2 consumed for the next call.
-__global__ void __launch_bounds__(kSelBlock) k_select2(SelectCtl* __restrict__ ctl, uint32_t* __restrict__ hist2,
-                                                       const uint32_t* __restrict__ stage_key,
-                                                       const int32_t* __restrict__ stage_idx,
-                                                       uint32_t* __restrict__ hist_c, uint32_t* __restrict__ hist,
-                                                       int pruned, uint32_t k, unsigned long long* __restrict__ flags,
-                                                       int64_t emit_blocks) {
-  __shared__ uint32_t h[2048];
-  __shared__ uint32_t shw[kSelBlock / 64];
-  __shared__ uint32_t res[2];
-  __shared__ uint32_t n_tie;
-  const int64_t n2 = ctl->n_stage2;
-  const uint32_t b1 = ctl->b1;
-  const uint32_t need1 = k - ctl->above1;
-  const bool dense = dense_cands(ctl, pruned);
-
-  // digit 2 (key bits 19..10) among keys in bucket b1, scanned from the top
-  for (int b = threadIdx.x; b < kDigitBins; b += kSelBlock) {
-    h[b] = hist2[b];
-    hist2[b] = 0u;
-  }
-  if (pruned)
-    for (int b = threadIdx.x; b < kDigit1Bins; b += kSelBlock) hist_c[b] = 0u;
-  if (dense)
-    for (int b = threadIdx.x; b < kDigit1Bins; b += kSelBlock) hist[b] = 0u;
-  for (int64_t b = threadIdx.x; b < emit_blocks; b += kSelBlock) flags[b] = 0ull;  // the emit's look-back words
-  __syncthreads();
-  find_bucket<kSelBlock, kDigitBins>(h, true, need1, shw, res);
-  const uint32_t pre2 = (b1 << 10) | res[0];
-  const uint32_t need2 = need1 - res[1];
-  __syncthreads();
-
-  // digit 3 (key bits 9..0) among the staged keys with the 22-bit prefix pre2
-  for (int b = threadIdx.x; b < kDigitBins; b += kSelBlock) h[b] = 0u;
-  __syncthreads();
-  for (int64_t t0 = 0; t0 < n2; t0 += (int64_t)kSelUnroll * kSelBlock) {
-    uint32_t key[kSelUnroll];
-#pragma unroll
-    for (int m = 0; m < kSelUnroll; ++m) {
-      const int64_t t = t0 + (int64_t)m * kSelBlock + threadIdx.x;
-      key[m] = t < n2 ? stage_key[t] : 0u;
-    }
-#pragma unroll
-    for (int m = 0; m < kSelUnroll; ++m) {
-      const int64_t t = t0 + (int64_t)m * kSelBlock + threadIdx.x;
-      hist_add(h, t < n2 && (key[m] >> 10) == pre2, key[m] & 1023u);
-    }
-  }
-  __syncthreads();
-  find_bucket<kSelBlock, kDigitBins>(h, true, need2, shw, res);
-  const uint32_t tau = (pre2 << 10) | res[0];
-  const uint32_t need3 = need2 - res[1];  // how many keys equal to tau are taken
-  const uint32_t n_eq = h[res[0]];
-  __syncthreads();
-
-  // every key equal to tau is in the stage (its digit 1 is b1)
-  uint32_t iota = 0x7fffffffu;
-  if (need3 < n_eq && n_eq <= kTieMax) {
-    // few keys equal to tau (the usual case: an estimate is one table cell): one pass
-    // collects their coordinates in LDS, and iota is the one with exactly need3 - 1 smaller
-    // (the coordinates are distinct)
-    if (threadIdx.x == 0) n_tie = 0u;
-    __syncthreads();
-    for (int64_t t0 = 0; t0 < n2; t0 += (int64_t)kSelUnroll * kSelBlock) {
-      uint32_t key[kSelUnroll];
-#pragma unroll
-      for (int m = 0; m < kSelUnroll; ++m) {
-        const int64_t t = t0 + (int64_t)m * kSelBlock + threadIdx.x;
-        key[m] = t < n2 ? stage_key[t] : 0u;
-      }
-#pragma unroll
-      for (int m = 0; m < kSelUnroll; ++m) {
-        const int64_t t = t0 + (int64_t)m * kSelBlock + threadIdx.x;
-        if (t < n2 && key[m] == tau) {
-          const uint32_t pos = atomicAdd(&n_tie, 1u);
-          if (pos < (uint32_t)kTieMax) h[pos] = (uint32_t)stage_idx[t];
-        }
-      }
-    }
-    __syncthreads();
-    const uint32_t m_tie = min(n_tie, (uint32_t)kTieMax);  // == n_eq
-    for (uint32_t a = threadIdx.x; a < m_tie; a += kSelBlock) {
-      const uint32_t xa = h[a];
-      uint32_t rank = 0;
-      for (uint32_t b = 0; b < m_tie; ++b) rank += h[b] < xa ? 1u : 0u;
-      if (rank == need3 - 1) res[0] = xa;
-    }
-    __syncthreads();
-    iota = res[0];
-  } else if (need3 < n_eq) {
-    // many ties: ascending index digits among keys equal to tau: bits 30..21, 20..10, 9..0
-    for (int b = threadIdx.x; b < 1024; b += kSelBlock) h[b] = 0u;
-    __syncthreads();
-    for (int64_t t0 = 0; t0 < n2; t0 += kSelBlock) {  // block-uniform
-      const int64_t t = t0 + threadIdx.x;
-      const bool tie = t < n2 && stage_key[t] == tau;
-      hist_add(h, tie, tie ? (uint32_t)stage_idx[t] >> 21 : 0u);
-    }
-    __syncthreads();
-    find_bucket<kSelBlock, 1024>(h, false, need3, shw, res);
-    const uint32_t c1 = res[0];
-    const uint32_t needc = need3 - res[1];
-    __syncthreads();
-
-    for (int b = threadIdx.x; b < 2048; b += kSelBlock) h[b] = 0u;
-    __syncthreads();
-    for (int64_t t0 = 0; t0 < n2; t0 += kSelBlock) {
-      const int64_t t = t0 + threadIdx.x;
-      const uint32_t ix = t < n2 && stage_key[t] == tau ? (uint32_t)stage_idx[t] : 0xffffffffu;
-      const bool in = ix != 0xffffffffu && (ix >> 21) == c1;
-      hist_add(h, in, (ix >> 10) & 2047u);
-    }
-    __syncthreads();
-    find_bucket<kSelBlock, 2048>(h, false, needc, shw, res);
-    const uint32_t pre_i = (c1 << 11) | res[0];
-    const uint32_t needd = needc - res[1];
-    __syncthreads();
-
-    for (int b = threadIdx.x; b < 1024; b += kSelBlock) h[b] = 0u;
-    __syncthreads();
-    for (int64_t t0 = 0; t0 < n2; t0 += kSelBlock) {
-      const int64_t t = t0 + threadIdx.x;
-      const uint32_t ix = t < n2 && stage_key[t] == tau ? (uint32_t)stage_idx[t] : 0xffffffffu;
-      const bool in = ix != 0xffffffffu && (ix >> 10) == pre_i;
-      hist_add(h, in, ix & 1023u);
-    }
-    __syncthreads();
-    find_bucket<kSelBlock, 1024>(h, false, needd, shw, res);
-    iota = (pre_i << 10) | res[0];
-  }
-  if (threadIdx.x == 0) {
-    ctl->tau = tau;
-    ctl->iota = iota;
-    ctl->n_staged = (uint32_t)n2;
-    ctl->n_stage2 = 0u;
-    ctl->emit_ticket = 0u;
-  }
-}
-
-// ------------------------------------------------------------------------------------
-// Step 4: mark the taken keys of the staged digit-1 bucket (the candidates above it set
-// their bits in k_digit2).
-
-__global__ void __launch_bounds__(kBlock) k_mark(const uint32_t* __restrict__ stage_key,
-                                                 const int32_t* __restrict__ stage_idx,
-                                                 const SelectCtl* __restrict__ ctl, uint32_t* __restrict__ bitmap) {
-  const int64_t n2 = ctl->n_staged;
-  const uint32_t tau = ctl->tau, iota = ctl->iota;
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < n2; t += stride) {
-    const uint32_t key = stage_key[t];
-    if (key < tau) continue;
-    const uint32_t ix = (uint32_t)stage_idx[t];
-    if (key > tau || ix <= iota) atomicOr(&bitmap[ix >> 5], 1u << (ix & 31u));
+  for (int b = threadIdx.x; b < min(nr, kCountMax); b += kDigit2Block) {
+    const uint32_t c = cnt[b];
+    if (c) atomicAdd(&a.counts[b], c);
   }
 }
 
@@ -549,17 +379,14 @@ __global__ void __launch_bounds__(kSelBlock) k_heavy(const float* __restrict__ m
                                                   int r,
                                                   SelectCtl* __restrict__ ctl, uint32_t* __restrict__ heavy,
                                                   int hm, const uint32_t* __restrict__ sample, int M,
-                                                  uint32_t rho, uint32_t k, const uint32_t* __restrict__ hist_s) {
+                                                  uint32_t rho, const uint32_t* __restrict__ hist_s) {
   __shared__ uint32_t h[kDigitBins];
   __shared__ uint32_t shw[kSelBlock / 64];
   __shared__ uint32_t res[2];
   const uint32_t tau0 = sampled_bound<kSelBlock>(sample, M, rho, hist_s, h, shw, res);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->tau0 = tau0;
-    ctl->k = k;
     ctl->n_cand = 0u;
-    ctl->n_surv = 0u;
-    ctl->fallback = 0u;
   }
   const double theta = ctl->theta;
   // The map in groups of 64 cells (one ballot, two words each; hrow is a multiple of 64, so a
@@ -619,15 +446,18 @@ __global__ void __launch_bounds__(kBlock) k_coarse(const uint32_t* __restrict__ 
   }
 }
 
-// The pruned pass, in two kernels.
-// k_pruned: every coordinate checks its r heavy bits (bitmap in LDS when it fits); the
-// survivors (ceil(r/2) heavy cells; for HEAVYMIX also every coordinate whose fill key
-// rnd[i] >> 1 reaches tau0) are queued -- through an LDS buffer, one global atomic per
-// flush -- and the output bitmap words are cleared on the way.
-// k_survivors: the queued coordinates, with every lane busy, compute their exact estimate
-// and append the candidates (key >= tau0; for HEAVYMIX heavy ones always, key
-// 0x80000000 | bits(|est|), others by their fill key) and count |H|. Splitting keeps the
-// table reads of the few survivors from stalling whole waves of the first pass.
+// The pruned pass (k_pruned), in two phases per workgroup.
+// 1. Every coordinate of the workgroup checks its r heavy bits (bitmap in LDS when it fits); the
+//    survivors (ceil(r/2) heavy cells; for HEAVYMIX also every coordinate whose fill key
+//    rnd[i] >> 1 reaches tau0) are queued, through an LDS buffer, in the workgroup's own part of
+//    the queue (as many entries as it has coordinates, so no counter is shared).
+// 2. The workgroup's survivors, two per thread with every lane busy, get their exact estimate;
+//    those with key >= tau0 (for HEAVYMIX the heavy ones always, key 0x80000000 | bits(|est|),
+//    the others by their fill key) are appended to the candidates and counted in their
+//    histogram, and |H| is counted.
+// Estimating a survivor where it is found stalled whole waves for a few lanes (159 us at
+// 25.6M x 8); a second kernel for the estimates cost its launch and drained the chip in between
+// (73 + 14 us, against 78 us in one kernel).
 // dynamic LDS of k_pruned: [map words?][buf indices]
 constexpr int kPruneBlock = 1024;  // 16 waves per CU; the heavy bitmap fills the LDS
 
@@ -640,6 +470,8 @@ constexpr int kMapCoarse = 1;  // a coarse map in LDS (one bit per 2^coarse_log2
 constexpr int kMapGlobal = 2;  // the fine map read from global memory
 
 constexpr int kPruneLdsWords = 160 * 1024 / 4;  // the whole LDS of a CU (one workgroup per CU)
+constexpr int kSurvBuf = 4 * kPruneBlock;       // candidate buffer of the second phase
+static_assert(kDigit1Bins + 2 * kSurvBuf + 3 <= kPruneLdsWords, "second phase of k_pruned");
 
 template <int MAP>
 __device__ __forceinline__ int64_t map_words_in_lds(int64_t map_words) {
@@ -656,18 +488,19 @@ __global__ void __launch_bounds__(kPruneBlock) k_pruned(HashSet hs, int64_t d, S
                                                    int64_t hrow, int coarse_log2, int buf_cap,
                                                    uint32_t* __restrict__ queue,
                                                    uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ rnd,
-                                                   uint32_t* __restrict__ hist_s) {
+                                                   uint32_t* __restrict__ hist_s, const float* __restrict__ merged,
+                                                   uint32_t* __restrict__ cand_key, int32_t* __restrict__ cand_idx,
+                                                   uint32_t* __restrict__ hist_c) {
   // coordinates per lane per pass: independent hash chains in flight (two registers each per
   // row, so fewer with many rows, where four would spill); six with the map in LDS and few
   // rows (d = 25.6M x 8, r = 5: 71 -> 68.5 us; with the coarse map six measured no better)
   constexpr int U = (MAP == kMapFine && R <= 6) ? 6 : R <= 8 ? 4 : R <= 12 ? 2 : 1;
   // map index j * hrow + col of a cell; below 2^32 whenever a map fits in LDS
   using Cell = typename std::conditional<MAP == kMapGlobal, uint64_t, uint32_t>::type;
-  // LDS: [map words][buf_cap queue entries][2 counters], one static array, so a lookup's
+  // LDS: [map words][buf_cap queue entries][counter], one static array, so a lookup's
   // address is known at compile time to need no base added
   __shared__ uint32_t sm[kPruneLdsWords];
   uint32_t& bn = sm[map_words_in_lds<MAP>(map_words) + buf_cap];
-  uint32_t& gbase = sm[map_words_in_lds<MAP>(map_words) + buf_cap + 1];
   if (blockIdx.x == 0)  // the samples' histogram, read by k_heavy, cleared for the next call
     for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) hist_s[b] = 0u;
   uint32_t* buf = sm;
@@ -697,6 +530,11 @@ __global__ void __launch_bounds__(kPruneBlock) k_pruned(HashSet hs, int64_t d, S
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * kPruneBlock * U;
   const int64_t base0 = (int64_t)blockIdx.x * kPruneBlock * U;
+  // this workgroup's part of the queue: as long as the number of its coordinates, after the
+  // parts of the workgroups before it (d / stride whole passes and a share of the rest)
+  const int64_t passes = d / stride;
+  queue += passes * base0 + min(d - passes * stride, base0);
+  int64_t qn = 0;  // survivors in it (block-uniform)
   // Raw bucket hashes and columns of this lane's U coordinates, advanced by one stride per
   // pass without a multiply: the raw hash moves by db = (a * stride) mod p, less p when it
   // passes p, so the column moves by dc1 = db mod c, or by dc2 = (db - p) mod c after such a
@@ -799,221 +637,103 @@ __global__ void __launch_bounds__(kPruneBlock) k_pruned(HashSet hs, int64_t d, S
       if constexpr (HM) keep = keep || (i < d && fill[m] >= tau0);
       if (keep) {
         const uint32_t pos = atomicAdd(&bn, 1u);
-        if (pos < (uint32_t)buf_cap) {
+        if (pos < (uint32_t)buf_cap)
           buf[pos] = (uint32_t)i;
-        } else {  // buffer full within this pass (dense survivors): queue directly
-          queue[atomicAdd(&ctl->n_surv, 1u)] = (uint32_t)i;
-        }
+        else
+          queue[qn + pos] = (uint32_t)i;  // buffer full within this pass (dense survivors)
       }
       if (i < d && (i & 31) == 0) bitmap[i >> 5] = 0u;
     }
     __syncthreads();
-    const uint32_t n = min(bn, (uint32_t)buf_cap);
+    const uint32_t n = bn;
     const bool last = base + stride >= d;
     if (n >= (uint32_t)(buf_cap / 2) || (last && n > 0)) {
-      if (threadIdx.x == 0) gbase = atomicAdd(&ctl->n_surv, n);
-      __syncthreads();
-      const uint32_t g0 = gbase;
-      for (uint32_t t = threadIdx.x; t < n; t += kPruneBlock) queue[g0 + t] = buf[t];
+      const uint32_t nb = min(n, (uint32_t)buf_cap);
+      for (uint32_t t = threadIdx.x; t < nb; t += kPruneBlock) queue[qn + t] = buf[t];
+      qn += n;
       __syncthreads();
       if (threadIdx.x == 0) bn = 0;
     }
     __syncthreads();
   }
-}
 
-// k_survivors: two blocks of 512 threads per CU (25.6M x 8: 15.8-16.1 us; one block of 256, 512
-// or 1024 threads per CU: 18.8, 17.0, 18.8 us; four of 512: 17.9 us)
-constexpr int kSurvBlock = 512;
-constexpr int kSurvBuf = 2048;  // per-block LDS candidate buffer of k_survivors (at least 2 * kSurvBlock)
-
-template <int R, bool HM>
-__global__ void __launch_bounds__(kSurvBlock) k_survivors(HashSet hs, const float* __restrict__ merged,
-                                                      SelectCtl* __restrict__ ctl, const uint32_t* __restrict__ queue,
-                                                      uint32_t* __restrict__ cand_key, int32_t* __restrict__ cand_idx,
-                                                      int64_t cap, const uint32_t* __restrict__ rnd,
-                                                      uint32_t* __restrict__ hist_c) {
-  __shared__ uint32_t bkey[kSurvBuf];
-  __shared__ int32_t bidx[kSurvBuf];
-  __shared__ uint32_t h[kDigit1Bins];
-  __shared__ uint32_t bn, gbase, nheavy;
-  for (int b = threadIdx.x; b < kDigit1Bins; b += kSurvBlock) h[b] = 0u;
-  RowConst kr[R];
-#pragma unroll
-  for (int j = 0; j < R; ++j) kr[j] = row_const(hs, j);
-  const uint32_t tau0 = ctl->tau0;
-  const double theta = HM ? ctl->theta : 0.0;
-  const int64_t n = ctl->n_surv;
-  const int lane = threadIdx.x & 63;
+  // Phase 2: the map's LDS now holds the candidates' histogram and append buffer.
+  constexpr int V = 2;  // survivors per thread and pass, all their cell loads in flight
+  uint32_t* const h = sm;
+  uint32_t* const bkey = sm + kDigit1Bins;
+  int32_t* const bidx = reinterpret_cast<int32_t*>(bkey + kSurvBuf);
+  uint32_t& cn = sm[kDigit1Bins + 2 * kSurvBuf];
+  uint32_t& cbase = sm[kDigit1Bins + 2 * kSurvBuf + 1];
+  uint32_t& nheavy = sm[kDigit1Bins + 2 * kSurvBuf + 2];
+  for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) h[b] = 0u;
   if (threadIdx.x == 0) {
-    bn = 0u;
+    cn = 0u;
     nheavy = 0u;
   }
   __syncthreads();
+  const double theta = HM ? ctl->theta : 0.0;
+  const CandBins bins = cand_bins(tau0, HM, theta, true);
+  const int lane = threadIdx.x & 63;
   uint32_t mine = 0;
-  const int64_t stride = (int64_t)gridDim.x * kSurvBlock;
-  for (int64_t t0 = (int64_t)blockIdx.x * kSurvBlock; t0 < n; t0 += stride) {  // block-uniform trip count
-    const int64_t t = t0 + threadIdx.x;
-    bool cand = false;
-    uint32_t key = 0u, i = 0u;
-    if (t < n) {
-      i = queue[t];
-      const float e = estimate_val<R>(kr, merged, i);
+  for (int64_t t0 = 0; t0 < qn; t0 += V * kPruneBlock) {  // block-uniform
+    uint32_t ii[V], key[V];
+    float e[V];
+    bool cand[V];
+#pragma unroll
+    for (int m = 0; m < V; ++m) {
+      const int64_t t = t0 + m * kPruneBlock + threadIdx.x;
+      cand[m] = t < qn;
+      ii[m] = cand[m] ? queue[t] : 0u;  // coordinate 0 stands in past the end (in range)
+    }
+#pragma unroll
+    for (int m = 0; m < V; ++m) e[m] = estimate_val<R>(kr, merged, ii[m]);
+#pragma unroll
+    for (int m = 0; m < V; ++m) {
       if constexpr (HM) {
-        const bool hv = (double)e * (double)e >= theta;
-        key = hv ? (0x80000000u | abs_key(e)) : (rnd[i] >> 1);
-        cand = hv || key >= tau0;
+        const bool hv = cand[m] && (double)e[m] * (double)e[m] >= theta;
+        key[m] = hv ? (0x80000000u | abs_key(e[m])) : (cand[m] ? rnd[ii[m]] >> 1 : 0u);
+        cand[m] = hv || (cand[m] && key[m] >= tau0);
         mine += hv ? 1u : 0u;
       } else {
-        key = abs_key(e);
-        cand = key >= tau0;
+        key[m] = abs_key(e[m]);
+        cand[m] = cand[m] && key[m] >= tau0;
       }
-    }
-    hist_add(h, cand, key >> kDigit1Shift);
-    // block-local append (one LDS atomic per wave); at most kSurvBlock per pass, so the buffer,
-    // flushed whenever it is half full, never overflows
-    const uint64_t bal = __ballot(cand);
-    uint32_t wbase = 0u;
-    if (lane == 0 && bal) wbase = atomicAdd(&bn, (uint32_t)__popcll(bal));
-    wbase = __shfl(wbase, 0);
-    if (cand) {
-      const uint32_t pos = wbase + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-      bkey[pos] = key;
-      bidx[pos] = (int32_t)i;
+      hist_add(h, cand[m], cand_bin(bins, key[m]));
+      // one LDS atomic per wave; at most V * kPruneBlock entries a pass, and the buffer, flushed
+      // whenever it is half full, holds twice that
+      const uint64_t bal = __ballot(cand[m]);
+      uint32_t wbase = 0u;
+      if (lane == 0 && bal) wbase = atomicAdd(&cn, (uint32_t)__popcll(bal));
+      wbase = __shfl(wbase, 0);
+      if (cand[m]) {
+        const uint32_t pos = wbase + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+        bkey[pos] = key[m];
+        bidx[pos] = (int32_t)ii[m];
+      }
     }
     __syncthreads();
-    const uint32_t nb = bn;
-    if (nb >= (uint32_t)(kSurvBuf / 2) || (t0 + stride >= n && nb > 0)) {
-      if (threadIdx.x == 0) gbase = atomicAdd(&ctl->n_cand, nb);
+    const uint32_t nb = cn;
+    if (nb >= (uint32_t)(kSurvBuf / 2) || (t0 + V * kPruneBlock >= qn && nb > 0)) {
+      if (threadIdx.x == 0) cbase = atomicAdd(&ctl->n_cand, nb);
       __syncthreads();
-      const int64_t g0 = gbase;
-      for (uint32_t u = threadIdx.x; u < nb; u += kSurvBlock) {
-        if (g0 + u < cap) {
-          cand_key[g0 + u] = bkey[u];
-          cand_idx[g0 + u] = bidx[u];
-        }
+      const int64_t g0 = cbase;
+      for (uint32_t t = threadIdx.x; t < nb; t += kPruneBlock) {
+        cand_key[g0 + t] = bkey[t];
+        cand_idx[g0 + t] = bidx[t];
       }
       __syncthreads();
-      if (threadIdx.x == 0) bn = 0u;
+      if (threadIdx.x == 0) cn = 0u;
     }
     __syncthreads();
   }
   if constexpr (HM) {
     if (mine) atomicAdd(&nheavy, mine);
-  }
-  __syncthreads();
-  if constexpr (HM) {
+    __syncthreads();
     if (threadIdx.x == 0 && nheavy) atomicAdd(&ctl->n_heavy, (unsigned long long)nheavy);
   }
-  for (int b = threadIdx.x; b < kDigit1Bins; b += kSurvBlock) {
+  for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) {
     const uint32_t c = h[b];
     if (c) atomicAdd(&hist_c[b], c);
-  }
-}
-
-// ------------------------------------------------------------------------------------
-// Step 5: bitmap -> ascending index list.
-
-// Look-back word of emit block b: 0 until published, then kFlagAgg | (the block's own count),
-// then kFlagIncl | (the count of blocks 0..b together). The count is all a word carries, so
-// relaxed device-scope loads and stores of the word suffice (no fence orders other data).
-constexpr unsigned long long kFlagAgg = 1ull << 62, kFlagIncl = 2ull << 62;
-constexpr unsigned long long kFlagCount = 0xffffffffull;
-// A block polls a window of predecessors' words at most spin_max times before it counts the
-// bitmap words before its own directly (the blocks start in ticket order, so a predecessor is
-// running and publishes without waiting on later blocks; the bound makes every wait finite
-// regardless). spin_max < 0: every block counts directly.
-
-__device__ __forceinline__ unsigned long long flag_load(const unsigned long long* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void flag_store(unsigned long long* p, unsigned long long v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Bitmap -> ascending index list in one pass. Block b (by ticket, i.e. in start order) owns
-// words [b W, (b + 1) W): it counts its bits, publishes the count, adds the counts of the
-// blocks before it (walking back until a block that has published its inclusive count),
-// publishes its own inclusive count and writes its indices from that offset.
-__global__ void __launch_bounds__(kSelBlock) k_emit(const uint32_t* __restrict__ bitmap, int64_t words,
-                                                    SelectCtl* __restrict__ ctl,
-                                                    unsigned long long* __restrict__ flags,
-                                                    int32_t* __restrict__ idx, uint32_t k, int spin_max) {
-  __shared__ uint32_t shw[kSelBlock / 64];
-  __shared__ uint32_t sb, sexcl, sdirect;
-  if (threadIdx.x == 0) {
-    sb = atomicAdd(&ctl->emit_ticket, 1u);
-    sdirect = 0u;
-  }
-  __syncthreads();
-  const int64_t b = sb;
-  const int64_t w0 = b * kEmitWordsPerBlock + (int64_t)threadIdx.x * kEmitWordsPerThread;
-  uint32_t wv[kEmitWordsPerThread];
-  uint32_t cnt = 0;
-#pragma unroll
-  for (int m = 0; m < kEmitWordsPerThread; ++m) {
-    wv[m] = (w0 + m < words) ? bitmap[w0 + m] : 0u;
-    cnt += __popc(wv[m]);
-  }
-  uint32_t total;
-  const uint32_t incl = block_scan_incl<kSelBlock>(cnt, shw, total);
-  if (threadIdx.x < 64) {  // the first wave publishes and looks back, 64 predecessors at a time
-    const int lane = threadIdx.x;
-    if (lane == 0) flag_store(&flags[b], (b == 0 ? kFlagIncl : kFlagAgg) | total);
-    uint32_t excl = 0;
-    bool direct = spin_max < 0 && b > 0;
-    for (int64_t top = direct ? -1 : b - 1; top >= 0; top -= 64) {
-      const int64_t j = top - lane;  // lane 0 is the nearest predecessor
-      unsigned long long f = j >= 0 ? flag_load(&flags[j]) : kFlagIncl;  // before block 0: 0
-      uint64_t incl_lanes, need;
-      for (int spin = 0;; ++spin) {
-        incl_lanes = __ballot((f & kFlagIncl) != 0ull);
-        // lanes up to the nearest inclusive word must have published
-        need = incl_lanes ? ((2ull << __builtin_ctzll(incl_lanes)) - 1ull) : ~0ull;
-        if ((__ballot(f == 0ull) & need) == 0ull) break;
-        if (spin >= spin_max) {
-          direct = true;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-        if (f == 0ull) f = flag_load(&flags[j]);
-      }
-      if (direct) break;
-      uint32_t part = ((need >> lane) & 1ull) ? (uint32_t)(f & kFlagCount) : 0u;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
-      excl += part;
-      if (incl_lanes) break;
-    }
-    if (lane == 0) {
-      sdirect = direct ? 1u : 0u;
-      if (b > 0 && !direct) flag_store(&flags[b], kFlagIncl | (excl + total));
-      sexcl = excl;
-    }
-  }
-  __syncthreads();
-  if (sdirect) {  // every word before this block's, counted by the whole block
-    uint32_t before = 0;
-    for (int64_t w = threadIdx.x; w < b * kEmitWordsPerBlock; w += kSelBlock) before += __popc(bitmap[w]);
-    uint32_t all;
-    (void)block_scan_incl<kSelBlock>(before, shw, all);
-    if (threadIdx.x == 0) {
-      sexcl = all;
-      flag_store(&flags[b], kFlagIncl | (all + total));
-    }
-    __syncthreads();
-  }
-  uint32_t pos = sexcl + incl - cnt;
-  const int64_t wb = b * kEmitWordsPerBlock + (int64_t)threadIdx.x * kEmitWordsPerThread;
-#pragma unroll
-  for (int m = 0; m < kEmitWordsPerThread; ++m) {
-    uint32_t w = wv[m];
-    while (w) {
-      const int bit = __ffs(w) - 1;
-      if (pos < k) idx[pos] = (int32_t)((wb + m) * 32 + bit);
-      ++pos;
-      w &= w - 1u;
-    }
   }
 }
 
@@ -1088,14 +808,10 @@ __global__ void k_theta(const double* __restrict__ rows, int r, int64_t k, Selec
 
 // Estimate + HEAVYMIX key + digit-1 histogram + |H|.
 template <int R>
-// gated: act only when the pruned pass raised the fallback flag; count_heavy: add |H| to
-// ctl->n_heavy (off after a pruned pass, which already counted it).
 __global__ void __launch_bounds__(kBlock) k_unsketch_hm(HashSet hs, const float* __restrict__ merged, int64_t d,
                                                         const uint32_t* __restrict__ rnd, float* __restrict__ est,
                                                         uint32_t* __restrict__ keys, uint32_t* __restrict__ hist,
-                                                        uint32_t* __restrict__ bitmap, SelectCtl* __restrict__ ctl,
-                                                        int gated, int count_heavy) {
-  if (gated && !fallback_needed(ctl)) return;
+                                                        SelectCtl* __restrict__ ctl) {
   __shared__ uint32_t h[kDigit1Bins];
   __shared__ uint32_t nh;
   for (int b = threadIdx.x; b < kDigit1Bins; b += kBlock) h[b] = 0u;
@@ -1133,8 +849,7 @@ __global__ void __launch_bounds__(kBlock) k_unsketch_hm(HashSet hs, const float*
     const uint32_t key = heavy ? (0x80000000u | abs_key(e)) : (rnd[i] >> 1);
     mine += heavy ? 1u : 0u;
     keys[i] = key;
-    atomicAdd(&h[key >> kDigit1Shift], 1u);
-    if ((i & 31) == 0) bitmap[i >> 5] = 0u;
+    atomicAdd(&h[key >> 20], 1u);  // cand_bin's coarse bins
   }
   if (mine) atomicAdd(&nh, mine);
   __syncthreads();
@@ -1142,24 +857,18 @@ __global__ void __launch_bounds__(kBlock) k_unsketch_hm(HashSet hs, const float*
     const uint32_t n = h[b];
     if (n) atomicAdd(&hist[b], n);
   }
-  if (count_heavy && threadIdx.x == 0 && nh) atomicAdd(&ctl->n_heavy, (unsigned long long)nh);
-}
-
-__global__ void k_hm_out(const SelectCtl* __restrict__ ctl, int64_t* __restrict__ n_heavy, double* __restrict__ l2sq) {
-  if (threadIdx.x != 0) return;
-  if (n_heavy) *n_heavy = (int64_t)ctl->n_heavy;
-  if (l2sq) *l2sq = ctl->l2sq;
+  if (threadIdx.x == 0 && nh) atomicAdd(&ctl->n_heavy, (unsigned long long)nh);
 }
 
 template <int R>
 void launch_unsketch_r(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
-                       const float* merged, float* est, SelectCtl* gate) {
+                       const float* merged, float* est) {
   if (d <= (int64_t)kUnsketchSmall * kBlock * num_cus)
     hipLaunchKernelGGL((k_unsketch<R, 2>), dim3(grid_for(d, 2 * kBlock, num_cus)), dim3(kBlock), 0, s, hs, merged, d,
-                       est, b.cand_key, b.hist, b.bitmap, gate);
+                       est, b.cand_key, b.hist);
   else
     hipLaunchKernelGGL((k_unsketch<R, 1>), dim3(grid_for(d, kBlock, 4 * num_cus)), dim3(kBlock), 0, s, hs, merged, d,
-                       est, b.cand_key, b.hist, b.bitmap, gate);
+                       est, b.cand_key, b.hist);
 }
 
 template <int R, bool HM>
@@ -1175,61 +884,77 @@ void launch_prune_r(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, co
   const int64_t nbits = (int64_t)x->r * x->heavy_row;  // heavy-cell map bits (padded rows)
   hipLaunchKernelGGL(k_heavy, dim3(grid_for(nbits, kSelBlock * kHeavyUnroll, x->num_cus)), dim3(kSelBlock), 0, s,
                      merged, x->c, x->heavy_row, x->r, x->ctl, x->heavy, HM ? 1 : 0, x->sample_keys, M,
-                     (uint32_t)rho_d, (uint32_t)k, x->hist_s);
+                     (uint32_t)rho_d, x->hist_s);
   // with the bitmap in LDS one block fits a CU: launch one per CU so the map is loaded once
   const int pgrid = grid_for(x->d, 4 * kPruneBlock, x->prune_map_in_lds ? x->num_cus : 2 * x->num_cus);
-  const dim3 pb(kPruneBlock);
+#define GS_PRUNED(MAP, LMAP, COARSE)                                                                               \
+  hipLaunchKernelGGL((k_pruned<R, HM, MAP>), dim3(pgrid), dim3(kPruneBlock), 0, s, x->hs, x->d, x->ctl, x->heavy,  \
+                     LMAP, x->prune_map_words, x->heavy_row, COARSE, x->prune_buf_cap, x->keys, x->bitmap, rnd, \
+                     x->hist_s, merged, x->cand_key, x->cand_idx, x->hist_c)
   if (!x->prune_map_in_lds) {
-    hipLaunchKernelGGL((k_pruned<R, HM, kMapGlobal>), dim3(pgrid), pb, 0, s, x->hs, x->d, x->ctl,
-                       x->heavy, x->heavy, x->prune_map_words, x->heavy_row, 0, x->prune_buf_cap, x->keys,
-                       x->bitmap, rnd, x->hist_s);
+    GS_PRUNED(kMapGlobal, x->heavy, 0);
   } else if (x->prune_coarse_log2 > 0) {
     hipLaunchKernelGGL(k_coarse, dim3(grid_for(x->prune_coarse_words, kBlock, 4 * x->num_cus)), dim3(kBlock), 0, s,
                        x->heavy, nbits / 32, x->prune_coarse_log2, x->coarse, x->prune_coarse_words);
-    hipLaunchKernelGGL((k_pruned<R, HM, kMapCoarse>), dim3(pgrid), pb, 0, s, x->hs, x->d, x->ctl,
-                       x->heavy, x->coarse, x->prune_map_words, x->heavy_row, x->prune_coarse_log2,
-                       x->prune_buf_cap, x->keys,
-                       x->bitmap, rnd, x->hist_s);
+    GS_PRUNED(kMapCoarse, x->coarse, x->prune_coarse_log2);
   } else {
-    hipLaunchKernelGGL((k_pruned<R, HM, kMapFine>), dim3(pgrid), pb, 0, s, x->hs, x->d, x->ctl,
-                       x->heavy, x->heavy, x->prune_map_words, x->heavy_row, 0, x->prune_buf_cap, x->keys,
-                       x->bitmap, rnd, x->hist_s);
+    GS_PRUNED(kMapFine, x->heavy, 0);
   }
-  hipLaunchKernelGGL((k_survivors<R, HM>), dim3(2 * x->num_cus), dim3(kSurvBlock), 0, s, x->hs, merged, x->ctl, x->keys,
-                     x->cand_key, x->cand_idx, x->cand_cap, rnd, x->hist_c);
+#undef GS_PRUNED
 }
 
-// digit2 -> select2 -> mark -> emit over the candidates: the pruned pass's (pruned = 1,
-// unless it fell short of k) or the full estimate's dense ones.
-hipError_t launch_select_tail(int64_t d, int num_cus, const SelectBufs& b, hipStream_t s, int64_t k, int pruned,
-                              int32_t* idx) {
+// digit2 (twice for a large dense selection) -> emit over the candidates: the pruned pass's or the
+// full estimate's dense ones.
+hipError_t launch_select_tail(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
+                              const float* merged, const uint32_t* rnd, int64_t k, int pruned, int hm, int32_t* idx,
+                              int64_t* n_heavy, double* l2sq, const GatherArgs* ga) {
+  DigitArgs a{};
+  a.key = b.cand_key;
+  a.idx = pruned ? b.cand_idx : nullptr;
+  a.ctl = b.ctl;
+  a.hist = pruned ? b.hist_c : b.hist;
+  a.out_key = b.keys;
+  a.out_idx = b.stage_idx;
+  a.cap = d;
+  a.bitmap = b.bitmap;
+  a.counts = b.counts;
+  a.merged = merged;
+  a.rnd = rnd;
+  a.d = d;
+  a.range = emit_range(d, num_cus);
+  a.k = (uint32_t)k;
+  a.pruned = pruned;
+  a.hm = hm;
+  // the second digit pass reads fewer keys than every emit workgroup would otherwise read by itself
+  const bool two = !pruned && d > (1 << 20);
+  if (two) a.hist_next = b.hist2;
   // one block (of 1,024 threads) per four CUs for the pruned candidates (a few times k: fewer
-  // blocks each append their staged keys and histogram with fewer atomics that queue at the
-  // same addresses); the full estimate's dense ones (d) get up to 8 * (CUs) blocks (a pruned
-  // pass's fallback keeps the smaller grid)
-  int g2 = std::max(1, num_cus / 4);
-  if (!pruned) g2 = std::max(g2, grid_for(d, 8192, 8 * num_cus));
-  hipLaunchKernelGGL(k_digit2, dim3(g2), dim3(kDigit2Block), 0, s, b.cand_key, b.cand_idx, b.ctl, b.cand_cap, d, b.hist_c,
-                     b.hist, pruned, (uint32_t)k, b.hist2, b.keys, b.stage_idx, b.bitmap);
-  hipLaunchKernelGGL(k_select2, dim3(1), dim3(kSelBlock), 0, s, b.ctl, b.hist2, b.keys, b.stage_idx, b.hist_c, b.hist,
-                     pruned, (uint32_t)k, b.emit_flags, b.emit_blocks);
-  hipLaunchKernelGGL(k_mark, dim3(num_cus), dim3(kBlock), 0, s, b.keys, b.stage_idx, b.ctl, b.bitmap);
-  const int64_t words = (d + 31) / 32;
-  hipLaunchKernelGGL(k_emit, dim3((unsigned)b.emit_blocks), dim3(kSelBlock), 0, s, b.bitmap, words, b.ctl,
-                     b.emit_flags, idx, (uint32_t)k, b.emit_spin);
-  return hipGetLastError();
-}
-
-hipError_t launch_select_tail(gs_ctx* x, hipStream_t s, int64_t k, int pruned, int32_t* idx) {
-  return launch_select_tail(x->d, x->num_cus, select_bufs(x), s, k, pruned, idx);
+  // blocks add their counts with fewer atomics), more where k is large; the full estimate's dense
+  // ones take slices of up to 16,384 keys
+  int64_t g2 = std::max<int64_t>(std::max(1, num_cus / 4), std::min<int64_t>(2 * num_cus, k / 4096));
+  if (!pruned) {
+    const int64_t parts = (a.range + 16383) / 16384;
+    a.slice = ((a.range + parts - 1) / parts + 63) / 64 * 64;
+    a.slices = (uint32_t)parts;
+    g2 = (d + a.range - 1) / a.range * parts;
+  }
+  hipLaunchKernelGGL(k_digit2, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a, hs);
+  if (two) {
+    DigitArgs a1 = a;
+    a1.key = b.keys;
+    a1.idx = b.stage_idx;
+    a1.hist = b.hist2;
+    a1.hist_next = nullptr;
+    a1.out_key = b.stage2;
+    a1.out_idx = reinterpret_cast<int32_t*>(b.stage2 + kStage2Cap);
+    a1.cap = kStage2Cap;
+    a1.level = 1;
+    hipLaunchKernelGGL(k_digit2, dim3(num_cus), dim3(kDigit2Block), 0, s, a1, hs);
+  }
+  return launch_emit(hs, d, num_cus, b, s, merged, k, pruned, two ? 1 : 0, idx, n_heavy, l2sq, ga);
 }
 
 }  // namespace
-
-int64_t emit_blocks_for(int64_t d) {
-  const int64_t words = (d + 31) / 32;
-  return (words + kEmitWordsPerBlock - 1) / kEmitWordsPerBlock;
-}
 
 hipError_t prepare_prune(gs_ctx* x) {
   const int64_t rc = (int64_t)x->r * x->heavy_row;  // bits of the heavy-cell map (padded rows)
@@ -1268,42 +993,45 @@ hipError_t prepare_prune(gs_ctx* x) {
   return hipSuccess;
 }
 
-hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, float* est, int32_t* idx) {
+// Whether a selection without an estimate vector prunes.
+static bool prunes(const gs_ctx* x, const float* est) { return est == nullptr && x->d * x->r > x->prune_min_cells; }
+
+hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, float* est, int32_t* idx,
+                                const GatherArgs* ga) {
   // With an estimate vector requested, or a sketch small enough (d*r at most
   // prune_min_cells) that the full estimate is the cheaper chain, every coordinate is
-  // estimated. Otherwise the pruned path runs and the full estimate only acts if the pruned
-  // candidates fell short of k.
-  const bool prune = est == nullptr && x->d * x->r > x->prune_min_cells;
-  SelectCtl* gate = prune ? x->ctl : nullptr;
+  // estimated. Otherwise the pruned path runs (and the digit pass estimates every coordinate if its
+  // candidates fell short of k).
+  if (!prunes(x, est))
+    return launch_unsketch_topk_dense(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, k, est, idx, ga);
   switch (x->r) {
 #define GS_R_CASE(RR) \
-  case RR:                                            \
-    if (prune) launch_prune_r<RR, false>(x, s, merged, k, nullptr);  \
-    launch_unsketch_r<RR>(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, est, gate);  \
-    break;
+  case RR: launch_prune_r<RR, false>(x, s, merged, k, nullptr); break;
     GS_R_CASE(1) GS_R_CASE(2) GS_R_CASE(3) GS_R_CASE(4) GS_R_CASE(5) GS_R_CASE(6) GS_R_CASE(7) GS_R_CASE(8)
     GS_R_CASE(9) GS_R_CASE(10) GS_R_CASE(11) GS_R_CASE(12) GS_R_CASE(13) GS_R_CASE(14) GS_R_CASE(15) GS_R_CASE(16)
 #undef GS_R_CASE
     default: return hipErrorInvalidValue;
   }
-  return launch_select_tail(x, s, k, prune ? 1 : 0, idx);
+  return launch_select_tail(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, nullptr, k, 1, 0, idx, nullptr,
+                            nullptr, ga);
 }
 
 hipError_t launch_unsketch_topk_dense(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
-                                      const float* merged, int64_t k, float* est, int32_t* idx) {
+                                      const float* merged, int64_t k, float* est, int32_t* idx,
+                                      const GatherArgs* ga) {
   switch (hs.r) {
 #define GS_R_CASE(RR) \
-  case RR: launch_unsketch_r<RR>(hs, d, num_cus, b, s, merged, est, nullptr); break;
+  case RR: launch_unsketch_r<RR>(hs, d, num_cus, b, s, merged, est); break;
     GS_R_CASE(1) GS_R_CASE(2) GS_R_CASE(3) GS_R_CASE(4) GS_R_CASE(5) GS_R_CASE(6) GS_R_CASE(7) GS_R_CASE(8)
     GS_R_CASE(9) GS_R_CASE(10) GS_R_CASE(11) GS_R_CASE(12) GS_R_CASE(13) GS_R_CASE(14) GS_R_CASE(15) GS_R_CASE(16)
 #undef GS_R_CASE
     default: return hipErrorInvalidValue;
   }
-  return launch_select_tail(d, num_cus, b, s, k, 0, idx);
+  return launch_select_tail(hs, d, num_cus, b, s, merged, nullptr, k, 0, 0, idx, nullptr, nullptr, ga);
 }
 
 hipError_t launch_heavymix_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, const uint32_t* rnd,
-                                float* est, int32_t* idx, int64_t* n_heavy, double* l2sq) {
+                                float* est, int32_t* idx, int64_t* n_heavy, double* l2sq, const GatherArgs* ga) {
   // row sums of squares, pass by pass (each reduces aligned groups of up to 2048 values)
   const int64_t npad = l2_pad(x->c);
   int64_t n = npad;
@@ -1323,22 +1051,23 @@ hipError_t launch_heavymix_topk(gs_ctx* x, hipStream_t s, const float* merged, i
   hipLaunchKernelGGL(k_theta, dim3(1), dim3(64), 0, s, in, x->r, k, x->ctl);
   // As in launch_unsketch_topk: the full estimate with an estimate vector or a small sketch,
   // else the pruned pass, with the full one acting only if its candidates fell short of k.
-  const bool prune = est == nullptr && x->d * x->r > x->prune_min_cells;
+  const bool prune = prunes(x, est);
   switch (x->r) {
-#define GS_R_CASE(RR)                                                                                              \
-  case RR:                                                                                                         \
-    if (prune) launch_prune_r<RR, true>(x, s, merged, k, rnd);                                                     \
-    hipLaunchKernelGGL(k_unsketch_hm<RR>, dim3(grid_for(x->d, kBlock, 4 * x->num_cus)), dim3(kBlock), 0, s, x->hs, \
-                       merged, x->d, rnd, est, x->cand_key, x->hist, x->bitmap, x->ctl, prune ? 1 : 0,            \
-                       prune ? 0 : 1);                                                                             \
+#define GS_R_CASE(RR)                                                                                                \
+  case RR:                                                                                                           \
+    if (prune)                                                                                                       \
+      launch_prune_r<RR, true>(x, s, merged, k, rnd);                                                                \
+    else                                                                                                             \
+      hipLaunchKernelGGL(k_unsketch_hm<RR>, dim3(grid_for(x->d, kBlock, 4 * x->num_cus)), dim3(kBlock), 0, s, x->hs, \
+                         merged, x->d, rnd, est, x->cand_key, x->hist, x->ctl);                                      \
     break;
     GS_R_CASE(1) GS_R_CASE(2) GS_R_CASE(3) GS_R_CASE(4) GS_R_CASE(5) GS_R_CASE(6) GS_R_CASE(7) GS_R_CASE(8)
     GS_R_CASE(9) GS_R_CASE(10) GS_R_CASE(11) GS_R_CASE(12) GS_R_CASE(13) GS_R_CASE(14) GS_R_CASE(15) GS_R_CASE(16)
 #undef GS_R_CASE
     default: return hipErrorInvalidValue;
   }
-  if (n_heavy || l2sq) hipLaunchKernelGGL(k_hm_out, dim3(1), dim3(64), 0, s, x->ctl, n_heavy, l2sq);
-  return launch_select_tail(x, s, k, prune ? 1 : 0, idx);
+  return launch_select_tail(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, rnd, k, prune ? 1 : 0, 1, idx,
+                            n_heavy, l2sq, ga);
 }
 
 int64_t l2_pad(int64_t c) {

@@ -8,9 +8,9 @@
 //   Delta_i = estimate of E at i, for i in Top_k               (the step's values)
 //   E <- fl(E - D) on every cell D touches, D = S(Delta) summed per cell in fp64 and
 //        rounded once; U <- 0 on those cells when momentum is reset
-// The subtraction runs in three passes over the k*r (coordinate, row) pairs: clear the
-// touched cells' fp64 accumulators and claim bits, add the signed values (fp64 atomics),
-// and let the first pair to claim each cell apply it.
+// The selection's last kernel writes the values and clears the touched cells' fp64 accumulators
+// and claim bits; two passes over the k*r (coordinate, row) pairs follow: add the signed values
+// (fp64 atomics), and let the first pair to claim each cell apply it.
 #include "gs_internal.hpp"
 
 namespace gs {
@@ -36,18 +36,6 @@ __global__ void __launch_bounds__(kBlock) k_sketch_mom(const float* __restrict__
   }
 }
 
-template <int R>
-__global__ void __launch_bounds__(kBlock) k_values_at(HashSet hs, const float* __restrict__ E,
-                                                      const int32_t* __restrict__ idx, int64_t k,
-                                                      float* __restrict__ values) {
-  RowConst kr[R];
-#pragma unroll
-  for (int j = 0; j < R; ++j) kr[j] = row_const(hs, j);
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < k; t += stride)
-    values[t] = estimate_val<R>(kr, E, (uint32_t)idx[t]);
-}
-
 // Pair p = t * r + j: row j of selected coordinate idx[t].
 __device__ __forceinline__ int64_t pair_cell(const HashSet& hs, const int32_t* __restrict__ idx, int64_t p,
                                              uint32_t& sflip) {
@@ -56,17 +44,6 @@ __device__ __forceinline__ int64_t pair_cell(const HashSet& hs, const int32_t* _
   uint32_t col;
   hash_ij(hs, j, (uint32_t)idx[t], col, sflip);
   return (int64_t)j * hs.c + col;
-}
-
-__global__ void __launch_bounds__(kBlock) k_sub_clear(HashSet hs, const int32_t* __restrict__ idx, int64_t n_pairs,
-                                                      double* __restrict__ acc, uint32_t* __restrict__ claim) {
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x; p < n_pairs; p += stride) {
-    uint32_t sflip;
-    const int64_t cell = pair_cell(hs, idx, p, sflip);
-    acc[cell] = 0.0;
-    atomicAnd(&claim[cell >> 5], ~(1u << (cell & 31)));
-  }
 }
 
 __global__ void __launch_bounds__(kBlock) k_sub_add(HashSet hs, const int32_t* __restrict__ idx, int64_t n_pairs,
@@ -102,26 +79,22 @@ hipError_t launch_sketch_state(gs_ctx* x, hipStream_t s, const float* merged, fl
   const int64_t rc = (int64_t)x->r * x->c;
   hipLaunchKernelGGL(k_sketch_mom, dim3(grid_for(rc, kBlock, 8 * x->num_cus)), dim3(kBlock), 0, s, merged, U, E, rc,
                      x->rho);
-  hipError_t e = launch_unsketch_topk(x, s, E, k, nullptr, idx);
+  // fp64 cell accumulators and claim bits: context scratch free once the selection is made; its
+  // last kernel writes the values and clears those of the cells the selection touches
+  GatherArgs ga{};
+  ga.op = kGatherSketch;
+  ga.gl = 1;
+  ga.values = values;
+  ga.acc = x->use_pull ? x->partial : x->acc64;
+  ga.claim = x->heavy;
+  const hipError_t e = launch_unsketch_topk(x, s, E, k, nullptr, idx, &ga);
   stage_mark(x, s, 4);
   if (e != hipSuccess) return e;
-  const dim3 gk(grid_for(k, kBlock, 4 * x->num_cus)), block(kBlock);
-  switch (x->r) {
-#define GS_R_CASE(RR) \
-  case RR: hipLaunchKernelGGL(k_values_at<RR>, gk, block, 0, s, x->hs, E, idx, k, values); break;
-    GS_R_CASE(1) GS_R_CASE(2) GS_R_CASE(3) GS_R_CASE(4) GS_R_CASE(5) GS_R_CASE(6) GS_R_CASE(7) GS_R_CASE(8)
-    GS_R_CASE(9) GS_R_CASE(10) GS_R_CASE(11) GS_R_CASE(12) GS_R_CASE(13) GS_R_CASE(14) GS_R_CASE(15) GS_R_CASE(16)
-#undef GS_R_CASE
-    default: return hipErrorInvalidValue;
-  }
-  // fp64 cell accumulators and claim bits: context scratch free at this point of the step
-  double* acc = x->use_pull ? x->partial : x->acc64;
-  uint32_t* claim = x->heavy;
+  const dim3 block(kBlock);
   const int64_t n_pairs = k * x->r;
   const dim3 gp(grid_for(n_pairs, kBlock, 8 * x->num_cus));
-  hipLaunchKernelGGL(k_sub_clear, gp, block, 0, s, x->hs, idx, n_pairs, acc, claim);
-  hipLaunchKernelGGL(k_sub_add, gp, block, 0, s, x->hs, idx, n_pairs, values, acc);
-  hipLaunchKernelGGL(k_sub_apply, gp, block, 0, s, x->hs, idx, n_pairs, acc, claim, U, E, x->reset_momentum);
+  hipLaunchKernelGGL(k_sub_add, gp, block, 0, s, x->hs, idx, n_pairs, values, ga.acc);
+  hipLaunchKernelGGL(k_sub_apply, gp, block, 0, s, x->hs, idx, n_pairs, ga.acc, ga.claim, U, E, x->reset_momentum);
   stage_mark(x, s, 5);
   return hipGetLastError();
 }

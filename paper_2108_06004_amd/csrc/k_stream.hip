@@ -1,5 +1,5 @@
 // k_stream.hip -- streaming kernels of the hot path: accumulation, table clearing, Count
-// Sketch insertion, binomial-tree merge, exact-value gather with reset.
+// Sketch insertion, binomial-tree merge, weight update.
 #include "gs_internal.hpp"
 
 namespace gs {
@@ -352,84 +352,6 @@ __global__ void __launch_bounds__(kBlock) k_merge64_dyn(const double* __restrict
 }
 
 // ------------------------------------------------------------------------------------
-// Exact values of the selected coordinates and their reset (Alg. 2, second round).
-
-// Interleaved state: GL lanes (a power of two, at least PP/4) share a coordinate, lane sub
-// holding the row's 16-byte piece of workers 4 sub .. 4 sub + 3. A row is then one coalesced
-// access of v and one of each cleared array; one lane per coordinate walked its row 4 bytes at a
-// time (2M x 32, k = 20,000: 25.8 us, 66M x 16, k = 66,000: 21.9 us). The tree runs in the
-// lane's own four (strides 1, 2), then across lanes (strides 4, 8, ... workers); an element
-// absorbs its partner only if that worker exists, so the sums are those of tree_sum.
-template <int GL>
-__global__ void __launch_bounds__(kBlock) k_gather_reset_il(const int32_t* __restrict__ idx, int64_t k,
-                                                            float* __restrict__ u, float* __restrict__ v,
-                                                            float* __restrict__ values, int P, int PP, int reset_u) {
-  const int sub = threadIdx.x % GL;
-  const int nw = P - 4 * sub;  // workers from this lane's first one on
-  const int64_t stride = (int64_t)gridDim.x * (kBlock / GL);
-  // the shuffles below read lanes of the same coordinate, which leave the loop together
-  for (int64_t t = (int64_t)blockIdx.x * (kBlock / GL) + threadIdx.x / GL; t < k; t += stride) {
-    const int64_t o = (int64_t)idx[t] * PP + 4 * sub;
-    f4 x = {0.f, 0.f, 0.f, 0.f};
-    if (nw > 0) x = *reinterpret_cast<const f4*>(v + o);
-    if (nw > 1) x.x = x.x + x.y;
-    if (nw > 3) x.z = x.z + x.w;
-    float y = nw > 2 ? x.x + x.z : x.x;
-#pragma unroll
-    for (int s = 1; s < GL; s <<= 1) {
-      const float z = __shfl_down(y, s, GL);
-      if (nw > 4 * s) y = y + z;
-    }
-    if (sub == 0) values[t] = y;
-    const f4 zero = {0.f, 0.f, 0.f, 0.f};
-    if (nw >= 4) {
-      *reinterpret_cast<f4*>(v + o) = zero;
-      if (reset_u) *reinterpret_cast<f4*>(u + o) = zero;
-    } else {
-      for (int q = 0; q < nw; ++q) {  // the row's padding is not written
-        v[o + q] = 0.f;
-        if (reset_u) u[o + q] = 0.f;
-      }
-    }
-  }
-}
-
-template <int P>
-__global__ void __launch_bounds__(kBlock) k_gather_reset(const int32_t* __restrict__ idx, int64_t k,
-                                                         float* __restrict__ u, float* __restrict__ v,
-                                                         float* __restrict__ values, StateView sv, int reset_u) {
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < k; t += stride) {
-    const int64_t i = idx[t];
-    float x[P];
-#pragma unroll
-    for (int q = 0; q < P; ++q) x[q] = v[sv.at(q, i)];
-    values[t] = tree_sum<P>(x);
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      v[sv.at(q, i)] = 0.f;
-      if (reset_u) u[sv.at(q, i)] = 0.f;
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kBlock) k_gather_reset_dyn(const int32_t* __restrict__ idx, int64_t k,
-                                                             float* __restrict__ u, float* __restrict__ v,
-                                                             float* __restrict__ values, StateView sv, int reset_u,
-                                                             int P) {
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < k; t += stride) {
-    const int64_t i = idx[t];
-    float x[kMaxWorkers];
-    for (int q = 0; q < P; ++q) x[q] = v[sv.at(q, i)];
-    values[t] = tree_sum_dyn(x, P);
-    for (int q = 0; q < P; ++q) {
-      v[sv.at(q, i)] = 0.f;
-      if (reset_u) u[sv.at(q, i)] = 0.f;
-    }
-  }
-}
-
 // Weight update of the selected coordinates (Alg. 1, last step): w[idx[t]] -= lr * values[t],
 // the product and the difference each rounded (no fused multiply-add).
 __global__ void __launch_bounds__(kBlock) k_apply_update(const int32_t* __restrict__ idx,
@@ -557,37 +479,6 @@ hipError_t launch_merge_acc(const gs_ctx* x, hipStream_t s, float* merged) {
     GS_MERGE_CASE(13) GS_MERGE_CASE(14) GS_MERGE_CASE(15) GS_MERGE_CASE(16)
 #undef GS_MERGE_CASE
     default: hipLaunchKernelGGL(k_merge64_dyn, grid, block, 0, s, x->acc64, merged, rc, x->P); break;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_reset(const gs_ctx* x, hipStream_t s, const int32_t* idx, int64_t k, float* u, float* v,
-                               float* values) {
-  const dim3 grid(grid_for(k, kBlock, 4 * x->num_cus)), block(kBlock);
-  const int ru = x->reset_momentum ? 1 : 0;
-  const StateView sv = state_view(x);
-  if (x->state_layout == GS_STATE_INTERLEAVED && aligned16(u) && aligned16(v)) {
-    const int G = x->state_stride / 4;
-    const int gl = G <= 1 ? 1 : G <= 2 ? 2 : G <= 4 ? 4 : G <= 8 ? 8 : 16;
-    const dim3 gi(grid_for(k, kBlock / gl, 8 * x->num_cus));
-    switch (gl) {
-#define GS_GATHER_IL(GL)                                                                                      \
-  case GL:                                                                                                    \
-    hipLaunchKernelGGL(k_gather_reset_il<GL>, gi, block, 0, s, idx, k, u, v, values, x->P, x->state_stride, ru); \
-    break;
-      GS_GATHER_IL(1) GS_GATHER_IL(2) GS_GATHER_IL(4) GS_GATHER_IL(8) GS_GATHER_IL(16)
-#undef GS_GATHER_IL
-    }
-    return hipGetLastError();
-  }
-  switch (x->P) {
-#define GS_GATHER_CASE(PP) \
-  case PP: hipLaunchKernelGGL(k_gather_reset<PP>, grid, block, 0, s, idx, k, u, v, values, sv, ru); break;
-    GS_GATHER_CASE(1) GS_GATHER_CASE(2) GS_GATHER_CASE(3) GS_GATHER_CASE(4) GS_GATHER_CASE(5) GS_GATHER_CASE(6)
-    GS_GATHER_CASE(7) GS_GATHER_CASE(8) GS_GATHER_CASE(9) GS_GATHER_CASE(10) GS_GATHER_CASE(11) GS_GATHER_CASE(12)
-    GS_GATHER_CASE(13) GS_GATHER_CASE(14) GS_GATHER_CASE(15) GS_GATHER_CASE(16)
-#undef GS_GATHER_CASE
-    default: hipLaunchKernelGGL(k_gather_reset_dyn, grid, block, 0, s, idx, k, u, v, values, sv, ru, x->P); break;
   }
   return hipGetLastError();
 }
