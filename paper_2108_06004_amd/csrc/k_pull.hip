@@ -41,6 +41,7 @@ constexpr bool pull_pipelined(int PP, bool flat) { return flat || PP >= 16; }
 // two lanes are 24 apart and four lanes hit distinct pairs; beyond four lanes pad 1 spaces eight
 // lanes by four pairs, all distinct, where pad 6 would pair them up.
 __host__ __device__ constexpr int tile_pad(int PP) { return PP > 16 ? 1 : 6; }
+constexpr int kCuLds = 160 * 1024;
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 int grid_for(int64_t work_items, int per_block, int cap) {
@@ -458,7 +459,7 @@ __device__ __forceinline__ f4 load_quad(const float* __restrict__ v, uint32_t i,
 }
 
 // NP > 0: P = NP workers, fixed at compile time; NP = 0 (P > 16): P = pl.P <= PP at run time.
-template <int NP, int U, bool PK, bool FLAT, int PP = (NP + 3) / 4 * 4>
+template <int NP, int U, bool PK, bool FLAT, int PP = (NP + 3) / 4 * 4, bool NT = false>
 __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, const uint32_t* __restrict__ list,
                                                      const uint16_t* __restrict__ codes,
                                                      const uint32_t* __restrict__ bases,
@@ -507,7 +508,7 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
 #pragma unroll
     for (int m = 0; m < U; ++m) {
       const int64_t e = ebx + m * B;
-      wn[m] = list[e];
+      wn[m] = NT ? __builtin_nontemporal_load(list + e) : list[e];
       if constexpr (PK && (L & (L - 1)) == 0) {
         static_assert(B % (64 / L) == 0 && kListGroup % (64 / L) == 0, "a wave's entries must share a group");
         // e0 is group-aligned, B is a multiple of 64 / L and a wave's lanes take 64 / L
@@ -553,6 +554,10 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
     f4 x[U];
 #pragma unroll
     for (int m = 0; m < U; ++m) x[m] = load_quad<PP, FLAT>(vI, i[m], sub);
+    // every row load of the pass issued before the first add is scheduled (40M x 2, one hash seed
+    // 735 -> 623 us, another 677 -> 671; 25.6M x 2 632 -> 587; 14.7M x 4 350 -> 342; 25.6M x 8 718
+    // -> 708 and 699 -> 691 us; four lanes per entry unchanged)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < U; ++m) {
       double* cell = mycol + tile_cell(pos[m], swz);
@@ -700,12 +705,26 @@ size_t tile_lds_bytes(const PullPlan& pl) {
   return (size_t)(((pl.W + 31) & ~31) + tile_pad(pl.PP)) * pl.P * sizeof(double);
 }
 
+// Lists read with non-temporal loads: those that outgrow the 256 MB Infinity Cache, so that no step
+// would find them there, with one lane per entry (14.7M x 4: 394 -> 367 us, 25.6M x 1: 208 -> 196
+// us, 25.6M x 2: 650 -> 635 us). Smaller lists stay cached from step to step (3M x 8: 83 -> 85 us
+// with non-temporal loads), and with several lanes per entry nothing changed (25.6M x 8) or it
+// was slower (22M x 12, 66M x 16: 1%).
+template <int PP>
+bool streamed_lists(const gs_ctx* x) {
+  return PP == 4 && x->list_cap * (int64_t)sizeof(uint32_t) > 256ll << 20;
+}
+
 template <int NP, bool FLAT = false, int PP = (NP + 3) / 4 * 4>
 void launch_pull_p(const gs_ctx* x, hipStream_t s, const float* rows, float* merged, float* tables) {
   const PullPlan& pl = x->plan;
   const dim3 grid((unsigned)((int64_t)pl.T * pl.S)), block(kPullBlock);
   const size_t lds = tile_lds_bytes(pl);
-  if (pl.packed)
+  constexpr bool NT = PP == 4;  // the form with non-temporal list loads exists for these only
+  if (pl.packed && streamed_lists<PP>(x))
+    hipLaunchKernelGGL((k_pull<NP, pull_unroll(PP), true, FLAT, PP, NT>), grid, block, lds, s, x->hs, pl, x->list,
+                       x->codes, x->bases, x->tile_off, x->tile_n, rows, x->partial, merged, tables);
+  else if (pl.packed)
     hipLaunchKernelGGL((k_pull<NP, pull_unroll(PP), true, FLAT, PP>), grid, block, lds, s, x->hs, pl, x->list, x->codes,
                        x->bases, x->tile_off, x->tile_n, rows, x->partial, merged, tables);
   else
@@ -715,12 +734,14 @@ void launch_pull_p(const gs_ctx* x, hipStream_t s, const float* rows, float* mer
 
 template <int NP, bool FLAT = false, int PP = (NP + 3) / 4 * 4>
 hipError_t allow_pull_lds(size_t bytes) {
-  const hipError_t e =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pull<NP, pull_unroll(PP), true, FLAT, PP>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pull<NP, pull_unroll(PP), false, FLAT, PP>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  const void* forms[] = {reinterpret_cast<const void*>(&k_pull<NP, pull_unroll(PP), true, FLAT, PP>),
+                         reinterpret_cast<const void*>(&k_pull<NP, pull_unroll(PP), true, FLAT, PP, PP == 4>),
+                         reinterpret_cast<const void*>(&k_pull<NP, pull_unroll(PP), false, FLAT, PP>)};
+  for (const void* f : forms) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace
@@ -837,7 +858,7 @@ PullPlan make_pull_plan(const HashSet& hs, int64_t d, int32_t P, int32_t r, int6
   // Tiles hold W columns x P workers of fp64 accumulators. Up to kTilesPerCu tiles of at
   // most 160 KiB / kTilesPerCu share a CU; W is then shrunk so that the tiles fill whole
   // rounds of resident workgroups (no ragged last round), or one round as fully as it can.
-  const int64_t cu_lds = 160 * 1024;
+  const int64_t cu_lds = kCuLds;
   int64_t max_w = (cu_lds / kTilesPerCu) / (8 * (int64_t)P) - 6;
   if (max_w >= 32) max_w &= ~31ll;  // a worker's column of cells is W rounded up to 32, plus 6
   int64_t W = max_w < 1 ? 1 : max_w;
