@@ -152,10 +152,15 @@ def stage_kernels(w, layout: str = "interleaved", plan: dict = None) -> dict:
     # the full estimate's form: two coordinates per thread per pass up to 8 * 256 * (CUs)
     unsketch = f"k_unsketch<{w.r}, {2 if w.d <= 8 * 256 * num_cus() else 1}>"
     if w.d * w.r > 2_000_000:  # pruned selection (the library's choice above 2,000,000 cells of d*r)
-        rows = w.r * -(-w.c // 64) * 64  # bits of the heavy-cell map
-        fine = 160 * 1024 - 256 - rows // 8 >= 4 * 512
-        select = [f"k_sample<{w.r}, false>", "k_heavy"] + ([] if fine else ["k_coarse"]) + \
-            [f"k_pruned<{w.r}, false, {0 if fine else 1}>"] + tail
+        row = -(-w.c // 128) * 128  # cells of a row of the heavy-cell map
+        if (160 * 1024 - 256 - w.r * row // 8) // 4 >= 512:  # all rows fit the LDS beside the queue buffer
+            lookups = [f"k_pruned<{w.r}, false, 0>"]
+        elif w.r < 4 or row > 2 * ((160 * 1024 // 4 - 64) * 32 - 128):  # all rows folded
+            lookups = ["k_coarse", f"k_pruned<{w.r}, false, 1>"]
+        else:  # row by row, a row of more cells than the LDS has bits folded
+            lookups = [f"k_planes<{'true' if row > (160 * 1024 // 4 - 64) * 32 else 'false'}>",
+                       f"k_combine<{w.r}, false>"]
+        select = [f"k_sample<{w.r}, false>", "k_heavy"] + lookups + tail
     else:  # every coordinate estimated
         select = [unsketch] + tail
     segmented = plan["segments"] > 1 if plan is not None else w.d <= 1_000_000

@@ -39,7 +39,7 @@ void free_scratch(gs_ctx* x) {
   void* ptrs[] = {x->keys,     x->hist,     x->hist2,       x->hist_s, x->hist_c, x->ctl,     x->stage_idx,
                   x->cand_key, x->cand_idx, x->bitmap,      x->counts, x->stage2, x->acc64, x->list,  x->codes,
                   x->bases,    x->tile_off, x->tile_n,      x->vI,     x->partial, x->sample_keys,
-                  x->heavy,    x->l2buf,    x->coarse};
+                  x->heavy,    x->l2buf,    x->planes, x->coarse};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   x->keys = nullptr;
@@ -65,6 +65,7 @@ void free_scratch(gs_ctx* x) {
   x->sample_keys = nullptr;
   x->heavy = nullptr;
   x->l2buf = nullptr;
+  x->planes = nullptr;
   x->coarse = nullptr;
 }
 
@@ -201,7 +202,7 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
   chk(alloc(&x->counts, ranges));
   chk(alloc(&x->stage2, 2 * gs::kStage2Cap));
   chk(alloc(&x->sample_keys, gs::kSampleMax));
-  x->heavy_row = (x->c + 63) / 64 * 64;
+  x->heavy_row = (x->c + 127) / 128 * 128;
   chk(alloc(&x->heavy, (int64_t)x->r * x->heavy_row / 32));
   {
     const int64_t npad = gs::l2_pad(x->c);

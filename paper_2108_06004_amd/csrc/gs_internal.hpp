@@ -142,12 +142,15 @@ struct gs_ctx {
   uint32_t* counts = nullptr;     // [emit ranges] taken keys of each range, zero between calls
   uint32_t* sample_keys = nullptr;  // [kSampleMax]
   uint32_t* heavy = nullptr;        // [r * heavy_row / 32] heavy-cell bitmap, rows padded to heavy_row bits
-  int64_t heavy_row = 0;            // c rounded up to a multiple of 64: bit j * heavy_row + col is cell (j, col)
+  int64_t heavy_row = 0;            // c rounded up to a multiple of 128: bit j * heavy_row + col is cell (j, col)
   int64_t prune_map_words = 0;      // words of the heavy bitmap
   int prune_map_in_lds = 0;         // 1: the pruned pass keeps a bitmap in LDS (fine, or coarse below)
   int prune_coarse_log2 = 0;        // > 0: LDS holds the coarse map, one bit per 2^this cells
   uint32_t* coarse = nullptr;       // coarse heavy-cell map (bit = OR of its cells' heavy bits)
-  int64_t prune_coarse_words = 0;
+  uint64_t* planes = nullptr;       // [r][ceil(d/64)] heavy bit of every coordinate per row, where they are
+                                    // looked up row by row
+  int64_t plane_fine = 0;           // cells of a row with a bit of their own; the others share one, 2^fold to a bit
+  int plane_fold = 0;
   int prune_buf_cap = 0;            // LDS candidate buffer entries of the pruned pass
   // selections without an estimate vector prune when d*r exceeds this (0: always); below it
   // the full estimate takes fewer launches than the pruned pass's chain

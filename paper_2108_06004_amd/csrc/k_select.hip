@@ -366,7 +366,7 @@ __device__ uint32_t sampled_bound(const uint32_t* __restrict__ sample, int M, ui
   return (pre << 10) | res[0];
 }
 
-// Heavy-cell bitmap: bit j * hrow + col (rows padded to hrow bits, a multiple of 64, so a
+// Heavy-cell bitmap: bit j * hrow + col (rows padded to hrow bits, a multiple of 128, so a
 // row starts on a word) is |merged[j][col]| >= tau0, or (HEAVYMIX,
 // hm = 1) merged[j][col]^2 >= theta in fp64 (one ballot per 64 cells); with hm the sampled fill
 // bound tau0 is still found here, for the pruned pass. A coordinate with
@@ -480,6 +480,116 @@ __device__ __forceinline__ int64_t map_words_in_lds(int64_t map_words) {
 
 // Bit e & 31 of word w (the hardware takes the low five bits of the offset).
 __device__ __forceinline__ uint32_t bit_at(uint32_t w, uint32_t e) { return __builtin_amdgcn_ubfe(w, e, 1u); }
+
+// Phase 2: exact estimates of the workgroup's survivors queue[0, qn), candidates appended and
+// binned. sm: kSurvWords words of LDS, free (a barrier before). kPruneBlock threads.
+constexpr int kSurvWords = kDigit1Bins + 2 * kSurvBuf + 3;
+template <int R, bool HM>
+__device__ __forceinline__ void estimate_survivors(uint32_t* sm, const RowConst (&kr)[R],
+                                                   const float* __restrict__ merged, SelectCtl* __restrict__ ctl,
+                                                   uint32_t tau0, const uint32_t* queue, int64_t qn,
+                                                   const uint32_t* __restrict__ rnd, uint32_t* __restrict__ cand_key,
+                                                   int32_t* __restrict__ cand_idx, uint32_t* __restrict__ hist_c,
+                                                   const uint32_t* __restrict__ confirm = nullptr,
+                                                   int64_t hrow = 0) {
+  constexpr int V = 2;  // survivors per thread and pass, all their cell loads in flight
+  uint32_t* const h = sm;
+  uint32_t* const bkey = sm + kDigit1Bins;
+  int32_t* const bidx = reinterpret_cast<int32_t*>(bkey + kSurvBuf);
+  uint32_t& cn = sm[kDigit1Bins + 2 * kSurvBuf];
+  uint32_t& cbase = sm[kDigit1Bins + 2 * kSurvBuf + 1];
+  uint32_t& nheavy = sm[kDigit1Bins + 2 * kSurvBuf + 2];
+  for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) h[b] = 0u;
+  if (threadIdx.x == 0) {
+    cn = 0u;
+    nheavy = 0u;
+  }
+  __syncthreads();
+  const double theta = HM ? ctl->theta : 0.0;
+  const CandBins bins = cand_bins(tau0, HM, theta, true);
+  const int lane = threadIdx.x & 63;
+  uint32_t mine = 0;
+  for (int64_t t0 = 0; t0 < qn; t0 += V * kPruneBlock) {  // block-uniform
+    uint32_t ii[V], key[V];
+    float e[V];
+    bool cand[V];
+#pragma unroll
+    for (int m = 0; m < V; ++m) {
+      const int64_t t = t0 + m * kPruneBlock + threadIdx.x;
+      cand[m] = t < qn;
+      ii[m] = cand[m] ? queue[t] : 0u;  // coordinate 0 stands in past the end (in range)
+    }
+    if (confirm) {
+      // folded heavy bits let coordinates through that have too few heavy cells: their cells' own
+      // bits (a map that stays in the L2s) are read first, and only what passes reads the table
+#pragma unroll
+      for (int m = 0; m < V; ++m) {
+        uint32_t n = 0u;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          uint32_t col, sflip;
+          hash_row(kr[j], ii[m], col, sflip);
+          n += bit_at(confirm[j * (hrow >> 5) + (col >> 5)], col);
+        }
+        bool pass = n >= (uint32_t)(R + 1) / 2;
+        if constexpr (HM) pass = pass || rnd[ii[m]] >> 1 >= tau0;
+        cand[m] = cand[m] && pass;
+      }
+#pragma unroll
+      for (int m = 0; m < V; ++m) e[m] = cand[m] ? estimate_val<R>(kr, merged, ii[m]) : 0.f;
+    } else {
+#pragma unroll
+      for (int m = 0; m < V; ++m) e[m] = estimate_val<R>(kr, merged, ii[m]);
+    }
+#pragma unroll
+    for (int m = 0; m < V; ++m) {
+      if constexpr (HM) {
+        const bool hv = cand[m] && (double)e[m] * (double)e[m] >= theta;
+        key[m] = hv ? (0x80000000u | abs_key(e[m])) : (cand[m] ? rnd[ii[m]] >> 1 : 0u);
+        cand[m] = hv || (cand[m] && key[m] >= tau0);
+        mine += hv ? 1u : 0u;
+      } else {
+        key[m] = abs_key(e[m]);
+        cand[m] = cand[m] && key[m] >= tau0;
+      }
+      hist_add(h, cand[m], cand_bin(bins, key[m]));
+      // one LDS atomic per wave; at most V * kPruneBlock entries a pass, and the buffer, flushed
+      // whenever it is half full, holds twice that
+      const uint64_t bal = __ballot(cand[m]);
+      uint32_t wbase = 0u;
+      if (lane == 0 && bal) wbase = atomicAdd(&cn, (uint32_t)__popcll(bal));
+      wbase = __shfl(wbase, 0);
+      if (cand[m]) {
+        const uint32_t pos = wbase + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+        bkey[pos] = key[m];
+        bidx[pos] = (int32_t)ii[m];
+      }
+    }
+    __syncthreads();
+    const uint32_t nb = cn;
+    if (nb >= (uint32_t)(kSurvBuf / 2) || (t0 + V * kPruneBlock >= qn && nb > 0)) {
+      if (threadIdx.x == 0) cbase = atomicAdd(&ctl->n_cand, nb);
+      __syncthreads();
+      const int64_t g0 = cbase;
+      for (uint32_t t = threadIdx.x; t < nb; t += kPruneBlock) {
+        cand_key[g0 + t] = bkey[t];
+        cand_idx[g0 + t] = bidx[t];
+      }
+      __syncthreads();
+      if (threadIdx.x == 0) cn = 0u;
+    }
+    __syncthreads();
+  }
+  if constexpr (HM) {
+    if (mine) atomicAdd(&nheavy, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && nheavy) atomicAdd(&ctl->n_heavy, (unsigned long long)nheavy);
+  }
+  for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) {
+    const uint32_t c = h[b];
+    if (c) atomicAdd(&hist_c[b], c);
+  }
+}
 
 template <int R, bool HM, int MAP>
 __global__ void __launch_bounds__(kPruneBlock) k_pruned(HashSet hs, int64_t d, SelectCtl* __restrict__ ctl,
@@ -657,84 +767,209 @@ __global__ void __launch_bounds__(kPruneBlock) k_pruned(HashSet hs, int64_t d, S
     __syncthreads();
   }
 
-  // Phase 2: the map's LDS now holds the candidates' histogram and append buffer.
-  constexpr int V = 2;  // survivors per thread and pass, all their cell loads in flight
-  uint32_t* const h = sm;
-  uint32_t* const bkey = sm + kDigit1Bins;
-  int32_t* const bidx = reinterpret_cast<int32_t*>(bkey + kSurvBuf);
-  uint32_t& cn = sm[kDigit1Bins + 2 * kSurvBuf];
-  uint32_t& cbase = sm[kDigit1Bins + 2 * kSurvBuf + 1];
-  uint32_t& nheavy = sm[kDigit1Bins + 2 * kSurvBuf + 2];
-  for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) h[b] = 0u;
-  if (threadIdx.x == 0) {
-    cn = 0u;
-    nheavy = 0u;
+  estimate_survivors<R, HM>(sm, kr, merged, ctl, tau0, queue, qn, rnd, cand_key, cand_idx, hist_c);
+}
+
+// The pruned pass where the heavy bits of all rows outgrow a CU's LDS (1.3M cells): k_planes looks
+// up one row per workgroup (the workgroups are dealt over the rows), whose bits do fit or nearly,
+// and writes the row's bit of every coordinate as a bit plane (d/8 bytes); k_combine counts the r
+// bits of 32 coordinates at a time and estimates the survivors. A row of more than kPlaneBits cells
+// keeps its first `fine` cells one bit each and folds the rest, 2^fold cells to a bit that is set
+// when any of them is heavy, so that the row fits exactly: a folded bit can only add survivors,
+// whose estimate decides.
+// Against k_pruned with all rows folded 8 to 32 cells to a bit, where most coordinates have
+// to confirm their set bits in the global map and the pass is bound by L2 requests (66M x 16,
+// r = 7: 69% of the folded bits set, 161M requests): the selection takes 448 against 891 us there,
+// 138 against 158 at 14.7M x 4 (c = 1.47M), 120 against 166 at 20M x 2 (c = 600,000), 262 against 314 at
+// 22M x 12 (c = 2.05M, k = 0.5%). It is used while a row is folded by two at most and for four rows or
+// more: folded by four it lost (50M x 2, r = 7, c = 5M: 1,571 against 1,237 us), and with three rows it
+// gained nothing (15M x 4, c = 1.5M: 136 against 131 us).
+constexpr int64_t kPlaneBits = (kPruneLdsWords - 64) / 4 * 4 * 32ll;
+
+template <bool FOLD>
+__global__ void __launch_bounds__(kPruneBlock) k_planes(HashSet hs, int64_t d, const uint32_t* __restrict__ heavy,
+                                                        int64_t hrow, int64_t fine, int fold,
+                                                        uint64_t* __restrict__ planes, int64_t plane_words,
+                                                        uint32_t* __restrict__ hist_s) {
+  constexpr int U = 8;  // coordinates per lane per pass
+  __shared__ uint32_t sm[kPruneLdsWords];
+  if (blockIdx.x == 0)  // the samples' histogram, read by k_heavy, cleared for the next call
+    for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) hist_s[b] = 0u;
+  const int j = blockIdx.x % hs.r;
+  const int64_t part = blockIdx.x / hs.r, parts = gridDim.x / hs.r;
+  const uint32_t* src = heavy + j * (hrow >> 5);  // 16-byte aligned: rows are padded to 128 cells
+  const int64_t f4 = fine >> 7;                   // fine is a multiple of 128
+  for (int64_t w0 = 0; w0 < f4; w0 += 8 * kPruneBlock) {
+    uint4 t[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int64_t w = w0 + m * kPruneBlock + threadIdx.x;
+      if (w < f4) t[m] = reinterpret_cast<const uint4*>(src)[w];
+    }
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int64_t w = w0 + m * kPruneBlock + threadIdx.x;
+      if (w < f4) reinterpret_cast<uint4*>(sm)[w] = t[m];
+    }
+  }
+  if constexpr (FOLD) {
+    // folded word w holds the cells fine + (32 w + b) * 2^fold of bits b: 2^fold source words
+    const int64_t rest = (hrow >> 5) - (fine >> 5), nf = (rest + (1ll << fold) - 1) >> fold;
+    const int per = 32 >> fold;  // folded bits from one source word
+    const uint32_t group = fold == 5 ? 0xffffffffu : (1u << (1 << fold)) - 1u;
+    for (int64_t w = threadIdx.x; w < nf; w += kPruneBlock) {
+      uint32_t out = 0u;
+      for (int f = 0; f < (1 << fold); ++f) {
+        const int64_t sw = (w << fold) + f;
+        const uint32_t x = sw < rest ? src[(fine >> 5) + sw] : 0u;
+        for (int q = 0; q < per; ++q)
+          if ((x >> (q << fold)) & group) out |= 1u << (f * per + q);
+      }
+      sm[(fine >> 5) + w] = out;
+    }
+  }
+  const RowConst k = row_const(hs, j);
+  const int64_t stride = parts * kPruneBlock * U;
+  // columns advanced by one stride per pass without a multiply (as in k_pruned)
+  constexpr uint32_t kBias = 0x80000001u;
+  const uint32_t pc = mod_c(kMersenne, k.c, k.magic, k.shift);
+  const uint32_t db = mod_mersenne_affine(k.a, 0u, (uint32_t)stride);
+  uint32_t dc1 = mod_c(db, k.c, k.magic, k.shift);
+  uint32_t dc2 = dc1 >= pc ? dc1 - pc : dc1 + (k.c - pc);
+  asm volatile("" : "+v"(dc1), "+v"(dc2));
+  const int64_t base0 = part * kPruneBlock * U;
+  uint32_t hb[U], cb[U];
+#pragma unroll
+  for (int m = 0; m < U; ++m) {
+    const uint32_t raw = mod_mersenne_affine(k.a, k.b, (uint32_t)(base0 + threadIdx.x + (int64_t)m * kPruneBlock));
+    hb[m] = raw + kBias;
+    cb[m] = mod_c(raw, k.c, k.magic, k.shift);
+  }
+  const int lane = threadIdx.x & 63;
+  uint64_t* const out = planes + j * plane_words;
+  __syncthreads();
+  for (int64_t base = base0; base < d; base += stride) {  // block-uniform
+    uint32_t bit[U];
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      uint32_t e = cb[m];
+      if constexpr (FOLD) {
+        const int32_t over = max((int32_t)(e - (uint32_t)fine), 0);  // cells beyond the fine ones
+        e = e - (uint32_t)over + ((uint32_t)over >> fold);
+      }
+      bit[m] = bit_at(sm[e >> 5], e);
+      const uint32_t t = hb[m] + db;
+      const bool wrap = t < db;
+      hb[m] = wrap ? t + kBias : t;
+      const uint32_t cn = cb[m] + (wrap ? dc2 : dc1);
+      cb[m] = min(cn, cn - k.c);
+    }
+    // the 64 bits of a wave's coordinates are one word of the plane; lane m stores word m
+    uint64_t mine = 0;
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      const uint64_t w = __ballot(bit[m] != 0u);
+      mine = lane == m ? w : mine;
+    }
+    const int64_t i = base + (threadIdx.x & ~63) + (int64_t)lane * kPruneBlock;
+    if (lane < U && i < d) out[i >> 6] = mine;
+  }
+}
+
+// Bits whose count over the R planes reaches `need`, by a bit-sliced counter.
+template <int R>
+__device__ __forceinline__ uint32_t count_reaches(const uint32_t (&x)[R], int need) {
+  uint32_t c[5] = {0u, 0u, 0u, 0u, 0u};  // counts up to 16
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    uint32_t carry = x[j];
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+      const uint32_t t = c[b] & carry;
+      c[b] ^= carry;
+      carry = t;
+    }
+  }
+  uint32_t ge = 0u, eq = ~0u;
+#pragma unroll
+  for (int b = 4; b >= 0; --b) {
+    const uint32_t n = (need >> b) & 1 ? ~0u : 0u;
+    ge |= eq & c[b] & ~n;
+    eq &= ~(c[b] ^ n);
+  }
+  return ge | eq;
+}
+
+template <int R, bool HM>
+__global__ void __launch_bounds__(kPruneBlock) k_combine(HashSet hs, int64_t d, SelectCtl* __restrict__ ctl,
+                                                         const uint32_t* __restrict__ planes, int64_t plane_words,
+                                                         uint32_t* __restrict__ queue, uint32_t* __restrict__ bitmap,
+                                                         const uint32_t* __restrict__ rnd,
+                                                         const float* __restrict__ merged,
+                                                         uint32_t* __restrict__ cand_key,
+                                                         int32_t* __restrict__ cand_idx,
+                                                         uint32_t* __restrict__ hist_c,
+                                                         const uint32_t* __restrict__ confirm, int64_t hrow) {
+  __shared__ uint32_t sm[kSurvWords];
+  __shared__ uint32_t qs;
+  constexpr int need = (R + 1) / 2;
+  RowConst kr[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) kr[j] = row_const(hs, j);
+  const uint32_t tau0 = ctl->tau0;
+  // contiguous words per workgroup; its part of the queue starts at its first coordinate
+  const int64_t words = (d + 31) / 32, per = (words + gridDim.x - 1) / gridDim.x;
+  const int64_t lo = blockIdx.x * per, hi = min(words, lo + per);
+  queue += lo * 32;
+  if (threadIdx.x == 0) qs = 0u;
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int64_t row_words = 2 * plane_words;  // 32-bit words per plane
+  if constexpr (!HM) {
+    for (int64_t w0 = lo; w0 < hi; w0 += kPruneBlock) {  // block-uniform; one word per thread
+      const int64_t w = w0 + threadIdx.x;
+      uint32_t x[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) x[j] = w < hi ? planes[j * row_words + w] : 0u;
+      uint32_t m = count_reaches<R>(x, need);
+      if (w < hi) bitmap[w] = 0u;
+      if (w >= hi) m = 0u;
+      if (w == words - 1 && (d & 31)) m &= (1u << (d & 31)) - 1u;
+      // the wave's survivors take consecutive places: one LDS atomic per wave
+      uint32_t before = (uint32_t)__popc(m);
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(before, o, 64);
+        if (lane >= o) before += y;
+      }
+      uint32_t base = 0u;
+      if (lane == 63 && before) base = atomicAdd(&qs, before);
+      base = __shfl(base, 63) + before - (uint32_t)__popc(m);
+      while (m) {
+        queue[base++] = (uint32_t)(32 * w + __ffs(m) - 1);
+        m &= m - 1u;
+      }
+    }
+  } else {  // one coordinate per lane: every draw is read as well
+    for (int64_t i0 = lo * 32; i0 < hi * 32; i0 += kPruneBlock) {
+      const int64_t i = i0 + threadIdx.x, w = i >> 5;
+      const bool in = i < min(d, hi * 32);
+      uint32_t x[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) x[j] = in ? planes[j * row_words + w] : 0u;
+      const uint32_t draw = in ? rnd[i] >> 1 : 0u;
+      if (in && (i & 31) == 0) bitmap[w] = 0u;
+      const bool keep = in && (((count_reaches<R>(x, need) >> (i & 31)) & 1u) || draw >= tau0);
+      const uint64_t bal = __ballot(keep);
+      uint32_t base = 0u;
+      if (lane == 0 && bal) base = atomicAdd(&qs, (uint32_t)__popcll(bal));
+      base = __shfl(base, 0);
+      if (keep) queue[base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull))] = (uint32_t)i;
+    }
   }
   __syncthreads();
-  const double theta = HM ? ctl->theta : 0.0;
-  const CandBins bins = cand_bins(tau0, HM, theta, true);
-  const int lane = threadIdx.x & 63;
-  uint32_t mine = 0;
-  for (int64_t t0 = 0; t0 < qn; t0 += V * kPruneBlock) {  // block-uniform
-    uint32_t ii[V], key[V];
-    float e[V];
-    bool cand[V];
-#pragma unroll
-    for (int m = 0; m < V; ++m) {
-      const int64_t t = t0 + m * kPruneBlock + threadIdx.x;
-      cand[m] = t < qn;
-      ii[m] = cand[m] ? queue[t] : 0u;  // coordinate 0 stands in past the end (in range)
-    }
-#pragma unroll
-    for (int m = 0; m < V; ++m) e[m] = estimate_val<R>(kr, merged, ii[m]);
-#pragma unroll
-    for (int m = 0; m < V; ++m) {
-      if constexpr (HM) {
-        const bool hv = cand[m] && (double)e[m] * (double)e[m] >= theta;
-        key[m] = hv ? (0x80000000u | abs_key(e[m])) : (cand[m] ? rnd[ii[m]] >> 1 : 0u);
-        cand[m] = hv || (cand[m] && key[m] >= tau0);
-        mine += hv ? 1u : 0u;
-      } else {
-        key[m] = abs_key(e[m]);
-        cand[m] = cand[m] && key[m] >= tau0;
-      }
-      hist_add(h, cand[m], cand_bin(bins, key[m]));
-      // one LDS atomic per wave; at most V * kPruneBlock entries a pass, and the buffer, flushed
-      // whenever it is half full, holds twice that
-      const uint64_t bal = __ballot(cand[m]);
-      uint32_t wbase = 0u;
-      if (lane == 0 && bal) wbase = atomicAdd(&cn, (uint32_t)__popcll(bal));
-      wbase = __shfl(wbase, 0);
-      if (cand[m]) {
-        const uint32_t pos = wbase + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-        bkey[pos] = key[m];
-        bidx[pos] = (int32_t)ii[m];
-      }
-    }
-    __syncthreads();
-    const uint32_t nb = cn;
-    if (nb >= (uint32_t)(kSurvBuf / 2) || (t0 + V * kPruneBlock >= qn && nb > 0)) {
-      if (threadIdx.x == 0) cbase = atomicAdd(&ctl->n_cand, nb);
-      __syncthreads();
-      const int64_t g0 = cbase;
-      for (uint32_t t = threadIdx.x; t < nb; t += kPruneBlock) {
-        cand_key[g0 + t] = bkey[t];
-        cand_idx[g0 + t] = bidx[t];
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) cn = 0u;
-    }
-    __syncthreads();
-  }
-  if constexpr (HM) {
-    if (mine) atomicAdd(&nheavy, mine);
-    __syncthreads();
-    if (threadIdx.x == 0 && nheavy) atomicAdd(&ctl->n_heavy, (unsigned long long)nheavy);
-  }
-  for (int b = threadIdx.x; b < kDigit1Bins; b += kPruneBlock) {
-    const uint32_t c = h[b];
-    if (c) atomicAdd(&hist_c[b], c);
-  }
+  estimate_survivors<R, HM>(sm, kr, merged, ctl, tau0, queue, qs, rnd, cand_key, cand_idx, hist_c, confirm,
+                            hrow);
 }
 
 // ------------------------------------------------------------------------------------
@@ -885,17 +1120,31 @@ void launch_prune_r(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, co
   hipLaunchKernelGGL(k_heavy, dim3(grid_for(nbits, kSelBlock * kHeavyUnroll, x->num_cus)), dim3(kSelBlock), 0, s,
                      merged, x->c, x->heavy_row, x->r, x->ctl, x->heavy, HM ? 1 : 0, x->sample_keys, M,
                      (uint32_t)rho_d, x->hist_s);
+  if (x->planes) {
+    const int64_t plane_words = (x->d + 63) / 64;
+    const int wgs = std::max(1, x->num_cus / x->r) * x->r;
+    if (x->plane_fold)
+      hipLaunchKernelGGL(k_planes<true>, dim3(wgs), dim3(kPruneBlock), 0, s, x->hs, x->d, x->heavy, x->heavy_row,
+                         x->plane_fine, x->plane_fold, x->planes, plane_words, x->hist_s);
+    else
+      hipLaunchKernelGGL(k_planes<false>, dim3(wgs), dim3(kPruneBlock), 0, s, x->hs, x->d, x->heavy, x->heavy_row,
+                         x->plane_fine, 0, x->planes, plane_words, x->hist_s);
+    hipLaunchKernelGGL((k_combine<R, HM>), dim3(x->num_cus), dim3(kPruneBlock), 0, s, x->hs, x->d, x->ctl,
+                       reinterpret_cast<const uint32_t*>(x->planes), plane_words, x->keys, x->bitmap, rnd, merged,
+                       x->cand_key, x->cand_idx, x->hist_c, x->plane_fold ? x->heavy : nullptr, x->heavy_row);
+    return;
+  }
   // with the bitmap in LDS one block fits a CU: launch one per CU so the map is loaded once
   const int pgrid = grid_for(x->d, 4 * kPruneBlock, x->prune_map_in_lds ? x->num_cus : 2 * x->num_cus);
-#define GS_PRUNED(MAP, LMAP, COARSE)                                                                               \
-  hipLaunchKernelGGL((k_pruned<R, HM, MAP>), dim3(pgrid), dim3(kPruneBlock), 0, s, x->hs, x->d, x->ctl, x->heavy,  \
-                     LMAP, x->prune_map_words, x->heavy_row, COARSE, x->prune_buf_cap, x->keys, x->bitmap, rnd, \
+#define GS_PRUNED(MAP, LMAP, COARSE)                                                                              \
+  hipLaunchKernelGGL((k_pruned<R, HM, MAP>), dim3(pgrid), dim3(kPruneBlock), 0, s, x->hs, x->d, x->ctl, x->heavy, \
+                     LMAP, x->prune_map_words, x->heavy_row, COARSE, x->prune_buf_cap, x->keys, x->bitmap, rnd,   \
                      x->hist_s, merged, x->cand_key, x->cand_idx, x->hist_c)
   if (!x->prune_map_in_lds) {
     GS_PRUNED(kMapGlobal, x->heavy, 0);
   } else if (x->prune_coarse_log2 > 0) {
-    hipLaunchKernelGGL(k_coarse, dim3(grid_for(x->prune_coarse_words, kBlock, 4 * x->num_cus)), dim3(kBlock), 0, s,
-                       x->heavy, nbits / 32, x->prune_coarse_log2, x->coarse, x->prune_coarse_words);
+    hipLaunchKernelGGL(k_coarse, dim3(grid_for(x->prune_map_words, kBlock, 4 * x->num_cus)), dim3(kBlock), 0, s,
+                       x->heavy, nbits / 32, x->prune_coarse_log2, x->coarse, x->prune_map_words);
     GS_PRUNED(kMapCoarse, x->coarse, x->prune_coarse_log2);
   } else {
     GS_PRUNED(kMapFine, x->heavy, 0);
@@ -960,8 +1209,9 @@ hipError_t prepare_prune(gs_ctx* x) {
   const int64_t rc = (int64_t)x->r * x->heavy_row;  // bits of the heavy-cell map (padded rows)
   const int64_t words = rc / 32;
   const int64_t lds_max = 160 * 1024 - 256;
-  // the fine map in LDS if it fits beside a 512-entry queue buffer; else the coarsest-needed
-  // coarse map (2 .. 32 cells per bit); else the fine map from global memory
+  // the fine map of all rows in LDS if it fits beside a 512-entry queue buffer; else row by row (see
+  // k_planes); else the coarsest-needed coarse map (2 .. 32 cells per bit); else the fine map from
+  // global memory
   int64_t map_words = words;
   int log2g = 0;
   while ((lds_max - map_words * 4) / 4 < 512 && log2g < 5) {
@@ -969,26 +1219,25 @@ hipError_t prepare_prune(gs_ctx* x) {
     map_words = (rc + (32ll << log2g) - 1) / (32ll << log2g);
     map_words += map_words & 1;
   }
-  int64_t buf = (lds_max - map_words * 4) / 4;
-  if (buf > 8192) buf = 8192;
-  if (buf >= 512) {
-    x->prune_map_in_lds = 1;
-    x->prune_coarse_log2 = log2g;
-    x->prune_map_words = map_words;
-    x->prune_buf_cap = (int)buf;
-    if (log2g > 0) {
-      x->prune_coarse_words = map_words;
-      const hipError_t e = hipMalloc(reinterpret_cast<void**>(&x->coarse), (size_t)map_words * sizeof(uint32_t));
-      if (e != hipSuccess) return e;
-    }
-  } else {
-    x->prune_map_in_lds = 0;
-    x->prune_coarse_log2 = 0;
-    x->prune_map_words = words;
-    x->prune_buf_cap = 8192;
+  if (log2g > 0 && x->r >= 4 && x->heavy_row <= 2 * (kPlaneBits - 128)) {
+    x->plane_fold = x->heavy_row > kPlaneBits ? 1 : 0;
+    // folded by two: `fine` cells as they are and (row - fine) / 2 bits after them fill kPlaneBits - 128
+    x->plane_fine = x->plane_fold ? (2 * (kPlaneBits - 128) - x->heavy_row) / 128 * 128 : x->heavy_row;
+    const hipError_t e =
+        hipMalloc(reinterpret_cast<void**>(&x->planes), (size_t)(x->r * ((x->d + 63) / 64)) * sizeof(uint64_t));
+    if (e != hipSuccess) return e;
   }
-  // the map (when in LDS), the queue buffer and two counters share the pass's LDS array
-  if ((x->prune_map_in_lds ? x->prune_map_words : 0) + x->prune_buf_cap + 2 > kPruneLdsWords)
+  const int64_t buf = std::min<int64_t>((lds_max - map_words * 4) / 4, 8192);
+  x->prune_map_in_lds = buf >= 512 ? 1 : 0;
+  x->prune_coarse_log2 = buf >= 512 ? log2g : 0;
+  x->prune_map_words = buf >= 512 ? map_words : words;
+  x->prune_buf_cap = buf >= 512 ? (int)buf : 8192;
+  if (x->prune_coarse_log2 > 0 && !x->planes) {
+    const hipError_t e = hipMalloc(reinterpret_cast<void**>(&x->coarse), (size_t)map_words * sizeof(uint32_t));
+    if (e != hipSuccess) return e;
+  }
+  // the map (when in LDS), the queue buffer and a counter share the pass's LDS array
+  if ((x->prune_map_in_lds ? x->prune_map_words : 0) + x->prune_buf_cap + 1 > kPruneLdsWords)
     return hipErrorInvalidValue;
   return hipSuccess;
 }
