@@ -14,9 +14,11 @@
 //   3. Bits become indices; the workgroup's own indices are gathered and reset.
 // One kernel instead of four (digit 3 in one workgroup, marking, emission with a look-back,
 // gather), at about 4.6 us each however little they do.
-// When the pruned pass fell short of k candidates, or the bin is crowded (ties: an all-zero
-// sketch), the first workgroup selects alone over the whole candidate list: slow (milliseconds at
-// d in the tens of millions), and right for every input. No workgroup ever waits for another.
+// When the bin does not fit the LDS (ties: a zero sketch, a diverged one), or the pruned pass fell
+// short of k candidates and the list holds every key, every workgroup reads the whole list: its
+// histograms give the k-th key, and one more pass the marks of the own range and the entries before
+// it; ties at the k-th key are taken in coordinate order (a zero sketch of 14.7M: 9 ms, and 60 ms
+// by one workgroup alone). No workgroup ever waits for another.
 #include "gs_internal.hpp"
 #include "gs_select.hpp"
 
@@ -26,14 +28,12 @@ namespace {
 constexpr int kBlock = 1024;
 constexpr int kBucketCap = 8192;   // words of the k-th key's bin kept in LDS
 constexpr int kRankCap = 256;      // words ranked against each other
-// Staged keys that every workgroup reads for itself; beyond, the first workgroup selects alone.
-constexpr uint32_t kListMax = (uint32_t)kStage2Cap;
 
 struct EmitArgs {
-  const uint32_t* key;        // [n] candidate keys; dense: key of coordinate t at t
-  const int32_t* idx;         // [n] their coordinates; dense: null
   const uint32_t* list_key;   // staged keys of the bin
   const int32_t* list_idx;    // and their coordinates
+  const uint32_t* list0_key;  // those of the first digit's bin (complete; or every key by coordinate)
+  const int32_t* list0_idx;
   uint32_t* bitmap;
   uint32_t* counts;
   SelectCtl* ctl;
@@ -62,13 +62,19 @@ struct Shared {
   uint32_t shw[kBlock / 64];
   uint32_t res[2];
   uint64_t cut;
-  uint32_t n, before, last;
+  uint32_t n, before, ties, last;
 };
+static_assert(kRangeMax <= (int64_t)kBucketCap * 64, "the ties of a range have a bit each in the bucket");
 
-// The `need`-th largest of the n_in words in [lo, hi] that `each` enumerates: each(f) calls
-// f(in the source?, word) the same number of times in every thread of the block.
-template <class Each>
-__device__ __forceinline__ uint64_t nth_largest(Shared& sh, Each each, uint64_t lo, uint64_t hi, uint32_t need, uint32_t n_in) {
+// The `need`-th largest of the n words in the bucket, all of them in [lo, hi].
+__device__ __forceinline__ uint64_t nth_largest(Shared& sh, uint64_t lo, uint64_t hi, uint32_t need, uint32_t n) {
+  auto each = [&](auto f) {  // f(a word?, word), in the same number of rounds for every thread
+    for (uint32_t t0 = 0; t0 < n; t0 += kBlock) {
+      const uint32_t t = t0 + threadIdx.x;
+      f(t < n, t < n ? sh.bucket[t] : 0ull);
+    }
+  };
+  uint32_t n_in = n;
   while (n_in > (uint32_t)kRankCap) {  // the words are distinct, so the interval is wider than 2^8
     const int bits = 64 - __clzll((long long)(hi - lo));
     const int shift = bits > 10 ? bits - 10 : 0;
@@ -97,34 +103,83 @@ __device__ __forceinline__ uint64_t nth_largest(Shared& sh, Each each, uint64_t 
     }
   });
   __syncthreads();
-  const uint32_t n = min(sh.n, (uint32_t)kRankCap);  // == n_in
-  if (threadIdx.x < n) {
+  const uint32_t nf = min(sh.n, (uint32_t)kRankCap);  // == n_in
+  if (threadIdx.x < nf) {
     const uint64_t w = sh.fin[threadIdx.x];
     uint32_t rank = 0;
-    for (uint32_t b = 0; b < n; ++b) rank += sh.fin[b] > w ? 1u : 0u;
+    for (uint32_t b = 0; b < nf; ++b) rank += sh.fin[b] > w ? 1u : 0u;
     if (rank == need - 1) sh.cut = w;
   }
   __syncthreads();
   return sh.cut;
 }
 
-// f(valid, word) for every entry of a list (idx null: entry t is coordinate t) by one block, in the
-// same number of rounds for every thread.
-template <class F>
-__device__ __forceinline__ void for_list(const uint32_t* __restrict__ key, const int32_t* __restrict__ idx, int64_t n,
-                                         F f) {
-  constexpr int U = 4;
+// A list too long for the LDS: the selection is its keys above T and the first need of those equal
+// to T (sets need and returns T). Only the keys in [klo, khi] are read as its entries. 10 bits of
+// the key range a pass; 16 loads per thread in flight, since one workgroup fills a CU.
+__device__ __forceinline__ uint32_t nth_key(Shared& sh, const uint32_t* __restrict__ key, int64_t n, uint32_t klo,
+                                            uint32_t khi, uint32_t& need) {
+  constexpr int U = 16;
+  while (khi > klo) {
+    const int bits = 32 - __clz((int)(khi - klo));
+    const int shift = bits > 10 ? bits - 10 : 0;
+    for (int b = threadIdx.x; b < 1024; b += kBlock) sh.h[b] = 0u;
+    __syncthreads();
+    for (int64_t t0 = 0; t0 < n; t0 += (int64_t)U * kBlock) {  // block-uniform
+      uint32_t kk[U];
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        const int64_t t = t0 + (int64_t)m * kBlock + threadIdx.x;
+        kk[m] = key[min(t, n - 1)];
+      }
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the adds
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        const bool in = t0 + (int64_t)m * kBlock + threadIdx.x < n && kk[m] - klo <= khi - klo;
+        hist_add(sh.h, in, in ? (kk[m] - klo) >> shift : 0u);
+      }
+    }
+    __syncthreads();
+    find_bucket<kBlock, 1024>(sh.h, true, need, sh.shw, sh.res);
+    const uint32_t b = sh.res[0];
+    need -= sh.res[1];
+    klo += b << shift;
+    khi = min(khi, klo + ((1u << shift) - 1u));
+    __syncthreads();
+  }
+  return klo;
+}
+
+// The entries of that list in [T, khi]: their bit in `above` or `ties` if they are in [lo, lo + width),
+// and their number before lo.
+__device__ __forceinline__ void mark_list(const uint32_t* __restrict__ key, const int32_t* __restrict__ idx, int64_t n,
+                                          uint32_t T, uint32_t khi, uint32_t lo, uint32_t width, uint32_t* above,
+                                          uint32_t* ties, uint32_t& above_before, uint32_t& ties_before) {
+  constexpr int U = 8;
   for (int64_t t0 = 0; t0 < n; t0 += (int64_t)U * kBlock) {
     uint32_t kk[U], ii[U];
 #pragma unroll
     for (int m = 0; m < U; ++m) {
-      const int64_t t = t0 + (int64_t)m * kBlock + threadIdx.x;
-      kk[m] = t < n ? key[t] : 0u;
-      ii[m] = t < n && idx ? (uint32_t)idx[t] : (uint32_t)t;
+      const int64_t t = min(t0 + (int64_t)m * kBlock + threadIdx.x, n - 1);
+      kk[m] = key[t];
+      ii[m] = idx ? (uint32_t)idx[t] : (uint32_t)t;
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int m = 0; m < U; ++m) f(t0 + (int64_t)m * kBlock + threadIdx.x < n, word_of(kk[m], ii[m]));
+    for (int m = 0; m < U; ++m) {
+      if (t0 + (int64_t)m * kBlock + threadIdx.x >= n || kk[m] < T || kk[m] > khi) continue;
+      if (ii[m] < lo)
+        ++(kk[m] == T ? ties_before : above_before);
+      else if (ii[m] - lo < width)
+        atomicOr(&(kk[m] == T ? ties : above)[(ii[m] - lo) >> 5], 1u << ((ii[m] - lo) & 31u));
+    }
   }
+}
+
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
 }
 
 // Entries idx[t0], idx[t0 + step], ... below n, a lane group of ga.gl threads each.
@@ -168,112 +223,88 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather_reset(const int32_t* __
                (int64_t)gridDim.x * per, k, rows);
 }
 
-// The whole selection by one block over a list of n entries (idx null: dense).
-__device__ __forceinline__ void select_alone(const EmitArgs& a, const HashSet& hs, const GatherArgs& ga, Shared& sh,
-                                             const uint32_t* key, const int32_t* idx, int64_t n) {
-  const int64_t words = (a.d + 31) / 32;
-  for (int64_t w = threadIdx.x; w < words; w += kBlock) a.bitmap[w] = 0u;
-  const uint64_t cut =
-      nth_largest(sh, [&](auto f) { for_list(key, idx, n, f); }, 0ull, ~0ull, a.k, (uint32_t)n);  // n <= d < 2^31
-  __threadfence();
-  __syncthreads();
-  for_list(key, idx, n, [&](bool ok, uint64_t w) {
-    const uint32_t ix = 0xffffffffu - (uint32_t)w;
-    if (ok && w >= cut) atomicOr(&a.bitmap[ix >> 5], 1u << (ix & 31u));
-  });
-  __threadfence();
-  __syncthreads();
-  uint32_t base = 0;
-  for (int64_t w0 = 0; w0 < words; w0 += kBlock) {  // block-uniform
-    const int64_t w = w0 + threadIdx.x;
-    uint32_t x = w < words ? __hip_atomic_load(&a.bitmap[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-    uint32_t total;
-    uint32_t pos = base + block_scan_incl<kBlock>((uint32_t)__popc(x), sh.shw, total) - (uint32_t)__popc(x);
-    while (x) {
-      const int bit = __ffs(x) - 1;
-      if (pos < a.k) a.out[pos] = (int32_t)(32 * w + bit);
-      ++pos;
-      x &= x - 1u;
-    }
-    base += total;
-  }
-  gather_own(a, hs, ga, sh, 0, a.k);
-}
-
 __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherArgs ga) {
   extern __shared__ uint32_t bits[];  // [range / 32]
   __shared__ Shared sh;
   const int64_t lo = (int64_t)blockIdx.x * a.range, hi = min(a.d, lo + a.range);
-  const uint32_t n_cand = a.pruned ? a.ctl->n_cand : (uint32_t)a.d;
   const uint32_t nb = a.ctl->n_stage[a.level];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (a.n_heavy) *a.n_heavy = (int64_t)a.ctl->n_heavy;
     if (a.l2sq) *a.l2sq = a.ctl->l2sq;
   }
-  const bool few = n_cand < a.k;  // the bound admitted too little: the digit pass left every key in list_key
-  if (few || nb > kListMax) {
-    if (blockIdx.x == 0) {
-      if (few)
-        select_alone(a, hs, ga, sh, a.list_key, nullptr, a.d);
-      else
-        select_alone(a, hs, ga, sh, a.key, a.idx, n_cand);
-    }
-  } else {
-    const uint32_t need = a.ctl->need[a.level];
-    const uint64_t wlo = (uint64_t)a.ctl->lo[a.level] << 32, whi = ((uint64_t)a.ctl->hi[a.level] << 32) | 0xffffffffull;
-    const uint32_t l32 = (uint32_t)lo, width = (uint32_t)(hi - lo);
-    const int nw = (int)(a.range / 32);
-    uint32_t before = 0;
-    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kBlock) before += a.counts[t];
-    const int64_t words = (a.d + 31) / 32, word0 = lo / 32;
-    for (int w = threadIdx.x; w < nw; w += kBlock) bits[w] = word0 + w < words ? a.bitmap[word0 + w] : 0u;
-    if (threadIdx.x == 0) sh.before = 0u;
-    const bool kept = nb <= (uint32_t)kBucketCap;
-    if (kept)
-      for (uint32_t t = threadIdx.x; t < nb; t += kBlock) sh.bucket[t] = word_of(a.list_key[t], (uint32_t)a.list_idx[t]);
+  // the bound admitted too little: the digit pass left every key in the list, and marked nothing
+  const bool few = a.pruned && a.ctl->n_cand < a.k;
+  const uint32_t l32 = (uint32_t)lo, width = (uint32_t)(hi - lo);
+  const int nw = (int)(a.range / 32);
+  uint32_t before = 0;
+  for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kBlock) before += a.counts[t];
+  const int64_t words = (a.d + 31) / 32, word0 = lo / 32;
+  for (int w = threadIdx.x; w < nw; w += kBlock) bits[w] = word0 + w < words ? a.bitmap[word0 + w] : 0u;
+  if (threadIdx.x == 0) sh.before = sh.ties = 0u;
+  uint32_t need = few ? a.k : a.ctl->need[a.level];
+  const uint32_t klo = few ? 0u : a.ctl->lo[a.level], khi = few ? ~0u : a.ctl->hi[a.level];
+  const int per = (nw + kBlock - 1) / kBlock, w0 = threadIdx.x * per;
+  if (!few && nb <= (uint32_t)kBucketCap) {
+    for (uint32_t t = threadIdx.x; t < nb; t += kBlock) sh.bucket[t] = word_of(a.list_key[t], (uint32_t)a.list_idx[t]);
     __syncthreads();
-    auto each = [&](auto f) {
-      if (kept) {
-        for (uint32_t t0 = 0; t0 < nb; t0 += kBlock) {
-          const uint32_t t = t0 + threadIdx.x;
-          f(t < nb, t < nb ? sh.bucket[t] : 0ull);
-        }
-      } else {
-        for_list(a.list_key, a.list_idx, nb, f);
-      }
-    };
-    const uint64_t cut = nth_largest(sh, each, wlo, whi, need, nb);
-    each([&](bool ok, uint64_t w) {
+    const uint64_t cut = nth_largest(sh, (uint64_t)klo << 32, ((uint64_t)khi << 32) | 0xffffffffull, need, nb);
+    for (uint32_t t = threadIdx.x; t < nb; t += kBlock) {
+      const uint64_t w = sh.bucket[t];
       const uint32_t ix = 0xffffffffu - (uint32_t)w;
-      if (ok && w >= cut) {
+      if (w >= cut) {
         if (ix < l32)
           ++before;
         else if (ix - l32 < width)
           atomicOr(&bits[(ix - l32) >> 5], 1u << ((ix - l32) & 31u));
       }
-    });
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    }
+    before = wave_sum(before);
     if ((threadIdx.x & 63) == 0 && before) atomicAdd(&sh.before, before);
     __syncthreads();
-    const int per = (nw + kBlock - 1) / kBlock, w0 = threadIdx.x * per;
-    uint32_t cnt = 0;
-    for (int m = 0; m < per; ++m)
-      if (w0 + m < nw) cnt += (uint32_t)__popc(bits[w0 + m]);
-    uint32_t total;
-    const uint32_t p0 = sh.before;
-    uint32_t pos = p0 + block_scan_incl<kBlock>(cnt, sh.shw, total) - cnt;
-    for (int m = 0; m < per; ++m) {
-      uint32_t x = w0 + m < nw ? bits[w0 + m] : 0u;
-      while (x) {
-        const int bit = __ffs(x) - 1;
-        if (pos < a.k) a.out[pos] = (int32_t)(lo + 32 * (w0 + m) + bit);
-        ++pos;
-        x &= x - 1u;
-      }
+  } else {
+    uint32_t* const ties = reinterpret_cast<uint32_t*>(sh.bucket);
+    for (int w = threadIdx.x; w < nw; w += kBlock) ties[w] = 0u;
+    __syncthreads();
+    const int64_t n = few ? a.d : (int64_t)a.ctl->n_stage[0];
+    const int32_t* const idx = few ? nullptr : a.list0_idx;
+    const uint32_t T = nth_key(sh, a.list0_key, n, klo, khi, need);
+    uint32_t ties_before = 0;
+    mark_list(a.list0_key, idx, n, T, khi, l32, width, bits, ties, before, ties_before);
+    before = wave_sum(before);
+    ties_before = wave_sum(ties_before);
+    if ((threadIdx.x & 63) == 0) {
+      atomicAdd(&sh.before, before);
+      atomicAdd(&sh.ties, ties_before);
     }
-    gather_own(a, hs, ga, sh, p0, total);
+    __syncthreads();
+    const uint32_t gone = min(sh.ties, need);  // ties taken by the ranges before
+    uint32_t cnt = 0, total;
+    for (int m = 0; m < per; ++m)
+      if (w0 + m < nw) cnt += (uint32_t)__popc(ties[w0 + m]);
+    uint32_t pos = gone + block_scan_incl<kBlock>(cnt, sh.shw, total) - cnt;
+    for (int m = 0; m < per; ++m) {
+      uint32_t x = w0 + m < nw ? ties[w0 + m] : 0u;
+      for (; x && pos < need; ++pos, x &= x - 1u) bits[w0 + m] |= x & (0u - x);
+    }
+    if (threadIdx.x == 0) sh.before += gone;
+    __syncthreads();
   }
+  uint32_t cnt = 0;
+  for (int m = 0; m < per; ++m)
+    if (w0 + m < nw) cnt += (uint32_t)__popc(bits[w0 + m]);
+  uint32_t total;
+  const uint32_t p0 = sh.before;
+  uint32_t pos = p0 + block_scan_incl<kBlock>(cnt, sh.shw, total) - cnt;
+  for (int m = 0; m < per; ++m) {
+    uint32_t x = w0 + m < nw ? bits[w0 + m] : 0u;
+    while (x) {
+      const int bit = __ffs(x) - 1;
+      if (pos < a.k) a.out[pos] = (int32_t)(lo + 32 * (w0 + m) + bit);
+      ++pos;
+      x &= x - 1u;
+    }
+  }
+  gather_own(a, hs, ga, sh, p0, total);
   // the last workgroup to get here clears what the next call needs zero
   __syncthreads();
   if (threadIdx.x == 0) sh.last = atomicAdd(&a.ctl->emit_ticket, 1u) == gridDim.x - 1 ? 1u : 0u;
@@ -295,10 +326,10 @@ hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBu
                        double* l2sq, const GatherArgs* ga) {
   EmitArgs a{};
   a.range = emit_range(d, num_cus);
-  a.key = b.cand_key;
-  a.idx = pruned ? b.cand_idx : nullptr;
   a.list_key = level ? b.stage2 : b.keys;
   a.list_idx = level ? reinterpret_cast<const int32_t*>(b.stage2 + kStage2Cap) : b.stage_idx;
+  a.list0_key = b.keys;
+  a.list0_idx = b.stage_idx;
   a.bitmap = b.bitmap;
   a.counts = b.counts;
   a.ctl = b.ctl;

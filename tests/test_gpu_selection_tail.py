@@ -1,6 +1,6 @@
 """The selection's tail (digit passes and emit) on sketches made for its edges: keys many octaves
-above the sampled bound, ties from a few to all coordinates (the crowded bin that one workgroup
-selects alone), one and two digit passes, one and many emit ranges, and the pruned pass falling
+above the sampled bound, ties from a few to all coordinates (the crowded bin that does not
+fit the LDS), one and two digit passes, one and many emit ranges, and the pruned pass falling
 short of k, all against the oracle's estimates and top-k bit for bit (needs an MI355X)."""
 import numpy as np
 import pytest
