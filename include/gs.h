@@ -117,9 +117,10 @@ typedef struct gs_ctx gs_ctx; /* opaque: a copy of the config plus device scratc
  * selects the atomic form for any shape, and GS_SKETCH_PATH=unpacked keeps the gather's
  * lists in their unpacked form (diagnostic overrides; results agree within the table
  * tolerance). A selection without an estimate vector prunes (estimates only coordinates
- * with enough heavy cells) when d*r exceeds 2,000,000 and estimates every coordinate
- * otherwise; GS_SELECT_PATH=pruned or =full fixes that choice (the selected set is the same
- * either way).
+ * with enough heavy cells) when d*r exceeds 2,000,000 and k is a small part of d (up to a tenth
+ * or a fifth, by the table's size) and estimates every coordinate
+ * otherwise; GS_SELECT_PATH=pruned or =full fixes that choice, and GS_ESTIMATE_PATH=tiles or
+ * =direct how every coordinate is estimated (the selected set is the same either way).
  * Device scratch is about (16 + 4.1 r) d + 8 S P r c bytes (S list segments per tile, 1
  * unless the sketch is small), plus the 4 PP d bytes of the interleaved copy (PP = P rounded
  * up to 4) in a worker-major context with P > 1 or with GS_OPT_ROW_COPY, plus 2 r d bytes while the
@@ -270,7 +271,8 @@ gs_status gs_unsketch_topk_static(const gs_config* cfg, void* stream, const floa
  *   tile_width        columns per tile (gather), tiles = r * tiles per row, segments = list
  *                     segments per tile (tiles split so that small sketches fill the GPU)
  *   packed_lists      1: one 32-bit word per list entry (coordinate offset, position, sign)
- *   prune             1: selections without an estimate vector prune (d * r > 2,000,000)
+ *   prune             1: selections of few coordinates without an estimate vector prune
+ *                     (d * r > 2,000,000)
  *   row_copy          1: the context holds the interleaved copy of v ([d][PP] floats)
  * Errors: GS_ERR_INVALID_ARG for a NULL argument. */
 #define GS_SKETCH_GATHER 0

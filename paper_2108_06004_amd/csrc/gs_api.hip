@@ -220,8 +220,23 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
     // GS_SELECT_PATH=pruned prunes every selection without an estimate vector, =full none
     x->prune_min_cells = gs::kPruneMinCells;
     const char* sel = std::getenv("GS_SELECT_PATH");
-    if (sel && std::strcmp(sel, "pruned") == 0) x->prune_min_cells = 0;
+    x->prune_max_density = 1;
+    if (sel && std::strcmp(sel, "pruned") == 0) x->prune_min_cells = x->prune_max_density = 0;
     if (sel && std::strcmp(sel, "full") == 0) x->prune_min_cells = INT64_MAX;
+    // The full estimate reads a table that outgrows an XCD's 4 MB L2 by tile (one fill per line
+    // instead of one per read: 14.7M, c = 1.47M: 1,127 -> 600 us, 4M, c = 400,000: 187 -> 147 us), a
+    // smaller one directly (25.6M, r x c = 5 x 256,000: 725 against 777 us, 2M, 5 x 50,000: 75 against
+    // 79 us). GS_ESTIMATE_PATH=tiles or =direct fixes the choice.
+    x->push = x->d >= gs::kPushMinD && (int64_t)x->r * x->c * (int64_t)sizeof(float) > gs::kPushMinTable;
+    const char* est = std::getenv("GS_ESTIMATE_PATH");
+    if (est && std::strcmp(est, "tiles") == 0) x->push = true;
+    if (est && std::strcmp(est, "direct") == 0) x->push = false;
+    x->push = x->push && x->use_pull;
+    // Selections of a large part of d estimate every coordinate: the pruned pass's survivors read the
+    // table at random. The line lies where the two cost the same (14.7M, by tile: 549 against 590 us
+    // at k = 0.0725 d, 783 against 595 at 0.125 d; 25.6M, directly: 528 against 725 at 0.125 d, 877
+    // against 725 at 0.25 d).
+    if (x->prune_max_density) x->prune_max_density = x->push ? 10 : 5;
   }
   if (x->use_pull) {
     x->list_cap = (int64_t)x->r * x->d + (int64_t)gs::kListGroup * x->plan.T;

@@ -73,6 +73,8 @@ inline int64_t emit_range(int64_t d, int num_cus) {
   return r < 4096 ? 4096 : r > kRangeMax ? kRangeMax : r;
 }
 constexpr int kSampleMax = 16384;  // sampled estimates for the pruning bound
+constexpr int64_t kPushMinD = 1000000;         // the full estimate reads the table by tile from this d on,
+constexpr int64_t kPushMinTable = 6ll << 20;   // when the table is larger than this (bytes; see gs_create)
 constexpr int64_t kPruneMinCells = 2000000;  // d*r below which the full estimate is faster (measured)
 
 // Geometry of the gather-based sketch: tiles of W columns of one row, all P workers, fp64.
@@ -155,6 +157,8 @@ struct gs_ctx {
   // selections without an estimate vector prune when d*r exceeds this (0: always); below it
   // the full estimate takes fewer launches than the pruned pass's chain
   int64_t prune_min_cells = 0;
+  int64_t prune_max_density = 0;  // and when k * this is at most d
+  bool push = false;              // the full estimate reads the table by tile
   // gather-based sketch (used when the plan fits; otherwise fp64 atomics into acc64)
   bool use_pull = false;
   gs::PullPlan plan{};
@@ -249,6 +253,13 @@ hipError_t launch_pull(const gs_ctx* x, hipStream_t s, const float* rows, float*
 hipError_t launch_pull_flat(const gs_ctx* x, hipStream_t s, const float* v, float* merged, float* tables);
 // A worker-major state with one worker is gathered directly (no interleaved copy).
 inline bool flat_state(const gs_ctx* x) { return x->P == 1 && x->state_layout == GS_STATE_WORKER_MAJOR; }
+// The full estimate's table reads by tile (k_push): the signed cells of the first n rows (push_rows:
+// as many as there is scratch for), one float per coordinate and row.
+struct RowValues {
+  float* p[kMaxRows];
+};
+int push_rows(const gs_ctx* x, RowValues* rows);
+hipError_t launch_push(const gs_ctx* x, hipStream_t s, const float* merged, const RowValues& rows, int n);
 bool pull_merges(const gs_ctx* x);
 // Rows for the pull from the caller's state array v (GS_STATE_INTERLEAVED): v itself when it
 // is 16-byte aligned, otherwise a copy enqueued into x->vI.

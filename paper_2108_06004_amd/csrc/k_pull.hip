@@ -614,6 +614,73 @@ __global__ void __launch_bounds__(kPullBlock) k_pull(HashSet hs, PullPlan pl, co
 }
 
 // ------------------------------------------------------------------------------------
+// The full estimate's table reads by tile: the lists turned round. A workgroup holds one tile's
+// merged cells (fp32) in LDS and walks the tile's list, writing each listed coordinate's signed cell
+// to its place in the row's values, rows.p[j][i]; k_median (k_select.hip) then reads each
+// coordinate's values in order. Reading the table at random instead costs an L2 request per
+// (coordinate, row), and a 128-byte line fill where the table outgrows the L2s. At 14.7M, r = 5,
+// c = 1.47M: 460 us and 79 us for the median, against 1,050 us. 128, 256 or 512 threads and the words
+// fetched a pass ahead measure the same: the runs of 4-byte stores set the rate (17.6M requests).
+constexpr int kPushBlock = 256;
+template <bool PK>
+__global__ void __launch_bounds__(kPushBlock) k_push(HashSet hs, PullPlan pl, int64_t items,
+                                                     const uint32_t* __restrict__ list,
+                                                     const uint16_t* __restrict__ codes,
+                                                     const uint32_t* __restrict__ bases,
+                                                     const int64_t* __restrict__ off, const uint32_t* __restrict__ tn,
+                                                     const float* __restrict__ merged, RowValues rows) {
+  extern __shared__ float cells[];  // [W]
+  constexpr int U = 8;
+  // neighbouring tiles on one XCD: their runs of coordinates meet in the same lines of the values
+  const int64_t t = grouped_item(blockIdx.x, items, (items + 7) / 8 * 8);
+  const int j = (int)(t / pl.tiles_per_row);
+  const int64_t kt = t - (int64_t)j * pl.tiles_per_row;
+  const uint32_t c = hs.c;
+  const int64_t wt = min((int64_t)pl.W, (int64_t)c - kt * pl.W);
+  const uint32_t cstep = (uint32_t)(((uint64_t)pl.theta_inv[j] * kPushBlock) % c);
+  uint32_t col = threadIdx.x < wt ? column_at(hs, pl, j, kt, threadIdx.x) : 0u;
+  for (int64_t o = threadIdx.x; o < wt; o += U * kPushBlock) {  // every cell a line of its own: U in flight
+    float y[U];
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      y[m] = o + m * kPushBlock < wt ? merged[(int64_t)j * c + col] : 0.f;
+      col = col + cstep >= c ? col + cstep - c : col + cstep;
+    }
+#pragma unroll
+    for (int m = 0; m < U; ++m)
+      if (o + m * kPushBlock < wt) cells[o + m * kPushBlock] = y[m];
+  }
+  __syncthreads();
+  float* const out = rows.p[j];
+  const int64_t e1 = off[t] + tn[t];
+  // the next pass's words are fetched before this pass's stores: loads and stores retire in order, and
+  // a pass that fetched after the stores would wait for them to reach memory
+  uint32_t w[U], a[U];
+  auto fetch = [&](int64_t eb) {
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      const int64_t e = min(eb + m * kPushBlock, e1 - 1);
+      w[m] = __builtin_nontemporal_load(list + e);
+      a[m] = PK ? bases[e / kListGroup] : (uint32_t)codes[e];
+    }
+  };
+  int64_t eb = off[t] + threadIdx.x;
+  if (eb < e1) fetch(eb);
+  for (; eb < e1; eb += U * kPushBlock) {
+    uint32_t i[U], pos[U], sg[U];
+    float y[U];
+#pragma unroll
+    for (int m = 0; m < U; ++m) decode_entry<PK>(w[m], a[m], pl.off_bits, i[m], pos[m], sg[m]);
+    fetch(eb + U * kPushBlock);
+#pragma unroll
+    for (int m = 0; m < U; ++m) y[m] = apply_sign(cells[pos[m]], sg[m]);
+#pragma unroll
+    for (int m = 0; m < U; ++m)
+      if (eb + m * kPushBlock < e1) out[i[m]] = y[m];
+  }
+}
+
+// ------------------------------------------------------------------------------------
 // Segment sum + single rounding + tree merge. partial is [S][P][r][c] fp64.
 
 // Segments are added in ascending order per worker; the P sums are independent chains and
@@ -932,6 +999,15 @@ hipError_t prepare_pull_kernels(const gs_ctx* x) {
     const hipError_t e = allow_pull_lds<1, true>(bytes);
     if (e != hipSuccess) return e;
   }
+  {
+    const int lds = (int)(x->plan.W * sizeof(float));  // at most 81,896 bytes (one worker)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_push<true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_push<false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
   if (x->P > 16) {
     const int wide = (int)vi_wide_lds(x->plan.PP);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vi_wide<true>),
@@ -1042,6 +1118,32 @@ const float* pull_rows_of_state(const gs_ctx* x, hipStream_t s, const float* v, 
   hipLaunchKernelGGL(k_copy_rows, dim3(grid_for(n, kBlock, 8 * x->num_cus)), dim3(kBlock), 0, s, v, x->vI, n);
   *e = hipGetLastError();
   return x->vI;
+}
+
+int push_rows(const gs_ctx* x, RowValues* rows) {
+  // the values of a row per array of d floats: the selection's own scratch and, where there is one,
+  // the interleaved copy of v, which nothing reads any more once the sketch is made
+  float* const own[] = {reinterpret_cast<float*>(x->cand_key), reinterpret_cast<float*>(x->cand_idx),
+                        reinterpret_cast<float*>(x->keys), reinterpret_cast<float*>(x->stage_idx)};
+  int n = 0;
+  for (; n < 4 && n < x->r; ++n) rows->p[n] = own[n];
+  if (x->vI)
+    for (int m = 0; m < x->plan.PP && n < x->r; ++m, ++n) rows->p[n] = x->vI + (int64_t)m * x->d;
+  return n;
+}
+
+hipError_t launch_push(const gs_ctx* x, hipStream_t s, const float* merged, const RowValues& rows, int n) {
+  const PullPlan& pl = x->plan;
+  const int64_t items = (int64_t)n * pl.tiles_per_row;
+  const dim3 grid((unsigned)items), block(kPushBlock);
+  const size_t lds = (size_t)pl.W * sizeof(float);
+  if (pl.packed)
+    hipLaunchKernelGGL(k_push<true>, grid, block, lds, s, x->hs, pl, items, x->list, x->codes, x->bases,
+                       x->tile_off, x->tile_n, merged, rows);
+  else
+    hipLaunchKernelGGL(k_push<false>, grid, block, lds, s, x->hs, pl, items, x->list, x->codes, x->bases,
+                       x->tile_off, x->tile_n, merged, rows);
+  return hipGetLastError();
 }
 
 bool pull_merges(const gs_ctx* x) { return x->plan.S == 1; }

@@ -7,20 +7,14 @@
 // integers); for HEAVYMIX, heavy coordinates get 0x80000000 | bits(|est_i|) and the others
 // their fill draw. The k-th key is found by a most-significant-digit radix select entirely
 // on the device (no host synchronisation inside the call):
-//   1. candidates: either every key reaching the pruned pass's sampled bound (k_sample ..
-//      k_survivors: bound, heavy-cell bitmap, survivor estimates, with the candidates'
-//      digit-1 histogram), or every coordinate, from the full estimate (k_unsketch /
-//      k_unsketch_hm), which also runs whenever the pruned candidates fall short of k;
-//   2. k_digit2 (many blocks): each block finds the digit-1 bucket (bits 31..20) of the
-//      k-th key in the candidates' histogram; candidates in higher buckets are all taken and
-//      set their bit in the output bitmap; digit 2 (bits 19..10) of the bucket's keys, and
-//      the bucket compacted (keys and coordinates);
-//   3. k_select2 (one block): digit 3 (bits 9..0) of the bucket gives the k-th key tau and
-//      how many keys equal to tau are taken; if not all of them, the largest coordinate iota
-//      taken among them (lowest coordinates win), by rank or by three index digits;
-//   4. k_mark: the bucket's keys > tau, or == tau with index <= iota, set their bit;
-//   5. k_emit: the bitmap is turned into ascending indices in one pass (each block counts
-//      its words and takes its offset from the blocks before it by a decoupled look-back).
+//   1. candidates: either every coordinate whose key reaches the pruned pass's sampled bound
+//      (k_sample, k_heavy, then k_pruned or k_planes and k_combine: bound, heavy-cell map, survivor
+//      estimates, with the candidates' histogram in fine bins), or every coordinate, from the full
+//      estimate (k_unsketch, k_unsketch_hm, or k_push by tile and k_median);
+//   2. k_digit2 (many blocks): each block finds the bin of the k-th key in the candidates'
+//      histogram; candidates above it are taken and set their bit in the output bitmap; the bin is
+//      compacted (keys and coordinates), twice where a large dense selection's bin is crowded;
+//   3. k_emit (k_emit.hip): the cut inside the bin, the ascending indices, the values and the reset.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -107,6 +101,69 @@ __global__ void __launch_bounds__(kBlock) k_unsketch(HashSet hs, const float* __
   }
 }
 
+// The full estimate from k_push's row values, four coordinates per thread and pass; the rows from
+// `pushed` on (no scratch for them) are read from the table. keys may be rows.p[0]: a
+// thread reads its coordinates' values before it writes their keys.
+constexpr int kMedianBlock = 1024;
+template <int R, bool HM>
+__global__ void __launch_bounds__(kMedianBlock) k_median(HashSet hs, const float* __restrict__ merged, int64_t d,
+                                                         RowValues rows, int pushed, const uint32_t* __restrict__ rnd,
+                                                         float* __restrict__ est, uint32_t* keys,
+                                                         uint32_t* __restrict__ hist, SelectCtl* __restrict__ ctl) {
+  __shared__ uint32_t h[kDigit1Bins];
+  __shared__ uint32_t nh;
+  for (int b = threadIdx.x; b < kDigit1Bins; b += kMedianBlock) h[b] = 0u;
+  if (threadIdx.x == 0) nh = 0u;
+  const double theta = HM ? ctl->theta : 0.0;
+  __syncthreads();
+  uint32_t mine = 0;
+  constexpr int U = 4;
+  for (int64_t b0 = (int64_t)blockIdx.x * kMedianBlock * U; b0 < d; b0 += (int64_t)gridDim.x * kMedianBlock * U) {
+    float val[U][R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (j < pushed) {
+#pragma unroll
+        for (int m = 0; m < U; ++m) {
+          const int64_t i = b0 + m * kMedianBlock + threadIdx.x;
+          val[m][j] = i < d ? rows.p[j][i] : 0.f;
+        }
+      } else {
+        const RowConst k = row_const(hs, j);
+#pragma unroll
+        for (int m = 0; m < U; ++m) {  // a column is valid for any hash value
+          uint32_t col, sflip;
+          hash_row(k, (uint32_t)(b0 + m * kMedianBlock + threadIdx.x), col, sflip);
+          val[m][j] = apply_sign(merged[(int64_t)j * k.c + col], sflip);
+        }
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < U; ++m) {
+      const int64_t i = b0 + m * kMedianBlock + threadIdx.x;
+      if (i >= d) break;
+      sort_net<R>(val[m]);
+      const float e = median_sorted<R>(val[m]);
+      if (est) est[i] = e;
+      uint32_t key = abs_key(e);
+      if constexpr (HM) {
+        const bool heavy = (double)e * (double)e >= theta;
+        key = heavy ? 0x80000000u | key : rnd[i] >> 1;
+        mine += heavy ? 1u : 0u;
+      }
+      keys[i] = key;
+      atomicAdd(&h[key >> (HM ? 20 : 19)], 1u);  // cand_bin's coarse bins
+    }
+  }
+  if (HM && mine) atomicAdd(&nh, mine);
+  __syncthreads();
+  for (int b = threadIdx.x; b < kDigit1Bins; b += kMedianBlock) {
+    const uint32_t n = h[b];
+    if (n) atomicAdd(&hist[b], n);
+  }
+  if (HM && threadIdx.x == 0 && nh) atomicAdd(&ctl->n_heavy, (unsigned long long)nh);
+}
+
 // ------------------------------------------------------------------------------------
 // Step 2: the digit pass. Candidates are either the pruned pass's (keys in cand_key, coordinates in
 // cand_idx, fine bins in hist_c) or dense (after the full estimate: every coordinate, key in
@@ -114,6 +171,7 @@ __global__ void __launch_bounds__(kBlock) k_unsketch(HashSet hs, const float* __
 
 constexpr int kDigit2Block = 1024;           // threads per k_digit2 block
 constexpr int kStageBuf = 8 * kDigit2Block;  // per-block LDS buffer of k_digit2 (keys and coordinates)
+constexpr int64_t kTwoMinK = 16384;          // dense selections beyond this k take a second digit pass
 constexpr int kCountMax = 1024;              // emit ranges counted in LDS: all of them up to d = 2^29
 
 struct DigitArgs {
@@ -138,12 +196,14 @@ struct DigitArgs {
 
 // Many blocks: every block finds the bin of the k-th key in the histogram (block 0 records it);
 // keys above it are taken (their bit in the output bitmap: an atomic each, or for dense candidates a
-// ballot per 64 coordinates; and the count of their emit range); the bin is compacted, key and coordinate, through an LDS buffer per
+// ballot per 64 coordinates; and the count of their emit range; a kernel of its own for each: 1.3 us
+// less at d = 4.1M than one that tests); the bin is compacted, key and coordinate, through an LDS buffer per
 // block and one global atomic per flush, with a histogram of the next ten bits on request. Level 1
 // runs the same over the keys staged by level 0, by that next digit: a dense bin holds percents
 // of d, too many for the emit's workgroups to read one by one.
 // When the pruned pass left fewer than k candidates, the blocks instead store every coordinate's
 // key in out_key for the emit.
+template <bool DENSE>
 __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs) {
   union Buf {
     struct {
@@ -154,13 +214,13 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
   };
   __shared__ Buf buf;
   __shared__ uint32_t h[kDigitBins];
-  __shared__ uint32_t cnt[kCountMax];
+  __shared__ uint32_t cnt[DENSE ? 1 : kCountMax];
   __shared__ uint32_t shw[kDigit2Block / 64];
   __shared__ uint32_t res[2];
   __shared__ uint32_t bn, gbase;
   SelectCtl* const ctl = a.ctl;
   const int64_t grid = gridDim.x;
-  if (a.pruned && ctl->n_cand < a.k) {
+  if (!DENSE && a.pruned && ctl->n_cand < a.k) {
     const double theta = ctl->theta;
     for (int64_t i = (int64_t)blockIdx.x * kDigit2Block + threadIdx.x; i < a.d; i += grid * kDigit2Block) {
       const float e = estimate_any(hs, a.merged, (uint32_t)i, buf.rows + threadIdx.x * kMaxRows);
@@ -173,7 +233,7 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
   int64_t n;
   uint32_t need = a.k, klo, khi;
   if (a.level == 0) {
-    n = a.pruned ? (int64_t)ctl->n_cand : a.d;
+    n = DENSE ? a.d : (int64_t)ctl->n_cand;
     find_bucket<kDigit2Block, kDigit1Bins>(a.hist, true, need, shw, res);
     const CandBins bins = cand_bins(a.pruned ? ctl->tau0 : 0u, a.hm != 0, a.hm ? ctl->theta : 0.0, a.pruned != 0);
     klo = (uint32_t)cand_bin_lo(bins, res[0]);
@@ -196,18 +256,17 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
   const uint32_t kw = khi - klo;
   const int nsh = 32 - __clz(kw | 1u) - 10;  // shift of the next digit (with hist_next: kw is 2^19 - 1 or 2^20 - 1)
   const int lane = threadIdx.x & 63;
-  const int nr = (int)((a.d + a.range - 1) / a.range);
+  const int nr = DENSE ? 1 : (int)((a.d + a.range - 1) / a.range);
   for (int b = threadIdx.x; b < kDigitBins; b += kDigit2Block) h[b] = 0u;
-  for (int b = threadIdx.x; b < kCountMax; b += kDigit2Block) cnt[b] = 0u;
+  for (int b = threadIdx.x; b < (DENSE ? 1 : kCountMax); b += kDigit2Block) cnt[b] = 0u;
   if (threadIdx.x == 0) bn = 0u;
   __syncthreads();
   const uint32_t range = (uint32_t)a.range;
-  const bool dense = a.idx == nullptr;
   // a dense slice lies in one emit range, and its words of the bitmap are its own
-  const int64_t per = dense ? a.slice : (n + grid - 1) / grid;
-  const int64_t r0 = dense ? blockIdx.x / a.slices * a.range : 0;
-  const int64_t lo = dense ? r0 + blockIdx.x % a.slices * per : blockIdx.x * per;
-  const int64_t hi = min(dense ? min(n, r0 + a.range) : n, lo + per);
+  const int64_t per = DENSE ? a.slice : (n + grid - 1) / grid;
+  const int64_t r0 = DENSE ? (int64_t)(blockIdx.x / a.slices) * a.range : 0;
+  const int64_t lo = DENSE ? r0 + blockIdx.x % a.slices * per : blockIdx.x * per;
+  const int64_t hi = min(DENSE ? min(n, r0 + a.range) : n, lo + per);
   uint32_t mine = 0;  // dense: this wave's keys above the bin
   constexpr int V = 4;
   for (int64_t c0 = lo; c0 < hi; c0 += (int64_t)V * kDigit2Block) {  // block-uniform
@@ -216,13 +275,13 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
     for (int m = 0; m < V; ++m) {
       const int64_t t = c0 + (int64_t)m * kDigit2Block + threadIdx.x;
       key[m] = t < hi ? a.key[t] : 0u;
-      ix[m] = !dense && t < hi ? (uint32_t)a.idx[t] : (uint32_t)t;
+      ix[m] = !DENSE && t < hi ? (uint32_t)a.idx[t] : (uint32_t)t;
     }
 #pragma unroll
     for (int m = 0; m < V; ++m) {
       const int64_t t = c0 + (int64_t)m * kDigit2Block + threadIdx.x;
       const bool above = t < hi && key[m] > khi;
-      if (dense) {
+      if constexpr (DENSE) {
         const uint64_t bal = __ballot(above);
         mine += (uint32_t)__popcll(bal);
         const int64_t w = (t - lane) / 32 + lane;  // slices are multiples of 64 coordinates
@@ -268,10 +327,10 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
       const uint32_t c = h[b];
       if (c) atomicAdd(&a.hist_next[b], c);
     }
-  if (dense) {
+  if constexpr (DENSE) {
     if (lane == 0 && mine) atomicAdd(&cnt[0], mine);
     __syncthreads();
-    if (threadIdx.x == 0 && cnt[0]) atomicAdd(&a.counts[lo / a.range], cnt[0]);
+    if (threadIdx.x == 0 && cnt[0]) atomicAdd(&a.counts[blockIdx.x / a.slices], cnt[0]);
     return;
   }
   for (int b = threadIdx.x; b < min(nr, kCountMax); b += kDigit2Block) {
@@ -1106,6 +1165,26 @@ void launch_unsketch_r(const HashSet& hs, int64_t d, int num_cus, const SelectBu
                        est, b.cand_key, b.hist);
 }
 
+// Every coordinate's estimate of a context: by tile for large d, else directly.
+template <int R, bool HM>
+hipError_t launch_full_r(gs_ctx* x, hipStream_t s, const float* merged, const uint32_t* rnd, float* est) {
+  const SelectBufs b = select_bufs(x);
+  if (x->push) {
+    RowValues rows{};
+    const int n = push_rows(x, &rows);
+    const hipError_t e = launch_push(x, s, merged, rows, n);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_median<R, HM>), dim3(grid_for(x->d, 4 * kMedianBlock, 2 * x->num_cus)), dim3(kMedianBlock), 0,
+                       s, x->hs, merged, x->d, rows, n, rnd, est, b.cand_key, b.hist, x->ctl);
+  } else if constexpr (HM) {
+    hipLaunchKernelGGL(k_unsketch_hm<R>, dim3(grid_for(x->d, kBlock, 4 * x->num_cus)), dim3(kBlock), 0, s, x->hs,
+                       merged, x->d, rnd, est, x->cand_key, x->hist, x->ctl);
+  } else {
+    launch_unsketch_r<R>(x->hs, x->d, x->num_cus, b, s, merged, est);
+  }
+  return hipGetLastError();
+}
+
 template <int R, bool HM>
 void launch_prune_r(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, const uint32_t* rnd) {
   const int M = (int)(x->d < kSampleMax ? x->d : kSampleMax);
@@ -1174,8 +1253,11 @@ hipError_t launch_select_tail(const HashSet& hs, int64_t d, int num_cus, const S
   a.k = (uint32_t)k;
   a.pruned = pruned;
   a.hm = hm;
-  // the second digit pass reads fewer keys than every emit workgroup would otherwise read by itself
-  const bool two = !pruned && d > (1 << 20);
+  // the k-th key's coarse bin holds about k/2 keys (a sixteenth of an octave of a Gaussian's tail);
+  // Up to 8,192 the emit's workgroups keep them in LDS and beyond they read them a few times, so a
+  // second digit pass (8 us) pays from there on: full estimate and selection of 1.1M at k = 5,500 and
+  // 55,000, r = 5: 52.8 and 59 us, against 57 with a second pass and 62 without
+  const bool two = !pruned && k > kTwoMinK;
   if (two) a.hist_next = b.hist2;
   // one block (of 1,024 threads) per four CUs for the pruned candidates (a few times k: fewer
   // blocks add their counts with fewer atomics), more where k is large; the full estimate's dense
@@ -1187,7 +1269,10 @@ hipError_t launch_select_tail(const HashSet& hs, int64_t d, int num_cus, const S
     a.slices = (uint32_t)parts;
     g2 = (d + a.range - 1) / a.range * parts;
   }
-  hipLaunchKernelGGL(k_digit2, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a, hs);
+  if (pruned)
+    hipLaunchKernelGGL(k_digit2<false>, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a, hs);
+  else
+    hipLaunchKernelGGL(k_digit2<true>, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a, hs);
   if (two) {
     DigitArgs a1 = a;
     a1.key = b.keys;
@@ -1198,7 +1283,7 @@ hipError_t launch_select_tail(const HashSet& hs, int64_t d, int num_cus, const S
     a1.out_idx = reinterpret_cast<int32_t*>(b.stage2 + kStage2Cap);
     a1.cap = kStage2Cap;
     a1.level = 1;
-    hipLaunchKernelGGL(k_digit2, dim3(num_cus), dim3(kDigit2Block), 0, s, a1, hs);
+    hipLaunchKernelGGL(k_digit2<false>, dim3(num_cus), dim3(kDigit2Block), 0, s, a1, hs);
   }
   return launch_emit(hs, d, num_cus, b, s, merged, k, pruned, two ? 1 : 0, idx, n_heavy, l2sq, ga);
 }
@@ -1243,7 +1328,9 @@ hipError_t prepare_prune(gs_ctx* x) {
 }
 
 // Whether a selection without an estimate vector prunes.
-static bool prunes(const gs_ctx* x, const float* est) { return est == nullptr && x->d * x->r > x->prune_min_cells; }
+static bool prunes(const gs_ctx* x, const float* est, int64_t k) {
+  return est == nullptr && x->d * x->r > x->prune_min_cells && k * x->prune_max_density <= x->d;
+}
 
 hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, float* est, int32_t* idx,
                                 const GatherArgs* ga) {
@@ -1251,18 +1338,24 @@ hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, i
   // prune_min_cells) that the full estimate is the cheaper chain, every coordinate is
   // estimated. Otherwise the pruned path runs (and the digit pass estimates every coordinate if its
   // candidates fell short of k).
-  if (!prunes(x, est))
-    return launch_unsketch_topk_dense(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, k, est, idx, ga);
+  const bool prune = prunes(x, est, k);
+  hipError_t e = hipSuccess;
   switch (x->r) {
-#define GS_R_CASE(RR) \
-  case RR: launch_prune_r<RR, false>(x, s, merged, k, nullptr); break;
+#define GS_R_CASE(RR)                                                \
+  case RR:                                                           \
+    if (prune)                                                       \
+      launch_prune_r<RR, false>(x, s, merged, k, nullptr);           \
+    else                                                             \
+      e = launch_full_r<RR, false>(x, s, merged, nullptr, est);      \
+    break;
     GS_R_CASE(1) GS_R_CASE(2) GS_R_CASE(3) GS_R_CASE(4) GS_R_CASE(5) GS_R_CASE(6) GS_R_CASE(7) GS_R_CASE(8)
     GS_R_CASE(9) GS_R_CASE(10) GS_R_CASE(11) GS_R_CASE(12) GS_R_CASE(13) GS_R_CASE(14) GS_R_CASE(15) GS_R_CASE(16)
 #undef GS_R_CASE
     default: return hipErrorInvalidValue;
   }
-  return launch_select_tail(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, nullptr, k, 1, 0, idx, nullptr,
-                            nullptr, ga);
+  if (e != hipSuccess) return e;
+  return launch_select_tail(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, nullptr, k, prune ? 1 : 0, 0, idx,
+                            nullptr, nullptr, ga);
 }
 
 hipError_t launch_unsketch_topk_dense(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
@@ -1300,21 +1393,22 @@ hipError_t launch_heavymix_topk(gs_ctx* x, hipStream_t s, const float* merged, i
   hipLaunchKernelGGL(k_theta, dim3(1), dim3(64), 0, s, in, x->r, k, x->ctl);
   // As in launch_unsketch_topk: the full estimate with an estimate vector or a small sketch,
   // else the pruned pass, with the full one acting only if its candidates fell short of k.
-  const bool prune = prunes(x, est);
+  const bool prune = prunes(x, est, k);
+  hipError_t e = hipSuccess;
   switch (x->r) {
 #define GS_R_CASE(RR)                                                                                                \
   case RR:                                                                                                           \
     if (prune)                                                                                                       \
       launch_prune_r<RR, true>(x, s, merged, k, rnd);                                                                \
     else                                                                                                             \
-      hipLaunchKernelGGL(k_unsketch_hm<RR>, dim3(grid_for(x->d, kBlock, 4 * x->num_cus)), dim3(kBlock), 0, s, x->hs, \
-                         merged, x->d, rnd, est, x->cand_key, x->hist, x->ctl);                                      \
+      e = launch_full_r<RR, true>(x, s, merged, rnd, est);                                                           \
     break;
     GS_R_CASE(1) GS_R_CASE(2) GS_R_CASE(3) GS_R_CASE(4) GS_R_CASE(5) GS_R_CASE(6) GS_R_CASE(7) GS_R_CASE(8)
     GS_R_CASE(9) GS_R_CASE(10) GS_R_CASE(11) GS_R_CASE(12) GS_R_CASE(13) GS_R_CASE(14) GS_R_CASE(15) GS_R_CASE(16)
 #undef GS_R_CASE
     default: return hipErrorInvalidValue;
   }
+  if (e != hipSuccess) return e;
   return launch_select_tail(x->hs, x->d, x->num_cus, select_bufs(x), s, merged, rnd, k, prune ? 1 : 0, 1, idx,
                             n_heavy, l2sq, ga);
 }
