@@ -976,23 +976,31 @@ __global__ void __launch_bounds__(kPruneBlock) k_combine(HashSet hs, int64_t d, 
 #pragma unroll
   for (int j = 0; j < R; ++j) kr[j] = row_const(hs, j);
   const uint32_t tau0 = ctl->tau0;
-  // contiguous words per workgroup; its part of the queue starts at its first coordinate
-  const int64_t words = (d + 31) / 32, per = (words + gridDim.x - 1) / gridDim.x;
-  const int64_t lo = blockIdx.x * per, hi = min(words, lo + per);
-  queue += lo * 32;
+  // Chunks of 64 words, a wave's pass, are dealt to the workgroups in turn, so that survivors crowded
+  // in one part of d (one layer's coordinates) still spread over the chip: with a contiguous
+  // part per workgroup, survivors within d/256 were all estimated by one (14.7M x 4: 530 us, 66M x 16:
+  // 2,630 us). A workgroup's part of the queue has room for its coordinates, after those of
+  // the workgroups before it.
+  constexpr int kWaves = kPruneBlock / 64;
+  constexpr int64_t kChunk = 64 * 32;  // coordinates
+  const int64_t words = (d + 31) / 32, chunks = (words + 63) / 64, grid = gridDim.x, wg = blockIdx.x;
+  const int64_t mine = chunks / grid + (wg < chunks % grid ? 1 : 0);
+  int64_t q0 = (wg * (chunks / grid) + min(wg, chunks % grid)) * kChunk;
+  if (wg > (chunks - 1) % grid) q0 -= chunks * kChunk - d;  // the last chunk may be short
+  queue += q0;
   if (threadIdx.x == 0) qs = 0u;
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int64_t row_words = 2 * plane_words;  // 32-bit words per plane
   if constexpr (!HM) {
-    for (int64_t w0 = lo; w0 < hi; w0 += kPruneBlock) {  // block-uniform; one word per thread
-      const int64_t w = w0 + threadIdx.x;
+    for (int64_t t = threadIdx.x >> 6; t < mine; t += kWaves) {  // one word per lane
+      const int64_t w = (wg + t * grid) * 64 + lane;
       uint32_t x[R];
 #pragma unroll
-      for (int j = 0; j < R; ++j) x[j] = w < hi ? planes[j * row_words + w] : 0u;
+      for (int j = 0; j < R; ++j) x[j] = w < words ? planes[j * row_words + w] : 0u;
       uint32_t m = count_reaches<R>(x, need);
-      if (w < hi) bitmap[w] = 0u;
-      if (w >= hi) m = 0u;
+      if (w < words) bitmap[w] = 0u;
+      if (w >= words) m = 0u;
       if (w == words - 1 && (d & 31)) m &= (1u << (d & 31)) - 1u;
       // the wave's survivors take consecutive places: one LDS atomic per wave
       uint32_t before = (uint32_t)__popc(m);
@@ -1010,9 +1018,9 @@ __global__ void __launch_bounds__(kPruneBlock) k_combine(HashSet hs, int64_t d, 
       }
     }
   } else {  // one coordinate per lane: every draw is read as well
-    for (int64_t i0 = lo * 32; i0 < hi * 32; i0 += kPruneBlock) {
-      const int64_t i = i0 + threadIdx.x, w = i >> 5;
-      const bool in = i < min(d, hi * 32);
+    for (int64_t t = threadIdx.x >> 6; t < mine * 32; t += kWaves) {  // 64 coordinates a pass
+      const int64_t i = (wg + t / 32 * grid) * kChunk + t % 32 * 64 + lane, w = i >> 5;
+      const bool in = i < d;
       uint32_t x[R];
 #pragma unroll
       for (int j = 0; j < R; ++j) x[j] = in ? planes[j * row_words + w] : 0u;

@@ -1,0 +1,100 @@
+"""Selections whose time hangs on where in d the large estimates lie, against the same call on a sketch
+without that structure: exact indices, and a time within a small factor (needs an MI355X)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from test_gpu_parity import DEV, host
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+gs = pytest.importorskip("paper_2108_06004_amd")
+
+P31 = synth.MERSENNE_P
+
+
+def sketch_of(x, hp, c):
+    """Count Sketch of a [d] device vector, summed in 64 bits."""
+    r = len(hp["a"])
+    out = torch.zeros((r, c), dtype=torch.float64, device=DEV)
+    i = torch.arange(x.numel(), dtype=torch.int64, device=DEV)
+    for j in range(r):
+        col = (i * int(hp["a"][j]) + int(hp["b"][j])) % P31 % c
+        sign = ((i * int(hp["a2"][j]) + int(hp["b2"][j])) % P31 % 2 * 2 - 1).double()
+        out[j].index_add_(0, col, x.double() * sign)
+    return out.float()
+
+
+def best_us(call, reps=5):
+    """The fastest of `reps` timings of three calls each, in us a call."""
+    call()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(3):
+            call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / 3)
+    return best
+
+
+def values(d, gen):
+    """Small everywhere: the background of the structured vectors below."""
+    return 1e-3 * torch.randn(d, generator=gen, device=DEV)
+
+
+def clustered(d, width, gen):
+    x = values(d, gen)
+    x[d // 2:d // 2 + width] *= 1e3
+    return x
+
+
+def spread(d, width, gen):
+    x = values(d, gen)
+    x[torch.randperm(d, generator=gen, device=DEV)[:width]] *= 1e3
+    return x
+
+
+@pytest.mark.parametrize("d,c,k", [(14_700_000, 1_470_000, 14_700), (25_600_000, 256_000, 25_600)])
+def test_clustered_selection(monkeypatch, d, c, k):
+    # every large coordinate within d / 256 of the others; measured 1.1 to 1.4 times the spread one
+    monkeypatch.delenv("GS_SELECT_PATH", raising=False)
+    r, gen = 5, torch.Generator(device=DEV).manual_seed(d)
+    hp = synth.hash_params(synth.BASE_SEED + 101, r)
+    ctx = gs.GsContext(d, 1, r, c, k, hp)
+    idx, full = (torch.empty(k, dtype=torch.int32, device=DEV) for _ in range(2))
+    est = torch.empty(d, dtype=torch.float32, device=DEV)
+    us = []
+    for make in (spread, clustered):
+        m = sketch_of(make(d, d // 256, gen), hp, c)
+        us.append(best_us(lambda: ctx.unsketch_topk(m, k, idx)))
+        ctx.unsketch_topk(m, k, full, est)
+        assert torch.equal(idx, full)
+    print(f"[clustered] d={d} spread {us[0]:.0f} us, clustered {us[1]:.0f} us", flush=True)
+    assert us[1] < 2.5 * us[0]
+    ctx.close()
+
+
+# chunks of 2,048 coordinates dealt to the workgroups: one short of a round, a full one, one more
+@pytest.mark.parametrize("d", [2_047, 2_049, 524_287, 524_288, 524_289, 526_336, 1_048_577])
+@pytest.mark.parametrize("call", ["topk", "heavymix"])
+def test_survivors_of_every_coordinate(monkeypatch, d, call):
+    # all cells equal: every coordinate survives the row-by-row pass and fills its place in the queue
+    monkeypatch.setenv("GS_SELECT_PATH", "pruned")
+    r, c, k = 4, 400_000, min(d, 1_000)
+    hp = synth.hash_params(synth.BASE_SEED + 103, r)
+    ctx = gs.GsContext(d, 1, r, c, k, hp)
+    m = torch.full((r, c), 0.5, dtype=torch.float32, device=DEV)
+    idx = torch.empty(k, dtype=torch.int32, device=DEV)
+    if call == "topk":
+        ctx.unsketch_topk(m, k, idx)
+        want = oracle.topk(oracle.unsketch(host(m), hp, d), k)[0]
+    else:
+        rnd = np.random.default_rng(d).integers(0, 1 << 32, d, dtype=np.uint64).astype(np.uint32)
+        ctx.heavymix_topk(m, k, torch.from_numpy(rnd.view(np.int32)).to(DEV), idx)
+        want = oracle.heavymix(host(m), hp, d, k, rnd)["idx"]
+    assert np.array_equal(host(idx), want)
+    ctx.close()
