@@ -976,14 +976,15 @@ __global__ void __launch_bounds__(kPruneBlock) k_combine(HashSet hs, int64_t d, 
 #pragma unroll
   for (int j = 0; j < R; ++j) kr[j] = row_const(hs, j);
   const uint32_t tau0 = ctl->tau0;
-  // Chunks of 64 words, a wave's pass, are dealt to the workgroups in turn, so that survivors crowded
+  // Chunks of words, a wave's pass, are dealt to the workgroups in turn, so that survivors crowded
   // in one part of d (one layer's coordinates) still spread over the chip: with a contiguous
   // part per workgroup, survivors within d/256 were all estimated by one (14.7M x 4: 530 us, 66M x 16:
   // 2,630 us). A workgroup's part of the queue has room for its coordinates, after those of
   // the workgroups before it.
   constexpr int kWaves = kPruneBlock / 64;
-  constexpr int64_t kChunk = 64 * 32;  // coordinates
-  const int64_t words = (d + 31) / 32, chunks = (words + 63) / 64, grid = gridDim.x, wg = blockIdx.x;
+  constexpr int kWords = HM ? 16 : 64;  // HEAVYMIX: smaller chunks, more waves for the draws' loads
+  constexpr int64_t kChunk = kWords * 32;  // coordinates
+  const int64_t words = (d + 31) / 32, chunks = (words + kWords - 1) / kWords, grid = gridDim.x, wg = blockIdx.x;
   const int64_t mine = chunks / grid + (wg < chunks % grid ? 1 : 0);
   int64_t q0 = (wg * (chunks / grid) + min(wg, chunks % grid)) * kChunk;
   if (wg > (chunks - 1) % grid) q0 -= chunks * kChunk - d;  // the last chunk may be short
@@ -992,46 +993,42 @@ __global__ void __launch_bounds__(kPruneBlock) k_combine(HashSet hs, int64_t d, 
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int64_t row_words = 2 * plane_words;  // 32-bit words per plane
-  if constexpr (!HM) {
-    for (int64_t t = threadIdx.x >> 6; t < mine; t += kWaves) {  // one word per lane
-      const int64_t w = (wg + t * grid) * 64 + lane;
-      uint32_t x[R];
+  for (int64_t t = threadIdx.x >> 6; t < mine; t += kWaves) {  // one word per lane
+    const int64_t chunk = wg + t * grid, w = lane < kWords ? chunk * kWords + lane : words;
+    uint32_t x[R];
 #pragma unroll
-      for (int j = 0; j < R; ++j) x[j] = w < words ? planes[j * row_words + w] : 0u;
-      uint32_t m = count_reaches<R>(x, need);
-      if (w < words) bitmap[w] = 0u;
-      if (w >= words) m = 0u;
-      if (w == words - 1 && (d & 31)) m &= (1u << (d & 31)) - 1u;
-      // the wave's survivors take consecutive places: one LDS atomic per wave
-      uint32_t before = (uint32_t)__popc(m);
+    for (int j = 0; j < R; ++j) x[j] = w < words ? planes[j * row_words + w] : 0u;
+    uint32_t m = count_reaches<R>(x, need);
+    if (w < words) bitmap[w] = 0u;
+    if (w >= words) m = 0u;
+    if (w == words - 1 && (d & 31)) m &= (1u << (d & 31)) - 1u;
+    if constexpr (HM) {
+      // the chunk's draws, 64 coordinates a load: their ballots are the words of lanes 2 q and 2 q + 1
+      // (a coordinate per lane, which reads each word of the planes 32 times: 15M x 4 51 us, so 27, 1M 13, so
+      // 12; chunks of 64 words: 36 and 19 us)
+      constexpr int D = kWords / 2;
+      uint32_t draw[D];
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(before, o, 64);
-        if (lane >= o) before += y;
-      }
-      uint32_t base = 0u;
-      if (lane == 63 && before) base = atomicAdd(&qs, before);
-      base = __shfl(base, 63) + before - (uint32_t)__popc(m);
-      while (m) {
-        queue[base++] = (uint32_t)(32 * w + __ffs(m) - 1);
-        m &= m - 1u;
+      for (int q = 0; q < D; ++q) draw[q] = rnd[min(chunk * kChunk + q * 64 + lane, d - 1)] >> 1;
+#pragma unroll
+      for (int q = 0; q < D; ++q) {
+        const uint64_t bal = __ballot(chunk * kChunk + q * 64 + lane < d && draw[q] >= tau0);
+        if ((lane >> 1) == q) m |= (uint32_t)(lane & 1 ? bal >> 32 : bal);
       }
     }
-  } else {  // one coordinate per lane: every draw is read as well
-    for (int64_t t = threadIdx.x >> 6; t < mine * 32; t += kWaves) {  // 64 coordinates a pass
-      const int64_t i = (wg + t / 32 * grid) * kChunk + t % 32 * 64 + lane, w = i >> 5;
-      const bool in = i < d;
-      uint32_t x[R];
+    // the wave's survivors take consecutive places: one LDS atomic per wave
+    uint32_t before = (uint32_t)__popc(m);
 #pragma unroll
-      for (int j = 0; j < R; ++j) x[j] = in ? planes[j * row_words + w] : 0u;
-      const uint32_t draw = in ? rnd[i] >> 1 : 0u;
-      if (in && (i & 31) == 0) bitmap[w] = 0u;
-      const bool keep = in && (((count_reaches<R>(x, need) >> (i & 31)) & 1u) || draw >= tau0);
-      const uint64_t bal = __ballot(keep);
-      uint32_t base = 0u;
-      if (lane == 0 && bal) base = atomicAdd(&qs, (uint32_t)__popcll(bal));
-      base = __shfl(base, 0);
-      if (keep) queue[base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull))] = (uint32_t)i;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(before, o, 64);
+      if (lane >= o) before += y;
+    }
+    uint32_t base = 0u;
+    if (lane == 63 && before) base = atomicAdd(&qs, before);
+    base = __shfl(base, 63) + before - (uint32_t)__popc(m);
+    while (m) {
+      queue[base++] = (uint32_t)(32 * w + __ffs(m) - 1);
+      m &= m - 1u;
     }
   }
   __syncthreads();

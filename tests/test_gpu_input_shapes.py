@@ -78,8 +78,9 @@ def test_clustered_selection(monkeypatch, d, c, k):
     ctx.close()
 
 
-# chunks of 2,048 coordinates dealt to the workgroups: one short of a round, a full one, one more
-@pytest.mark.parametrize("d", [2_047, 2_049, 524_287, 524_288, 524_289, 526_336, 1_048_577])
+# chunks of 2,048 coordinates (512 with HEAVYMIX) dealt to the workgroups: one short of a round, a full
+# one, one more
+@pytest.mark.parametrize("d", [511, 513, 2_047, 2_049, 131_071, 131_073, 524_287, 524_288, 524_289, 526_336, 1_048_577])
 @pytest.mark.parametrize("call", ["topk", "heavymix"])
 def test_survivors_of_every_coordinate(monkeypatch, d, call):
     # all cells equal: every coordinate survives the row-by-row pass and fills its place in the queue
