@@ -151,8 +151,8 @@ struct gs_ctx {
   uint32_t* coarse = nullptr;       // coarse heavy-cell map (bit = OR of its cells' heavy bits)
   uint64_t* planes = nullptr;       // [r][ceil(d/64)] heavy bit of every coordinate per row, where they are
                                     // looked up row by row
-  int64_t plane_fine = 0;           // cells of a row with a bit of their own; the others share one, 2^fold to a bit
-  int plane_fold = 0;
+  int64_t plane_fine = 0;           // cells of a row with a bit of their own; the others share one, two to a bit
+  bool plane_fold = false;
   int prune_buf_cap = 0;            // LDS candidate buffer entries of the pruned pass
   // selections without an estimate vector prune when d*r exceeds this (0: always); below it
   // the full estimate takes fewer launches than the pruned pass's chain

@@ -833,21 +833,32 @@ __global__ void __launch_bounds__(kPruneBlock) k_pruned(HashSet hs, int64_t d, S
 // up one row per workgroup (the workgroups are dealt over the rows), whose bits do fit or nearly,
 // and writes the row's bit of every coordinate as a bit plane (d/8 bytes); k_combine counts the r
 // bits of 32 coordinates at a time and estimates the survivors. A row of more than kPlaneBits cells
-// keeps its first `fine` cells one bit each and folds the rest, 2^fold cells to a bit that is set
-// when any of them is heavy, so that the row fits exactly: a folded bit can only add survivors,
-// whose estimate decides.
+// keeps its first `fine` cells one bit each and folds the rest, two cells to a bit that is set
+// when either is heavy, so that the row fits exactly: a folded bit can only add survivors,
+// whose estimate decides. Each workgroup folds its row as it loads it, 16 bytes a lane (bit by
+// bit that cost more than the lookups: 4M, r = 4, c = 2.4M, the selection 133 us, so 77).
 // Against k_pruned with all rows folded 8 to 32 cells to a bit, where most coordinates have
 // to confirm their set bits in the global map and the pass is bound by L2 requests (66M x 16,
 // r = 7: 69% of the folded bits set, 161M requests): the selection takes 448 against 891 us there,
 // 138 against 158 at 14.7M x 4 (c = 1.47M), 120 against 166 at 20M x 2 (c = 600,000), 262 against 314 at
-// 22M x 12 (c = 2.05M, k = 0.5%). It is used while a row is folded by two at most and for four rows or
+// 22M x 12 (c = 2.05M, k = 0.5%); over d of 1M to 30M, c of 1.25M to 2.4M, r = 4 and 7, a folded row takes
+// 0.64 to 1.05 of it (the largest ratio at 1M, c = 1.25M, r = 4: 66 against 63 us). It is used while a row is folded by two at most and for four rows or
 // more: folded by four it lost (50M x 2, r = 7, c = 5M: 1,571 against 1,237 us), and with three rows it
 // gained nothing (15M x 4, c = 1.5M: 136 against 131 us).
 constexpr int64_t kPlaneBits = (kPruneLdsWords - 64) / 4 * 4 * 32ll;
 
+// Bit q of the result: bit 2 q or 2 q + 1 of x.
+__device__ __forceinline__ uint32_t pair_bits(uint32_t x) {
+  x = (x | (x >> 1)) & 0x55555555u;
+  x = (x | (x >> 1)) & 0x33333333u;
+  x = (x | (x >> 2)) & 0x0f0f0f0fu;
+  x = (x | (x >> 4)) & 0x00ff00ffu;
+  return (x | (x >> 8)) & 0x0000ffffu;
+}
+
 template <bool FOLD>
 __global__ void __launch_bounds__(kPruneBlock) k_planes(HashSet hs, int64_t d, const uint32_t* __restrict__ heavy,
-                                                        int64_t hrow, int64_t fine, int fold,
+                                                        int64_t hrow, int64_t fine,
                                                         uint64_t* __restrict__ planes, int64_t plane_words,
                                                         uint32_t* __restrict__ hist_s) {
   constexpr int U = 8;  // coordinates per lane per pass
@@ -872,19 +883,23 @@ __global__ void __launch_bounds__(kPruneBlock) k_planes(HashSet hs, int64_t d, c
     }
   }
   if constexpr (FOLD) {
-    // folded word w holds the cells fine + (32 w + b) * 2^fold of bits b: 2^fold source words
-    const int64_t rest = (hrow >> 5) - (fine >> 5), nf = (rest + (1ll << fold) - 1) >> fold;
-    const int per = 32 >> fold;  // folded bits from one source word
-    const uint32_t group = fold == 5 ? 0xffffffffu : (1u << (1 << fold)) - 1u;
-    for (int64_t w = threadIdx.x; w < nf; w += kPruneBlock) {
-      uint32_t out = 0u;
-      for (int f = 0; f < (1 << fold); ++f) {
-        const int64_t sw = (w << fold) + f;
-        const uint32_t x = sw < rest ? src[(fine >> 5) + sw] : 0u;
-        for (int q = 0; q < per; ++q)
-          if ((x >> (q << fold)) & group) out |= 1u << (f * per + q);
+    // the rest in pairs of cells: four source words make two folded ones
+    const uint4* const rest = reinterpret_cast<const uint4*>(src) + f4;
+    uint2* const out2 = reinterpret_cast<uint2*>(sm + (fine >> 5));
+    const int64_t n4 = (hrow - fine) >> 7;
+    for (int64_t w0 = 0; w0 < n4; w0 += 8 * kPruneBlock) {
+      uint4 t[8];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const int64_t w = w0 + m * kPruneBlock + threadIdx.x;
+        if (w < n4) t[m] = rest[w];
       }
-      sm[(fine >> 5) + w] = out;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const int64_t w = w0 + m * kPruneBlock + threadIdx.x;
+        if (w < n4)
+          out2[w] = make_uint2(pair_bits(t[m].x) | pair_bits(t[m].y) << 16, pair_bits(t[m].z) | pair_bits(t[m].w) << 16);
+      }
     }
   }
   const RowConst k = row_const(hs, j);
@@ -914,7 +929,7 @@ __global__ void __launch_bounds__(kPruneBlock) k_planes(HashSet hs, int64_t d, c
       uint32_t e = cb[m];
       if constexpr (FOLD) {
         const int32_t over = max((int32_t)(e - (uint32_t)fine), 0);  // cells beyond the fine ones
-        e = e - (uint32_t)over + ((uint32_t)over >> fold);
+        e = e - (uint32_t)over + ((uint32_t)over >> 1);
       }
       bit[m] = bit_at(sm[e >> 5], e);
       const uint32_t t = hb[m] + db;
@@ -1209,10 +1224,10 @@ void launch_prune_r(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, co
     const int wgs = std::max(1, x->num_cus / x->r) * x->r;
     if (x->plane_fold)
       hipLaunchKernelGGL(k_planes<true>, dim3(wgs), dim3(kPruneBlock), 0, s, x->hs, x->d, x->heavy, x->heavy_row,
-                         x->plane_fine, x->plane_fold, x->planes, plane_words, x->hist_s);
+                         x->plane_fine, x->planes, plane_words, x->hist_s);
     else
       hipLaunchKernelGGL(k_planes<false>, dim3(wgs), dim3(kPruneBlock), 0, s, x->hs, x->d, x->heavy, x->heavy_row,
-                         x->plane_fine, 0, x->planes, plane_words, x->hist_s);
+                         x->plane_fine, x->planes, plane_words, x->hist_s);
     hipLaunchKernelGGL((k_combine<R, HM>), dim3(x->num_cus), dim3(kPruneBlock), 0, s, x->hs, x->d, x->ctl,
                        reinterpret_cast<const uint32_t*>(x->planes), plane_words, x->keys, x->bitmap, rnd, merged,
                        x->cand_key, x->cand_idx, x->hist_c, x->plane_fold ? x->heavy : nullptr, x->heavy_row);
@@ -1310,7 +1325,7 @@ hipError_t prepare_prune(gs_ctx* x) {
     map_words += map_words & 1;
   }
   if (log2g > 0 && x->r >= 4 && x->heavy_row <= 2 * (kPlaneBits - 128)) {
-    x->plane_fold = x->heavy_row > kPlaneBits ? 1 : 0;
+    x->plane_fold = x->heavy_row > kPlaneBits;
     // folded by two: `fine` cells as they are and (row - fine) / 2 bits after them fill kPlaneBits - 128
     x->plane_fine = x->plane_fold ? (2 * (kPlaneBits - 128) - x->heavy_row) / 128 * 128 : x->heavy_row;
     const hipError_t e =

@@ -99,3 +99,20 @@ def test_survivors_of_every_coordinate(monkeypatch, d, call):
         want = oracle.heavymix(host(m), hp, d, k, rnd)["idx"]
     assert np.array_equal(host(idx), want)
     ctx.close()
+
+
+def test_folded_rows_cost_little_more(monkeypatch):
+    # rows of 2.4M cells, two to a bit, against 1.2M cells with a bit each; measured 1.1
+    monkeypatch.delenv("GS_SELECT_PATH", raising=False)
+    d, r, k = 4_000_003, 4, 4_000
+    us = []
+    for c in (1_200_000, 2_400_000):
+        hp = synth.hash_params(synth.BASE_SEED + 105, r)
+        m = torch.randn((r, c), generator=torch.Generator(device=DEV).manual_seed(c), device=DEV)
+        m *= torch.exp(2.0 * torch.randn((r, c), generator=torch.Generator(device=DEV).manual_seed(c + 1), device=DEV))
+        ctx = gs.GsContext(d, 1, r, c, k, hp)
+        idx = torch.empty(k, dtype=torch.int32, device=DEV)
+        us.append(best_us(lambda: ctx.unsketch_topk(m, k, idx)))
+        ctx.close()
+    print(f"[folded] {us[0]:.0f} us, folded {us[1]:.0f} us", flush=True)
+    assert us[1] < 1.5 * us[0]
