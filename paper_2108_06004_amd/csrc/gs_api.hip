@@ -226,8 +226,12 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
     // The full estimate reads a table that outgrows an XCD's 4 MB L2 by tile (one fill per line
     // instead of one per read: 14.7M, c = 1.47M: 1,127 -> 600 us, 4M, c = 400,000: 187 -> 147 us), a
     // smaller one directly (25.6M, r x c = 5 x 256,000: 725 against 777 us, 2M, 5 x 50,000: 75 against
-    // 79 us). GS_ESTIMATE_PATH=tiles or =direct fixes the choice.
-    x->push = x->d >= gs::kPushMinD && (int64_t)x->r * x->c * (int64_t)sizeof(float) > gs::kPushMinTable;
+    // 79 us). The tiles' cells are a permutation of the columns, so loading them costs a line a
+    // cell: beyond 3/4 d columns reading only the cells that coordinates have is cheaper (r = 3 and 5,
+    // d = 1M, 4M, 14.7M: by tile 0.55 to 0.95 of the direct time at c = 0.7 d, 0.8 to 1.4 at c = d, 1.0 to
+    // 1.7 at 1.4 d). GS_ESTIMATE_PATH=tiles or =direct fixes the choice.
+    x->push = x->d >= gs::kPushMinD && (int64_t)x->r * x->c * (int64_t)sizeof(float) > gs::kPushMinTable &&
+              4 * x->c <= 3 * x->d;
     const char* est = std::getenv("GS_ESTIMATE_PATH");
     if (est && std::strcmp(est, "tiles") == 0) x->push = true;
     if (est && std::strcmp(est, "direct") == 0) x->push = false;

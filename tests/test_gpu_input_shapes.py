@@ -116,3 +116,27 @@ def test_folded_rows_cost_little_more(monkeypatch):
         ctx.close()
     print(f"[folded] {us[0]:.0f} us, folded {us[1]:.0f} us", flush=True)
     assert us[1] < 1.5 * us[0]
+
+
+@pytest.mark.parametrize("d,r,c", [(4_000_003, 3, 16_000_000), (4_000_003, 5, 400_000), (14_700_000, 5, 14_700_000)])
+def test_full_estimate_takes_the_cheaper_form(monkeypatch, d, r, c):
+    # tables wide and narrow against d: the rule's choice within 1.3 of the better form (the forms
+    # measured 3.7, 1.3 and 1.4 apart)
+    k, us = 1_000, {}
+    hp = synth.hash_params(synth.BASE_SEED + 107, r)
+    m = torch.randn((r, c), generator=torch.Generator(device=DEV).manual_seed(c), device=DEV)
+    est, idx = torch.empty(d, dtype=torch.float32, device=DEV), torch.empty(k, dtype=torch.int32, device=DEV)
+    got = []
+    for form in ("tiles", "direct", None):
+        if form:
+            monkeypatch.setenv("GS_ESTIMATE_PATH", form)
+        else:
+            monkeypatch.delenv("GS_ESTIMATE_PATH")
+        ctx = gs.GsContext(d, 1, r, c, k, hp)
+        us[form] = best_us(lambda: ctx.unsketch_topk(m, k, idx, est))
+        ctx.close()
+        got.append((host(idx).copy(), host(est).copy()))
+    print(f"[forms] d={d} r={r} c={c}: {us}", flush=True)
+    for i, e in got[1:]:
+        assert np.array_equal(i, got[0][0]) and np.array_equal(e, got[0][1])
+    assert us[None] < 1.3 * min(us["tiles"], us["direct"])
