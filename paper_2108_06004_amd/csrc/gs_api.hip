@@ -220,8 +220,7 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
     // GS_SELECT_PATH=pruned prunes every selection without an estimate vector, =full none
     x->prune_min_cells = gs::kPruneMinCells;
     const char* sel = std::getenv("GS_SELECT_PATH");
-    x->prune_max_density = 1;
-    if (sel && std::strcmp(sel, "pruned") == 0) x->prune_min_cells = x->prune_max_density = 0;
+    if (sel && std::strcmp(sel, "pruned") == 0) x->prune_min_cells = 0;
     if (sel && std::strcmp(sel, "full") == 0) x->prune_min_cells = INT64_MAX;
     // The full estimate reads a table that outgrows an XCD's 4 MB L2 by tile (one fill per line
     // instead of one per read: 14.7M, c = 1.47M: 1,127 -> 600 us, 4M, c = 400,000: 187 -> 147 us), a
@@ -230,17 +229,26 @@ gs_status gs_create(const gs_config* cfg, gs_ctx** out) {
     // cell: beyond 3/4 d columns reading only the cells that coordinates have is cheaper (r = 3 and 5,
     // d = 1M, 4M, 14.7M: by tile 0.55 to 0.95 of the direct time at c = 0.7 d, 0.8 to 1.4 at c = d, 1.0 to
     // 1.7 at 1.4 d). GS_ESTIMATE_PATH=tiles or =direct fixes the choice.
-    x->push = x->d >= gs::kPushMinD && (int64_t)x->r * x->c * (int64_t)sizeof(float) > gs::kPushMinTable &&
-              4 * x->c <= 3 * x->d;
+    const bool wide = (int64_t)x->r * x->c * (int64_t)sizeof(float) > gs::kPushMinTable;
+    x->push = x->d >= gs::kPushMinD && wide && 4 * x->c <= 3 * x->d;
     const char* est = std::getenv("GS_ESTIMATE_PATH");
     if (est && std::strcmp(est, "tiles") == 0) x->push = true;
     if (est && std::strcmp(est, "direct") == 0) x->push = false;
     x->push = x->push && x->use_pull;
     // Selections of a large part of d estimate every coordinate: the pruned pass's survivors read the
-    // table at random. The line lies where the two cost the same (14.7M, by tile: 549 against 590 us
-    // at k = 0.0725 d, 783 against 595 at 0.125 d; 25.6M, directly: 528 against 725 at 0.125 d, 877
-    // against 725 at 0.25 d).
-    if (x->prune_max_density) x->prune_max_density = x->push ? 10 : 5;
+    // table at random. The lines lie about where the two cost the same. By tile, a tenth (14.7M, c =
+    // 1.47M, k = 0.1 d: r = 5 573 pruned, 601 us; r = 7, c = 700,000 752 and 645; 4M, c = 400,000 r = 5 132
+    // and 145, r = 7 199 and 199; r = 3 crosses at 0.06), with HEAVYMIX of five to eight rows a
+    // sixth (the same four at 0.14 d: 533 and 682, 620 and 720, 140 and 164, 174 and 223 us; at 0.2 d 703
+    // and 687, 857 and 716, 170 and 166, 210 and 224; r = 3 crosses at 0.08, r = 16 at 0.1 and 0.19).
+    // Directly, a fifth (25.6M, c = 256,000: 765 and 736 us; 4M, c = 60,000 142 and 127), a large table too
+    // wide for the tiles a third (4M, c = 4M at 0.28 d 356 and 401 us, at 0.4 d 446 and 401; 14.7M, c = 12M
+    // 1,396 and 1,461, 1,783 and 1,475; 1M, c = 1M and 4M, r = 3, c = 16M cross at 0.2).
+    const int64_t topk = x->push ? 10 : wide && x->d >= gs::kPushMinD ? 3 : 5;
+    const int64_t hm = x->push && x->r >= 5 && x->r <= 8 ? 6 : topk;
+    const bool always = sel && std::strcmp(sel, "pruned") == 0;
+    x->prune_max_density[0] = always ? 0 : topk;
+    x->prune_max_density[1] = always ? 0 : hm;
   }
   if (x->use_pull) {
     x->list_cap = (int64_t)x->r * x->d + (int64_t)gs::kListGroup * x->plan.T;

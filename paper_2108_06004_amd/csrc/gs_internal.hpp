@@ -157,7 +157,7 @@ struct gs_ctx {
   // selections without an estimate vector prune when d*r exceeds this (0: always); below it
   // the full estimate takes fewer launches than the pruned pass's chain
   int64_t prune_min_cells = 0;
-  int64_t prune_max_density = 0;  // and when k * this is at most d
+  int64_t prune_max_density[2] = {0, 0};  // and when k * this is at most d (the top-k, HEAVYMIX)
   bool push = false;              // the full estimate reads the table by tile
   // gather-based sketch (used when the plan fits; otherwise fp64 atomics into acc64)
   bool use_pull = false;

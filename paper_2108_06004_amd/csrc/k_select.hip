@@ -1348,8 +1348,8 @@ hipError_t prepare_prune(gs_ctx* x) {
 }
 
 // Whether a selection without an estimate vector prunes.
-static bool prunes(const gs_ctx* x, const float* est, int64_t k) {
-  return est == nullptr && x->d * x->r > x->prune_min_cells && k * x->prune_max_density <= x->d;
+static bool prunes(const gs_ctx* x, const float* est, int64_t k, bool hm) {
+  return est == nullptr && x->d * x->r > x->prune_min_cells && k * x->prune_max_density[hm ? 1 : 0] <= x->d;
 }
 
 hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, float* est, int32_t* idx,
@@ -1358,7 +1358,7 @@ hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, i
   // prune_min_cells) that the full estimate is the cheaper chain, every coordinate is
   // estimated. Otherwise the pruned path runs (and the digit pass estimates every coordinate if its
   // candidates fell short of k).
-  const bool prune = prunes(x, est, k);
+  const bool prune = prunes(x, est, k, false);
   hipError_t e = hipSuccess;
   switch (x->r) {
 #define GS_R_CASE(RR)                                                \
@@ -1413,7 +1413,7 @@ hipError_t launch_heavymix_topk(gs_ctx* x, hipStream_t s, const float* merged, i
   hipLaunchKernelGGL(k_theta, dim3(1), dim3(64), 0, s, in, x->r, k, x->ctl);
   // As in launch_unsketch_topk: the full estimate with an estimate vector or a small sketch,
   // else the pruned pass, with the full one acting only if its candidates fell short of k.
-  const bool prune = prunes(x, est, k);
+  const bool prune = prunes(x, est, k, true);
   hipError_t e = hipSuccess;
   switch (x->r) {
 #define GS_R_CASE(RR)                                                                                                \

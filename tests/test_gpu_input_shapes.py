@@ -140,3 +140,32 @@ def test_full_estimate_takes_the_cheaper_form(monkeypatch, d, r, c):
     for i, e in got[1:]:
         assert np.array_equal(i, got[0][0]) and np.array_equal(e, got[0][1])
     assert us[None] < 1.3 * min(us["tiles"], us["direct"])
+
+
+@pytest.mark.parametrize("d,r,c,k", [(14_700_000, 5, 1_470_000, 1_764_000), (14_700_000, 5, 1_470_000, 3_675_000),
+                                     (4_000_003, 5, 4_000_000, 840_000)])
+@pytest.mark.parametrize("call", ["topk", "heavymix"])
+def test_large_selection_takes_the_cheaper_form(monkeypatch, d, r, c, k, call):
+    # an eighth, a quarter and a fifth of d: the density rule's choice within 1.25 of the better form (the
+    # forms measured up to 2.0 apart; HEAVYMIX at an eighth 1.45)
+    hp = synth.hash_params(synth.BASE_SEED + 109, r)
+    gen = torch.Generator(device=DEV).manual_seed(k)
+    x = torch.randn(d, generator=gen, device=DEV)
+    m = sketch_of(x * torch.exp(1.5 * torch.randn(d, generator=gen, device=DEV)), hp, c)
+    rnd = torch.empty(d, dtype=torch.int32, device=DEV).random_(-(1 << 31), 1 << 31, generator=gen)
+    idx, us, got = torch.empty(k, dtype=torch.int32, device=DEV), {}, []
+    for form in ("pruned", "full", None):
+        if form:
+            monkeypatch.setenv("GS_SELECT_PATH", form)
+        else:
+            monkeypatch.delenv("GS_SELECT_PATH")
+        ctx = gs.GsContext(d, 4, r, c, k, hp)
+        if call == "topk":
+            us[form] = best_us(lambda: ctx.unsketch_topk(m, k, idx))
+        else:
+            us[form] = best_us(lambda: ctx.heavymix_topk(m, k, rnd, idx))
+        ctx.close()
+        got.append(idx.clone())
+    print(f"[density] {call} d={d} k={k}: {us}", flush=True)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    assert us[None] < 1.25 * min(us["pruned"], us["full"])
