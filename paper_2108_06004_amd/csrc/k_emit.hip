@@ -19,6 +19,8 @@
 // histograms give the k-th key, and one more pass the marks of the own range and the entries before
 // it; ties at the k-th key are taken in coordinate order (a zero sketch of 14.7M: 9 ms, and 60 ms
 // by one workgroup alone). No workgroup ever waits for another.
+#include <algorithm>
+
 #include "gs_internal.hpp"
 #include "gs_select.hpp"
 
@@ -344,9 +346,19 @@ hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBu
   a.pruned = pruned;
   a.level = level;
   const unsigned blocks = (unsigned)((d + a.range - 1) / a.range);
+  // The emit gathers what each workgroup has written, unless one could have so much of it (the selection
+  // in one part of d, a layer's gradients) that it would work alone: more than 12 passes of its threads,
+  // in a selection of at most d/8. With all large estimates within d/256, 66M x 16 takes 10.9 ms so, 10.1
+  // with a gather of its own, 25.6M x 8 worker-major 1,968 and 1,662 us, 14.7M x 4 712 and 675; where they
+  // are spread the kernel more costs 2 us (14.7M x 4 659 and 661; 1.2M x 6, 12 passes at most, 119
+  // and 122). Beyond d/8 no workgroup has more than 8 times the mean (14.7M x 4, k = d/4: spread
+  // 1,402 and 1,437 us, in one quarter of d 1,431 and 1,454).
+  const bool own = !ga || std::min(k, a.range) * ga->gl <= 12 * kBlock || 8 * k > d;
   hipLaunchKernelGGL(k_emit, dim3(blocks), dim3(kBlock), (size_t)(a.range / 32) * sizeof(uint32_t), s, a, hs,
-                     ga ? *ga : GatherArgs{});
-  return hipGetLastError();
+                     ga && own ? *ga : GatherArgs{});
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || own) return e;
+  return launch_gather(num_cus, s, hs, merged, idx, k, *ga);
 }
 
 hipError_t prepare_emit() {

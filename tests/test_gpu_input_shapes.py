@@ -169,3 +169,61 @@ def test_large_selection_takes_the_cheaper_form(monkeypatch, d, r, c, k, call):
     print(f"[density] {call} d={d} k={k}: {us}", flush=True)
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
     assert us[None] < 1.25 * min(us["pruned"], us["full"])
+
+
+# 12 passes of an emit workgroup's 1,024 lanes at 16 lanes a coordinate: 768 coordinates, and d/8 = 50,000
+@pytest.mark.parametrize("k", [768, 769, 50_000, 50_001])
+@pytest.mark.parametrize("layout", ["worker_major", "interleaved"])
+@pytest.mark.parametrize("call", ["step", "heavymix", "sketch_state"])
+def test_gather_in_the_emit_or_on_its_own(call, layout, k):
+    d, P, r, c, rho = 400_007, 16, 5, 4_001, 0.9
+    if call == "sketch_state":
+        d = 4_000_037  # one lane a coordinate: 12,288, and 50,000 of which at most 15,680 lie in a range
+        k = {768: 12_288, 769: 12_289}.get(k, k)
+    hp = synth.hash_params(synth.BASE_SEED + 111, r)
+    rng = np.random.default_rng(k)
+    ctx = gs.GsContext(d, P if call != "sketch_state" else 1, r, c, k, hp, rho=rho, state_layout=layout)
+    merged = torch.empty((r, c), dtype=torch.float32, device=DEV)
+    idx, values = torch.empty(k, dtype=torch.int32, device=DEV), torch.empty(k, dtype=torch.float32, device=DEV)
+    if call == "sketch_state":
+        g = rng.standard_normal((1, d)).astype(np.float32)
+        U, E = (rng.standard_normal((r, c)).astype(np.float32) for _ in range(2))
+        U_d, E_d = torch.from_numpy(U).to(DEV), torch.from_numpy(E).to(DEV)
+        ctx.step_sketch_momentum(torch.from_numpy(g).to(DEV), U_d, E_d, k, merged, idx, values)
+        ref = oracle.sketch_state_update(host(merged), U, E, hp, d, k, rho=rho, reset_momentum=True)
+        assert np.array_equal(host(idx), ref["idx"]) and np.array_equal(host(values), ref["values"])
+        assert np.array_equal(host(U_d), U) and np.array_equal(host(E_d), E)
+        ctx.close()
+        return
+    g, u, v = (rng.standard_normal((P, d)).astype(np.float32) for _ in range(3))
+    g[:, d // 2:d // 2 + 3_000] *= 1e3  # part of the selection crowded
+    u_d, v_d = ctx.to_state(torch.from_numpy(u).to(DEV)), ctx.to_state(torch.from_numpy(v).to(DEV))
+    g_d = torch.from_numpy(g).to(DEV)
+    if call == "step":
+        ctx.step(g_d, u_d, v_d, k, merged, idx, values)
+    else:
+        rnd = torch.from_numpy(rng.integers(0, 1 << 32, d, dtype=np.uint64).astype(np.uint32).view(np.int32)).to(DEV)
+        ctx.step_heavymix(g_d, u_d, v_d, k, rnd, merged, idx, values)
+    oracle.accumulate(g, u, v, rho)
+    assert np.array_equal(host(values), oracle.gather_reset(host(idx), u, v, True))
+    assert np.array_equal(host(ctx.from_state(u_d)), u) and np.array_equal(host(ctx.from_state(v_d)), v)
+    ctx.close()
+
+
+def test_clustered_step():
+    # the gather of a selection within d / 256: measured 1.00 times the spread
+    # one, 1.10 where one workgroup gathers it
+    d, P, r, c, k = 25_600_000, 8, 5, 256_000, 25_600
+    hp = synth.hash_params(synth.BASE_SEED + 113, r)
+    us = []
+    for make in (spread, clustered):
+        gen = torch.Generator(device=DEV).manual_seed(7)
+        g = make(d, d // 256, gen).repeat(P, 1)
+        ctx = gs.GsContext(d, P, r, c, k, hp)
+        u, v = torch.zeros((P, d), device=DEV), torch.zeros((P, d), device=DEV)
+        merged = torch.empty((r, c), dtype=torch.float32, device=DEV)
+        idx, values = torch.empty(k, dtype=torch.int32, device=DEV), torch.empty(k, dtype=torch.float32, device=DEV)
+        us.append(best_us(lambda: ctx.step(g, u, v, k, merged, idx, values)))
+        ctx.close()
+    print(f"[clustered step] spread {us[0]:.0f} us, clustered {us[1]:.0f} us", flush=True)
+    assert us[1] < 1.07 * us[0]
