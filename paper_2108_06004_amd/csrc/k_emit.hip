@@ -225,6 +225,39 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather_reset(const int32_t* __
                (int64_t)gridDim.x * per, k, rows);
 }
 
+// Many coordinates of a worker-major state: one lane per coordinate, so that the lanes of a wave read
+// one worker's row at neighbouring places, and the workers of a coordinate in groups of at most 16, a
+// group's loads in flight together. NP: P up to 16; 0: any P.
+template <int NP>
+__global__ void __launch_bounds__(kGatherBlock) k_gather_columns(const int32_t* __restrict__ idx, int64_t k,
+                                                                 GatherArgs ga) {
+  constexpr int G = NP ? NP : 16, B = NP ? 1 : kMaxWorkers / G;
+  const int P = NP ? NP : ga.P;
+  const int64_t qs = ga.sv.qs, stride = (int64_t)gridDim.x * kGatherBlock;
+  for (int64_t t = (int64_t)blockIdx.x * kGatherBlock + threadIdx.x; t < k; t += stride) {
+    const int64_t i = idx[t];
+    float sum[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int n = P - G * b;
+      if (n <= 0) break;
+      float* const v = ga.v + G * b * qs + i;
+      float* const u = ga.u + G * b * qs + i;
+      float x[G];
+#pragma unroll
+      for (int q = 0; q < G; ++q) x[q] = q < n ? v[q * qs] : 0.f;
+      sum[b] = tree_sum_upto<G>(x, n);
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        if (q >= n) break;
+        v[q * qs] = 0.f;
+        if (ga.reset_u) u[q * qs] = 0.f;
+      }
+    }
+    ga.values[t] = tree_sum_upto<B>(sum, (P + G - 1) / G);
+  }
+}
+
 __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherArgs ga) {
   extern __shared__ uint32_t bits[];  // [range / 32]
   __shared__ Shared sh;
@@ -368,10 +401,26 @@ hipError_t prepare_emit() {
 
 hipError_t launch_gather(int num_cus, hipStream_t s, const HashSet& hs, const float* merged, const int32_t* idx,
                          int64_t k, const GatherArgs& ga) {
-  const int64_t per = kGatherBlock / ga.gl;
-  int64_t blocks = (k + per - 1) / per;
-  if (blocks > 8 * num_cus) blocks = 8 * num_cus;
-  hipLaunchKernelGGL(k_gather_reset, dim3((unsigned)blocks), dim3(kGatherBlock), 0, s, idx, k, hs, merged, ga);
+  // A lane per (coordinate, worker) is worth its scattered accesses only while there are too few coordinates
+  // to fill the chip: at 32,768 the two cost the same (P = 4, 8, 16 at 2M, k = 20,000: 10 us, 10 and 12,
+  // 15 and 19 by columns; k = 65,000: 12, 18, 34 us both; 20M, k = 65,000, P = 16: 68 us, 44 by columns; 2M,
+  // k = 400,000, P = 3, 8, 16, 64: 16, 42, 93 and 1,012 us, 14, 36, 68 and 420 by columns).
+  const bool columns = ga.op == kGatherWorkers && ga.sv.is == 1 && ga.P > 1 && k >= 32768;
+  const int64_t per = columns ? kGatherBlock : kGatherBlock / ga.gl;
+  const int64_t blocks = std::min<int64_t>((k + per - 1) / per, (columns ? 4 : 8) * num_cus);
+  const dim3 grid((unsigned)blocks), block(kGatherBlock);
+  if (!columns) {
+    hipLaunchKernelGGL(k_gather_reset, grid, block, 0, s, idx, k, hs, merged, ga);
+    return hipGetLastError();
+  }
+  switch (ga.P) {
+#define GS_COLUMNS(P) \
+  case P: hipLaunchKernelGGL(k_gather_columns<P>, grid, block, 0, s, idx, k, ga); break;
+    GS_COLUMNS(2) GS_COLUMNS(3) GS_COLUMNS(4) GS_COLUMNS(5) GS_COLUMNS(6) GS_COLUMNS(7) GS_COLUMNS(8) GS_COLUMNS(9)
+    GS_COLUMNS(10) GS_COLUMNS(11) GS_COLUMNS(12) GS_COLUMNS(13) GS_COLUMNS(14) GS_COLUMNS(15) GS_COLUMNS(16)
+#undef GS_COLUMNS
+    default: hipLaunchKernelGGL(k_gather_columns<0>, grid, block, 0, s, idx, k, ga); break;
+  }
   return hipGetLastError();
 }
 
