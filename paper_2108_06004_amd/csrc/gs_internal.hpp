@@ -22,6 +22,22 @@ constexpr int kDigit1Shift = 20;  // digit 1: key bits 31..20 (12 bits; |est| ke
 constexpr int kDigit1Bins = 4096; // HEAVYMIX keys use it to rank the heavy set above the fill)
 constexpr int kDigitBins = 1024;  // digits 2 and 3: key bits 19..10 and 9..0
 
+// Passes of the emit's workgroups over a list too long for the LDS: 10 bits of a word of up to 63 each,
+// one that marks, and the end.
+constexpr int kSettlePasses = 9;
+constexpr uint32_t kSettleDigit = 0, kSettleMark = 1, kSettleDone = 2, kSettleFailed = 3;
+struct SettlePass {
+  uint64_t lo, hi;      // the words that still may be the cut
+  uint32_t need, kind;  // how many of them are selected; what the pass does
+};
+// All but pass[] zero between calls.
+struct Settle {
+  uint32_t open;        // the pass that is open
+  uint32_t claim[kSettlePasses], done[kSettlePasses];  // its items taken and completed
+  uint32_t hist[1024];
+  SettlePass pass[kSettlePasses];
+};
+
 // Device-resident control block of the selection (one per context).
 struct SelectCtl {
   uint32_t n_cand;      // candidates appended by the pruned pass (dense candidates: d)
@@ -33,6 +49,7 @@ struct SelectCtl {
   double l2sq;          // HEAVYMIX: l2-norm-squared estimate (median of the pairwise row sums)
   double theta;         // HEAVYMIX: heavy threshold l2sq / k
   unsigned long long n_heavy;  // HEAVYMIX: |H|
+  Settle settle;
 };
 // What to do with the coordinates a selection has chosen (gather_entry in gs_select.hpp).
 struct GatherArgs {

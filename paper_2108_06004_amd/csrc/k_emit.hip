@@ -15,10 +15,10 @@
 // One kernel instead of four (digit 3 in one workgroup, marking, emission with a look-back,
 // gather), at about 4.6 us each however little they do.
 // When the bin does not fit the LDS (ties: a zero sketch, a diverged one), or the pruned pass fell
-// short of k candidates and the list holds every key, every workgroup reads the whole list: its
-// histograms give the k-th key, and one more pass the marks of the own range and the entries before
-// it; ties at the k-th key are taken in coordinate order (a zero sketch of 14.7M: 9 ms, and 60 ms
-// by one workgroup alone). No workgroup ever waits for another.
+// short of k candidates and the list holds every key, the workgroups first settle the list together
+// (settle_list): every pass reads it once, so its time grows with the list alone. Ties of nearly all
+// coordinates, r = 1, pruned: 0.58 ms at 14.7M, 3.1 at 140M, 21 at 537M, where every workgroup reading the
+// whole list took 8.8, 162 and 1,556; 113 us at 100,003 (107 so).
 #include <algorithm>
 
 #include "gs_internal.hpp"
@@ -64,9 +64,9 @@ struct Shared {
   uint32_t shw[kBlock / 64];
   uint32_t res[2];
   uint64_t cut;
-  uint32_t n, before, ties, last;
+  SettlePass pass;
+  uint32_t n, before, last, item;
 };
-static_assert(kRangeMax <= (int64_t)kBucketCap * 64, "the ties of a range have a bit each in the bucket");
 
 // The `need`-th largest of the n words in the bucket, all of them in [lo, hi].
 __device__ __forceinline__ uint64_t nth_largest(Shared& sh, uint64_t lo, uint64_t hi, uint32_t need, uint32_t n) {
@@ -116,66 +116,159 @@ __device__ __forceinline__ uint64_t nth_largest(Shared& sh, uint64_t lo, uint64_
   return sh.cut;
 }
 
-// A list too long for the LDS: the selection is its keys above T and the first need of those equal
-// to T (sets need and returns T). Only the keys in [klo, khi] are read as its entries. 10 bits of
-// the key range a pass; 16 loads per thread in flight, since one workgroup fills a CU.
-__device__ __forceinline__ uint32_t nth_key(Shared& sh, const uint32_t* __restrict__ key, int64_t n, uint32_t klo,
-                                            uint32_t khi, uint32_t& need) {
-  constexpr int U = 16;
-  while (khi > klo) {
-    const int bits = 32 - __clz((int)(khi - klo));
-    const int shift = bits > 10 ? bits - 10 : 0;
-    for (int b = threadIdx.x; b < 1024; b += kBlock) sh.h[b] = 0u;
-    __syncthreads();
-    for (int64_t t0 = 0; t0 < n; t0 += (int64_t)U * kBlock) {  // block-uniform
-      uint32_t kk[U];
-#pragma unroll
-      for (int m = 0; m < U; ++m) {
-        const int64_t t = t0 + (int64_t)m * kBlock + threadIdx.x;
-        kk[m] = key[min(t, n - 1)];
-      }
-      __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the adds
-#pragma unroll
-      for (int m = 0; m < U; ++m) {
-        const bool in = t0 + (int64_t)m * kBlock + threadIdx.x < n && kk[m] - klo <= khi - klo;
-        hist_add(sh.h, in, in ? (kk[m] - klo) >> shift : 0u);
-      }
-    }
-    __syncthreads();
-    find_bucket<kBlock, 1024>(sh.h, true, need, sh.shw, sh.res);
-    const uint32_t b = sh.res[0];
-    need -= sh.res[1];
-    klo += b << shift;
-    khi = min(khi, klo + ((1u << shift) - 1u));
-    __syncthreads();
-  }
-  return klo;
+// ------------------------------------------------------------------------------------
+// A list too long for the LDS is settled by all workgroups together, in passes over it: 10 bits of
+// the words a pass until the cut is known, then a pass that marks what is selected in the output bitmap
+// and counts it per range. A pass is cut into items that the workgroups claim; the one whose items
+// complete a pass finds the digit and opens the next. A workgroup that finds no item left waits
+// for that, so only for items that running workgroups hold: those not yet launched are not needed (they find
+// the passes done, or help), and no wait depends on them. The waits are bounded all the same.
+constexpr int kSettleUnroll = 8;                           // entries per thread and round
+constexpr int64_t kSettleRound = kSettleUnroll * kBlock;
+constexpr uint32_t kMaxPolls = 1u << 20;                   // about a second
+
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The entries of that list in [T, khi]: their bit in `above` or `ties` if they are in [lo, lo + width),
-// and their number before lo.
-__device__ __forceinline__ void mark_list(const uint32_t* __restrict__ key, const int32_t* __restrict__ idx, int64_t n,
-                                          uint32_t T, uint32_t khi, uint32_t lo, uint32_t width, uint32_t* above,
-                                          uint32_t* ties, uint32_t& above_before, uint32_t& ties_before) {
-  constexpr int U = 8;
-  for (int64_t t0 = 0; t0 < n; t0 += (int64_t)U * kBlock) {
-    uint32_t kk[U], ii[U];
+// The word of an entry: the key's distance from klo, then the coordinate from the last one down,
+// in as many bits (ib) as coordinates have.
+struct List {
+  const uint32_t* key;
+  const int32_t* idx;  // null: entry t is coordinate t
+  int64_t n;
+  uint32_t klo, width;  // entries with keys in [klo, klo + width] count
+  uint32_t last;        // d - 1
+  int ib;
+  __device__ __forceinline__ uint64_t word(uint32_t k, uint32_t ix) const {
+    return ((uint64_t)(k - klo) << ib) | (last - ix);
+  }
+};
+
+// Items of `chunk` entries (a multiple of 64): some for every workgroup, none short of a round.
+__device__ __forceinline__ int64_t settle_chunk(int64_t n) {
+  const int64_t per = n / 2048;
+  return (per / kSettleRound + 1) * kSettleRound;
+}
+
+// f(a listed entry?, word, coordinate) for the entries of item `it`, in as many rounds for every thread.
+template <class F>
+__device__ __forceinline__ void each_entry(const List& l, int64_t it, F f) {
+  const int64_t chunk = settle_chunk(l.n), end = min(l.n, (it + 1) * chunk);
+  for (int64_t t0 = it * chunk; t0 < end; t0 += kSettleRound) {
+    uint32_t kk[kSettleUnroll], ii[kSettleUnroll];
 #pragma unroll
-    for (int m = 0; m < U; ++m) {
-      const int64_t t = min(t0 + (int64_t)m * kBlock + threadIdx.x, n - 1);
-      kk[m] = key[t];
-      ii[m] = idx ? (uint32_t)idx[t] : (uint32_t)t;
+    for (int m = 0; m < kSettleUnroll; ++m) {
+      const int64_t t = min(t0 + (int64_t)m * kBlock + threadIdx.x, l.n - 1);
+      kk[m] = l.key[t];
+      ii[m] = l.idx ? (uint32_t)l.idx[t] : (uint32_t)t;
     }
-    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the adds
 #pragma unroll
-    for (int m = 0; m < U; ++m) {
-      if (t0 + (int64_t)m * kBlock + threadIdx.x >= n || kk[m] < T || kk[m] > khi) continue;
-      if (ii[m] < lo)
-        ++(kk[m] == T ? ties_before : above_before);
-      else if (ii[m] - lo < width)
-        atomicOr(&(kk[m] == T ? ties : above)[(ii[m] - lo) >> 5], 1u << ((ii[m] - lo) & 31u));
+    for (int m = 0; m < kSettleUnroll; ++m) {
+      const bool in = t0 + (int64_t)m * kBlock + threadIdx.x < end && kk[m] - l.klo <= l.width;
+      f(in, l.word(kk[m], ii[m]), ii[m]);
     }
   }
+}
+
+// The selection's `need` largest words of the list marked in the bitmap and counted per range.
+// False when a wait ran out (the control block in use by a call that overlaps this one).
+__device__ __forceinline__ bool settle_list(const EmitArgs& a, Shared& sh, const List& l, uint32_t need) {
+  SelectCtl* const ctl = a.ctl;
+  Settle& g = ctl->settle;
+  const int64_t items = (l.n + settle_chunk(l.n) - 1) / settle_chunk(l.n);
+  const int nr = (int)gridDim.x;
+  for (int p = 0; p < kSettlePasses; ++p) {
+    if (threadIdx.x == 0) {
+      sh.pass = SettlePass{0, (((uint64_t)l.width + 1) << l.ib) - 1, need, kSettleDigit};
+      if (p > 0) {
+        uint32_t polls = 0;
+        while (load_agent(&g.open) < (uint32_t)p && ++polls < kMaxPolls) __builtin_amdgcn_s_sleep(4);
+        if (polls >= kMaxPolls) {
+          sh.pass.kind = kSettleFailed;
+        } else {
+          __threadfence();  // what the pass before wrote
+          const SettlePass* q = &g.pass[p];
+          sh.pass = SettlePass{load_agent(&q->lo), load_agent(&q->hi), load_agent(&q->need), load_agent(&q->kind)};
+        }
+      }
+    }
+    for (int b = threadIdx.x; b < 1024; b += kBlock) sh.h[b] = 0u;
+    __syncthreads();
+    const SettlePass q = sh.pass;
+    if (q.kind == kSettleFailed) return false;
+    if (q.kind == kSettleDone) return true;
+    const int bits = 64 - __clzll((long long)(q.hi - q.lo));
+    const int shift = bits > 10 ? bits - 10 : 0;
+    uint32_t mine = 0;  // items taken (block-uniform)
+    for (;;) {
+      if (threadIdx.x == 0) sh.item = atomicAdd(&g.claim[p], 1u);
+      __syncthreads();
+      const int64_t it = sh.item;
+      __syncthreads();
+      if (it >= items) break;
+      ++mine;
+      if (q.kind == kSettleDigit) {
+        each_entry(l, it, [&](bool in, uint64_t w, uint32_t) {
+          const bool take = in && w >= q.lo && w <= q.hi;
+          hist_add(sh.h, take, take ? (uint32_t)((w - q.lo) >> shift) : 0u);
+        });
+      } else {
+        each_entry(l, it, [&](bool in, uint64_t w, uint32_t ix) {
+          const bool take = in && w >= q.lo;
+          if (l.idx) {
+            if (take) atomicOr(&a.bitmap[ix >> 5], 1u << (ix & 31u));
+          } else if (const uint64_t bal = __ballot(take)) {  // 64 coordinates from a multiple of 64
+            const uint32_t half = threadIdx.x & 1 ? (uint32_t)(bal >> 32) : (uint32_t)bal;
+            const uint32_t first = __shfl(ix, 0) >> 5;
+            if ((threadIdx.x & 63) < 2 && half) atomicOr(&a.bitmap[first + (threadIdx.x & 1)], half);
+          }
+          const uint32_t b = take ? ix / (uint32_t)a.range : 0u;
+          if (nr <= 1024)
+            hist_add(sh.h, take, b);
+          else if (take)
+            atomicAdd(&a.counts[b], 1u);
+        });
+      }
+    }
+    if (mine == 0) continue;
+    __syncthreads();
+    uint32_t* const to = q.kind == kSettleDigit ? g.hist : a.counts;
+    for (int b = threadIdx.x; b < (q.kind == kSettleDigit || nr > 1024 ? 1024 : nr); b += kBlock)
+      if (const uint32_t c = sh.h[b]) atomicAdd(&to[b], c);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __threadfence();
+      sh.last = atomicAdd(&g.done[p], mine) + mine == (uint32_t)items ? 1u : 0u;
+      __threadfence();
+    }
+    __syncthreads();
+    if (!sh.last) continue;
+    SettlePass next{q.lo, q.hi, q.need, kSettleDone};
+    if (q.kind == kSettleDigit) {
+      for (int b = threadIdx.x; b < 1024; b += kBlock) {
+        sh.h[b] = load_agent(&g.hist[b]);
+        g.hist[b] = 0u;
+      }
+      __syncthreads();
+      find_bucket<kBlock, 1024>(sh.h, true, q.need, sh.shw, sh.res);
+      const uint64_t b = sh.res[0];
+      next.need -= sh.res[1];
+      next.lo += b << shift;
+      next.hi = min(q.hi, next.lo + ((1ull << shift) - 1ull));
+      // all of the bin is taken (or it is one word): its first word is the cut
+      next.kind = next.need == sh.h[b] ? kSettleMark : kSettleDigit;
+    }
+    if (threadIdx.x == 0 && p + 1 < kSettlePasses) {
+      g.pass[p + 1] = next;
+      __threadfence();
+      __hip_atomic_store(&g.open, (uint32_t)(p + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+  }
+  return false;
 }
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
@@ -271,15 +364,28 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherA
   const bool few = a.pruned && a.ctl->n_cand < a.k;
   const uint32_t l32 = (uint32_t)lo, width = (uint32_t)(hi - lo);
   const int nw = (int)(a.range / 32);
-  uint32_t before = 0;
-  for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kBlock) before += a.counts[t];
-  const int64_t words = (a.d + 31) / 32, word0 = lo / 32;
-  for (int w = threadIdx.x; w < nw; w += kBlock) bits[w] = word0 + w < words ? a.bitmap[word0 + w] : 0u;
-  if (threadIdx.x == 0) sh.before = sh.ties = 0u;
-  uint32_t need = few ? a.k : a.ctl->need[a.level];
   const uint32_t klo = few ? 0u : a.ctl->lo[a.level], khi = few ? ~0u : a.ctl->hi[a.level];
+  const uint32_t need = few ? a.k : a.ctl->need[a.level];
+  const bool in_lds = !few && nb <= (uint32_t)kBucketCap;
+  uint32_t before = 0;
+  const int64_t words = (a.d + 31) / 32, word0 = lo / 32;
+  auto load_own = [&](bool ok) {
+    before = 0;
+    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kBlock) before += a.counts[t];
+    for (int w = threadIdx.x; w < nw; w += kBlock) bits[w] = ok && word0 + w < words ? a.bitmap[word0 + w] : 0u;
+  };
+  load_own(true);
+  if (threadIdx.x == 0) sh.before = 0u;
+  bool ok = true;
+  if (!in_lds) {
+    const uint32_t last = (uint32_t)(a.d - 1);
+    const List l{a.list0_key, few ? nullptr : a.list0_idx, few ? a.d : (int64_t)a.ctl->n_stage[0],
+                 klo, khi - klo, last, 32 - __clz((int)(last | 1u))};
+    ok = settle_list(a, sh, l, need);
+    load_own(ok);
+  }
   const int per = (nw + kBlock - 1) / kBlock, w0 = threadIdx.x * per;
-  if (!few && nb <= (uint32_t)kBucketCap) {
+  if (in_lds) {
     for (uint32_t t = threadIdx.x; t < nb; t += kBlock) sh.bucket[t] = word_of(a.list_key[t], (uint32_t)a.list_idx[t]);
     __syncthreads();
     const uint64_t cut = nth_largest(sh, (uint64_t)klo << 32, ((uint64_t)khi << 32) | 0xffffffffull, need, nb);
@@ -293,37 +399,12 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherA
           atomicOr(&bits[(ix - l32) >> 5], 1u << ((ix - l32) & 31u));
       }
     }
-    before = wave_sum(before);
-    if ((threadIdx.x & 63) == 0 && before) atomicAdd(&sh.before, before);
-    __syncthreads();
   } else {
-    uint32_t* const ties = reinterpret_cast<uint32_t*>(sh.bucket);
-    for (int w = threadIdx.x; w < nw; w += kBlock) ties[w] = 0u;
-    __syncthreads();
-    const int64_t n = few ? a.d : (int64_t)a.ctl->n_stage[0];
-    const int32_t* const idx = few ? nullptr : a.list0_idx;
-    const uint32_t T = nth_key(sh, a.list0_key, n, klo, khi, need);
-    uint32_t ties_before = 0;
-    mark_list(a.list0_key, idx, n, T, khi, l32, width, bits, ties, before, ties_before);
-    before = wave_sum(before);
-    ties_before = wave_sum(ties_before);
-    if ((threadIdx.x & 63) == 0) {
-      atomicAdd(&sh.before, before);
-      atomicAdd(&sh.ties, ties_before);
-    }
-    __syncthreads();
-    const uint32_t gone = min(sh.ties, need);  // ties taken by the ranges before
-    uint32_t cnt = 0, total;
-    for (int m = 0; m < per; ++m)
-      if (w0 + m < nw) cnt += (uint32_t)__popc(ties[w0 + m]);
-    uint32_t pos = gone + block_scan_incl<kBlock>(cnt, sh.shw, total) - cnt;
-    for (int m = 0; m < per; ++m) {
-      uint32_t x = w0 + m < nw ? ties[w0 + m] : 0u;
-      for (; x && pos < need; ++pos, x &= x - 1u) bits[w0 + m] |= x & (0u - x);
-    }
-    if (threadIdx.x == 0) sh.before += gone;
     __syncthreads();
   }
+  before = wave_sum(before);
+  if ((threadIdx.x & 63) == 0 && before) atomicAdd(&sh.before, before);
+  __syncthreads();
   uint32_t cnt = 0;
   for (int m = 0; m < per; ++m)
     if (w0 + m < nw) cnt += (uint32_t)__popc(bits[w0 + m]);
@@ -352,6 +433,12 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherA
     a.ctl->n_stage[0] = a.ctl->n_stage[1] = 0u;
     a.ctl->emit_ticket = 0u;
   }
+  if (in_lds) return;
+  Settle& g = a.ctl->settle;
+  if (threadIdx.x < kSettlePasses) g.claim[threadIdx.x] = g.done[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) g.open = 0u;
+  if (!ok)
+    for (int b = threadIdx.x; b < 1024; b += kBlock) g.hist[b] = 0u;
 }
 
 }  // namespace

@@ -262,3 +262,61 @@ def test_gather_of_a_large_part_is_cheap():
     print(f"[gather] {us}", flush=True)
     assert us[1] < 8.5 * us[0]
     ctx.close()
+
+
+def ranked(key, k):
+    """The k largest keys (int64, below 2^32), ties to the lower index, as ascending indices."""
+    i = torch.arange(key.numel(), dtype=torch.int64, device=DEV)
+    word = key * (1 << 31) + ((1 << 31) - 1 - i)
+    return torch.sort(torch.sort(word, descending=True).indices[:k]).values.int()
+
+
+# one emit range per CU up to 2^19 coordinates each (134M on 256 CUs), more ranges beyond; 1,024 of
+# them counted in LDS (2^29 coordinates)
+@pytest.mark.parametrize("path", ["pruned", "full"])
+@pytest.mark.parametrize("d,c,k", [(100_003, 100, 60_000), (14_700_000, 1_000, 147_000), (140_000_003, 1_000, 1_000_000),
+                                   (537_000_001, 100_000, 1_000_000)])
+def test_ties_of_most_coordinates(monkeypatch, path, d, c, k):
+    # one column of c carries a value, all other coordinates tie at zero
+    monkeypatch.setenv("GS_SELECT_PATH", path)
+    hp = synth.hash_params(synth.BASE_SEED + 123, 1)
+    m = torch.zeros((1, c), dtype=torch.float32, device=DEV)
+    m[0, 7] = 0.5
+    i = torch.arange(d, dtype=torch.int64, device=DEV)
+    hit = (i * int(hp["a"][0]) + int(hp["b"][0])) % P31 % c == 7
+    del i
+    n = int(hit.sum())
+    assert 0 < n < k
+    zeros = torch.nonzero(~hit[:2 * k]).flatten()[:k - n]
+    assert zeros.numel() == k - n
+    want = torch.sort(torch.cat((torch.nonzero(hit).flatten(), zeros))).values.int()
+    del hit
+    ctx = gs.GsContext(d, 1, 1, c, k, hp)
+    idx = torch.empty(k, dtype=torch.int32, device=DEV)
+    us = []
+    for table in (torch.randn((1, c), device=DEV), m):
+        us.append(best_us(lambda: ctx.unsketch_topk(table, k, idx), reps=2))
+    print(f"[ties] {path} d={d} c={c}: cells at random {us[0]:.0f} us, ties {us[1]:.0f} us", flush=True)
+    assert torch.equal(idx, want)
+    ctx.close()
+
+
+def test_ties_cost_a_few_full_estimates(monkeypatch):
+    # every coordinate a survivor and a candidate: measured 4 times the call that estimates every
+    # coordinate of an ordinary sketch
+    monkeypatch.delenv("GS_SELECT_PATH", raising=False)
+    d, r, c, k = 14_700_000, 5, 1_470_000, 14_700
+    hp = synth.hash_params(synth.BASE_SEED + 125, r)
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    ctx = gs.GsContext(d, 1, r, c, k, hp)
+    m = sketch_of(torch.randn(d, generator=gen, device=DEV), hp, c)
+    est, idx = torch.empty(d, device=DEV), torch.empty(k, dtype=torch.int32, device=DEV)
+    full = best_us(lambda: ctx.unsketch_topk(m, k, idx, est))
+    for table in (torch.zeros_like(m), torch.sign(m)):  # a zero sketch, one of few levels
+        us = best_us(lambda: ctx.unsketch_topk(table, k, idx))
+        print(f"[ties] full estimate {full:.0f} us, ties {us:.0f} us", flush=True)
+        ctx.unsketch_topk(table, k, idx.new_empty(k), est)
+        key = est.view(torch.int32).long() & 0x7FFFFFFF
+        assert torch.equal(idx, ranked(key, k))
+        assert us < 8 * full
+    ctx.close()
