@@ -232,8 +232,8 @@ hipError_t launch_heavymix_topk(gs_ctx* x, hipStream_t s, const float* merged, i
 // From the last digit pass's staged keys to the ascending index list (and the gather); `level` is
 // that pass (0 or 1), pruned and hm say what the candidates are.
 hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
-                       const float* merged, int64_t k, int pruned, int level, int32_t* idx, int64_t* n_heavy,
-                       double* l2sq, const GatherArgs* ga);
+                       const float* merged, const uint32_t* rnd, int64_t k, int pruned, int level, int32_t* idx,
+                       int64_t* n_heavy, double* l2sq, const GatherArgs* ga);
 hipError_t prepare_emit();
 // The gather alone, over idx[0, k).
 hipError_t launch_gather(int num_cus, hipStream_t s, const HashSet& hs, const float* merged, const int32_t* idx,

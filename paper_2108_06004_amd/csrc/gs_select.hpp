@@ -134,9 +134,8 @@ __device__ __forceinline__ uint64_t cand_bin_lo(const CandBins& c, uint32_t b) {
 }
 
 // Median estimate with r rows at run time, sorted by insertion in the thread's own kMaxRows floats
-// of LDS: small code for the rare and the short uses (the slow form, the sketch-space values).
-// Unrolled over kMaxRows in registers, the rows' hash constants crowded the scalar registers of the
-// whole kernel (990 spills, in the list scan too).
+// of LDS: small code for the few values of the sketch-space state. Unrolled over kMaxRows in registers, the
+// rows' hash constants crowded the scalar registers of the whole kernel.
 __device__ __forceinline__ float estimate_any(const HashSet& hs, const float* __restrict__ merged, uint32_t i,
                                               float* val) {
   const int r = hs.r;

@@ -15,10 +15,12 @@
 // One kernel instead of four (digit 3 in one workgroup, marking, emission with a look-back,
 // gather), at about 4.6 us each however little they do.
 // When the bin does not fit the LDS (ties: a zero sketch, a diverged one), or the pruned pass fell
-// short of k candidates and the list holds every key, the workgroups first settle the list together
+// short of k candidates and the list is every coordinate's keys, the workgroups first settle the list together
 // (settle_list): every pass reads it once, so its time grows with the list alone. Ties of nearly all
 // coordinates, r = 1, pruned: 0.58 ms at 14.7M, 3.1 at 140M, 21 at 537M, where every workgroup reading the
 // whole list took 8.8, 162 and 1,556; 113 us at 100,003 (107 so).
+// Short of k the first pass estimates the keys: the selection takes 1,318 us at 14.7M, r = 5, c = 1.47M and
+// 933 at 25.6M, c = 256,000 (the full estimate read directly: 1,065 and 695).
 #include <algorithm>
 
 #include "gs_internal.hpp"
@@ -27,6 +29,9 @@
 namespace gs {
 namespace {
 
+#define GS_FOR_ROWS(M) \
+  M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) M(16)
+
 constexpr int kBlock = 1024;
 constexpr int kBucketCap = 8192;   // words of the k-th key's bin kept in LDS
 constexpr int kRankCap = 256;      // words ranked against each other
@@ -34,7 +39,7 @@ constexpr int kRankCap = 256;      // words ranked against each other
 struct EmitArgs {
   const uint32_t* list_key;   // staged keys of the bin
   const int32_t* list_idx;    // and their coordinates
-  const uint32_t* list0_key;  // those of the first digit's bin (complete; or every key by coordinate)
+  const uint32_t* list0_key;  // those of the first digit's bin
   const int32_t* list0_idx;
   uint32_t* bitmap;
   uint32_t* counts;
@@ -42,12 +47,14 @@ struct EmitArgs {
   uint32_t* hist;             // histograms cleared here for the next call
   uint32_t* hist2;
   const float* merged;
+  uint32_t* all_keys;         // short of k: every coordinate's key (list0_key)
+  const uint32_t* rnd;        // HEAVYMIX: the draws, or null
   int32_t* out;
   int64_t* n_heavy;
   double* l2sq;
   int64_t d, range;
   uint32_t k;
-  int pruned, level;
+  int level;
 };
 
 __device__ __forceinline__ uint64_t word_of(uint32_t key, uint32_t ix) {
@@ -173,9 +180,39 @@ __device__ __forceinline__ void each_entry(const List& l, int64_t it, F f) {
   }
 }
 
+// The same for a list that is not there yet, every coordinate's keys: they are estimated, with all R cell
+// loads of kEstimate coordinates in flight per thread, and written.
+template <int R, class F>
+__device__ __forceinline__ void each_estimate(const EmitArgs& a, const HashSet& hs, const List& l, int64_t it, F f) {
+  constexpr int kEstimate = R <= 8 ? 2 : 1;
+  RowConst kr[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) kr[j] = row_const(hs, j);
+  const double theta = a.rnd ? a.ctl->theta : 0.0;
+  const int64_t chunk = settle_chunk(l.n), end = min(l.n, (it + 1) * chunk);
+  for (int64_t t0 = it * chunk; t0 < end; t0 += kEstimate * kBlock) {
+    float e[kEstimate];
+#pragma unroll
+    for (int m = 0; m < kEstimate; ++m)  // a column is valid for any hash value
+      e[m] = estimate_val<R>(kr, a.merged, (uint32_t)(t0 + m * kBlock + threadIdx.x));
+#pragma unroll
+    for (int m = 0; m < kEstimate; ++m) {
+      const int64_t t = t0 + m * kBlock + threadIdx.x;
+      const bool in = t < end;
+      uint32_t key = abs_key(e[m]);
+      if (a.rnd) key = (double)e[m] * (double)e[m] >= theta ? 0x80000000u | key : a.rnd[min(t, l.n - 1)] >> 1;
+      if (in) a.all_keys[t] = key;
+      f(in, l.word(key, (uint32_t)t), (uint32_t)t);
+    }
+  }
+}
+
 // The selection's `need` largest words of the list marked in the bitmap and counted per range.
 // False when a wait ran out (the control block in use by a call that overlaps this one).
-__device__ __forceinline__ bool settle_list(const EmitArgs& a, Shared& sh, const List& l, uint32_t need) {
+// R > 0: without indices, the list is every coordinate's keys, which the first pass estimates.
+template <int R>
+__device__ __forceinline__ bool settle_list(const EmitArgs& a, const HashSet& hs, Shared& sh, const List& l,
+                                            uint32_t need) {
   SelectCtl* const ctl = a.ctl;
   Settle& g = ctl->settle;
   const int64_t items = (l.n + settle_chunk(l.n) - 1) / settle_chunk(l.n);
@@ -211,10 +248,18 @@ __device__ __forceinline__ bool settle_list(const EmitArgs& a, Shared& sh, const
       if (it >= items) break;
       ++mine;
       if (q.kind == kSettleDigit) {
-        each_entry(l, it, [&](bool in, uint64_t w, uint32_t) {
+        auto add = [&](bool in, uint64_t w, uint32_t) {
           const bool take = in && w >= q.lo && w <= q.hi;
           hist_add(sh.h, take, take ? (uint32_t)((w - q.lo) >> shift) : 0u);
-        });
+        };
+        bool listed = true;
+        if constexpr (R > 0) {
+          if (p == 0 && !l.idx) {
+            listed = false;
+            each_estimate<R>(a, hs, l, it, add);
+          }
+        }
+        if (listed) each_entry(l, it, add);
       } else {
         each_entry(l, it, [&](bool in, uint64_t w, uint32_t ix) {
           const bool take = in && w >= q.lo;
@@ -351,6 +396,8 @@ __global__ void __launch_bounds__(kGatherBlock) k_gather_columns(const int32_t* 
   }
 }
 
+// R: rows, where a pruned pass may have fallen short of k candidates; 0 for the full estimate's.
+template <int R>
 __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherArgs ga) {
   extern __shared__ uint32_t bits[];  // [range / 32]
   __shared__ Shared sh;
@@ -360,8 +407,8 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherA
     if (a.n_heavy) *a.n_heavy = (int64_t)a.ctl->n_heavy;
     if (a.l2sq) *a.l2sq = a.ctl->l2sq;
   }
-  // the bound admitted too little: the digit pass left every key in the list, and marked nothing
-  const bool few = a.pruned && a.ctl->n_cand < a.k;
+  // the bound admitted too little: the digit pass marked nothing, and every coordinate is estimated
+  const bool few = R > 0 && a.ctl->n_cand < a.k;
   const uint32_t l32 = (uint32_t)lo, width = (uint32_t)(hi - lo);
   const int nw = (int)(a.range / 32);
   const uint32_t klo = few ? 0u : a.ctl->lo[a.level], khi = few ? ~0u : a.ctl->hi[a.level];
@@ -381,7 +428,7 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherA
     const uint32_t last = (uint32_t)(a.d - 1);
     const List l{a.list0_key, few ? nullptr : a.list0_idx, few ? a.d : (int64_t)a.ctl->n_stage[0],
                  klo, khi - klo, last, 32 - __clz((int)(last | 1u))};
-    ok = settle_list(a, sh, l, need);
+    ok = settle_list<R>(a, hs, sh, l, need);
     load_own(ok);
   }
   const int per = (nw + kBlock - 1) / kBlock, w0 = threadIdx.x * per;
@@ -444,8 +491,8 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherA
 }  // namespace
 
 hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
-                       const float* merged, int64_t k, int pruned, int level, int32_t* idx, int64_t* n_heavy,
-                       double* l2sq, const GatherArgs* ga) {
+                       const float* merged, const uint32_t* rnd, int64_t k, int pruned, int level, int32_t* idx,
+                       int64_t* n_heavy, double* l2sq, const GatherArgs* ga) {
   EmitArgs a{};
   a.range = emit_range(d, num_cus);
   a.list_key = level ? b.stage2 : b.keys;
@@ -458,12 +505,13 @@ hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBu
   a.hist = pruned ? b.hist_c : b.hist;
   a.hist2 = b.hist2;
   a.merged = merged;
+  a.all_keys = b.keys;
+  a.rnd = rnd;
   a.out = idx;
   a.n_heavy = n_heavy;
   a.l2sq = l2sq;
   a.d = d;
   a.k = (uint32_t)k;
-  a.pruned = pruned;
   a.level = level;
   const unsigned blocks = (unsigned)((d + a.range - 1) / a.range);
   // The emit gathers what each workgroup has written, unless one could have so much of it (the selection
@@ -474,16 +522,28 @@ hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBu
   // and 122). Beyond d/8 no workgroup has more than 8 times the mean (14.7M x 4, k = d/4: spread
   // 1,402 and 1,437 us, in one quarter of d 1,431 and 1,454).
   const bool own = !ga || std::min(k, a.range) * ga->gl <= 12 * kBlock || 8 * k > d;
-  hipLaunchKernelGGL(k_emit, dim3(blocks), dim3(kBlock), (size_t)(a.range / 32) * sizeof(uint32_t), s, a, hs,
-                     ga && own ? *ga : GatherArgs{});
+  const size_t lds = (size_t)(a.range / 32) * sizeof(uint32_t);
+  const GatherArgs g = ga && own ? *ga : GatherArgs{};
+  switch (pruned ? hs.r : 0) {
+#define GS_EMIT(R) \
+  case R: hipLaunchKernelGGL(k_emit<R>, dim3(blocks), dim3(kBlock), lds, s, a, hs, g); break;
+    GS_EMIT(0) GS_FOR_ROWS(GS_EMIT)
+#undef GS_EMIT
+    default: return hipErrorInvalidValue;
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || own) return e;
   return launch_gather(num_cus, s, hs, merged, idx, k, *ga);
 }
 
 hipError_t prepare_emit() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_emit), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             kRangeMax / 8);
+#define GS_EMIT(R) reinterpret_cast<const void*>(&k_emit<R>),
+  for (const void* f : {GS_FOR_ROWS(GS_EMIT) reinterpret_cast<const void*>(&k_emit<0>)}) {
+#undef GS_EMIT
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kRangeMax / 8);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_gather(int num_cus, hipStream_t s, const HashSet& hs, const float* merged, const int32_t* idx,

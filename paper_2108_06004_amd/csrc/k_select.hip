@@ -185,8 +185,6 @@ struct DigitArgs {
   int64_t cap;           // room in out_key and out_idx
   uint32_t* bitmap;      // keys above the bin set their bit (dense: every word is written)
   uint32_t* counts;      // and are counted per emit range
-  const float* merged;   // the estimates, when the pruned pass fell short
-  const uint32_t* rnd;
   int64_t d, range;
   int64_t slice;         // dense: keys per block (a multiple of 64)
   uint32_t slices;       // and blocks per emit range
@@ -201,18 +199,12 @@ struct DigitArgs {
 // block and one global atomic per flush, with a histogram of the next ten bits on request. Level 1
 // runs the same over the keys staged by level 0, by that next digit: a dense bin holds percents
 // of d, too many for the emit's workgroups to read one by one.
-// When the pruned pass left fewer than k candidates, the blocks instead store every coordinate's
-// key in out_key for the emit.
+// When the pruned pass left fewer than k candidates there is nothing to find here: the emit estimates
+// every coordinate.
 template <bool DENSE>
-__global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs) {
-  union Buf {
-    struct {
-      uint32_t key[kStageBuf];
-      int32_t idx[kStageBuf];
-    } s;
-    float rows[kDigit2Block * kMaxRows];
-  };
-  __shared__ Buf buf;
+__global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a) {
+  __shared__ uint32_t buf_key[kStageBuf];
+  __shared__ int32_t buf_idx[kStageBuf];
   __shared__ uint32_t h[kDigitBins];
   __shared__ uint32_t cnt[DENSE ? 1 : kCountMax];
   __shared__ uint32_t shw[kDigit2Block / 64];
@@ -220,16 +212,7 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
   __shared__ uint32_t bn, gbase;
   SelectCtl* const ctl = a.ctl;
   const int64_t grid = gridDim.x;
-  if (!DENSE && a.pruned && ctl->n_cand < a.k) {
-    const double theta = ctl->theta;
-    for (int64_t i = (int64_t)blockIdx.x * kDigit2Block + threadIdx.x; i < a.d; i += grid * kDigit2Block) {
-      const float e = estimate_any(hs, a.merged, (uint32_t)i, buf.rows + threadIdx.x * kMaxRows);
-      uint32_t key = abs_key(e);
-      if (a.hm) key = (double)e * (double)e >= theta ? 0x80000000u | key : a.rnd[i] >> 1;
-      a.out_key[i] = key;
-    }
-    return;
-  }
+  if (!DENSE && a.pruned && ctl->n_cand < a.k) return;
   int64_t n;
   uint32_t need = a.k, klo, khi;
   if (a.level == 0) {
@@ -301,8 +284,8 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
       wbase = __shfl(wbase, 0);
       if (take) {
         const uint32_t pos = wbase + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-        buf.s.key[pos] = key[m];
-        buf.s.idx[pos] = (int32_t)ix[m];
+        buf_key[pos] = key[m];
+        buf_idx[pos] = (int32_t)ix[m];
       }
     }
     __syncthreads();
@@ -313,8 +296,8 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
       const int64_t g0 = gbase;
       for (uint32_t t = threadIdx.x; t < nb; t += kDigit2Block) {
         if (g0 + t < a.cap) {
-          a.out_key[g0 + t] = buf.s.key[t];
-          a.out_idx[g0 + t] = buf.s.idx[t];
+          a.out_key[g0 + t] = buf_key[t];
+          a.out_idx[g0 + t] = buf_idx[t];
         }
       }
       __syncthreads();
@@ -346,9 +329,8 @@ __global__ void __launch_bounds__(kDigit2Block) k_digit2(DigitArgs a, HashSet hs
 // fl(fl(m1 + m2) * 0.5) never exceeds m2 in magnitude). So with tau0 no larger than the
 // k-th |est|, only coordinates with ceil(r/2) "heavy" cells can be selected, and a bitmap
 // of heavy cells replaces most table reads. tau0 is the rho-th largest of M sampled exact
-// estimates, rho ~ 2 M k / d plus a margin; if fewer than k coordinates reach tau0 the
-// unpruned kernels (gated on ctl->fallback) redo the selection, so the result is exact
-// either way.
+// estimates, rho ~ 1.2 M k / d plus a margin; if fewer than k coordinates reach tau0 the emit's
+// workgroups estimate every coordinate (settle_list), so the result is exact either way.
 
 template <int R>
 __device__ __forceinline__ uint32_t estimate_key(const RowConst (&kr)[R], const float* __restrict__ merged,
@@ -1266,8 +1248,6 @@ hipError_t launch_select_tail(const HashSet& hs, int64_t d, int num_cus, const S
   a.cap = d;
   a.bitmap = b.bitmap;
   a.counts = b.counts;
-  a.merged = merged;
-  a.rnd = rnd;
   a.d = d;
   a.range = emit_range(d, num_cus);
   a.k = (uint32_t)k;
@@ -1290,9 +1270,9 @@ hipError_t launch_select_tail(const HashSet& hs, int64_t d, int num_cus, const S
     g2 = (d + a.range - 1) / a.range * parts;
   }
   if (pruned)
-    hipLaunchKernelGGL(k_digit2<false>, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a, hs);
+    hipLaunchKernelGGL(k_digit2<false>, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a);
   else
-    hipLaunchKernelGGL(k_digit2<true>, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a, hs);
+    hipLaunchKernelGGL(k_digit2<true>, dim3((unsigned)g2), dim3(kDigit2Block), 0, s, a);
   if (two) {
     DigitArgs a1 = a;
     a1.key = b.keys;
@@ -1303,9 +1283,9 @@ hipError_t launch_select_tail(const HashSet& hs, int64_t d, int num_cus, const S
     a1.out_idx = reinterpret_cast<int32_t*>(b.stage2 + kStage2Cap);
     a1.cap = kStage2Cap;
     a1.level = 1;
-    hipLaunchKernelGGL(k_digit2<false>, dim3(num_cus), dim3(kDigit2Block), 0, s, a1, hs);
+    hipLaunchKernelGGL(k_digit2<false>, dim3(num_cus), dim3(kDigit2Block), 0, s, a1);
   }
-  return launch_emit(hs, d, num_cus, b, s, merged, k, pruned, two ? 1 : 0, idx, n_heavy, l2sq, ga);
+  return launch_emit(hs, d, num_cus, b, s, merged, rnd, k, pruned, two ? 1 : 0, idx, n_heavy, l2sq, ga);
 }
 
 }  // namespace

@@ -271,6 +271,75 @@ def ranked(key, k):
     return torch.sort(torch.sort(word, descending=True).indices[:k]).values.int()
 
 
+def short_of_k(key, sample_key, d, k):
+    """Whether fewer than k keys reach the bound that the pruned pass takes from its evenly spaced samples."""
+    M = min(d, 16_384)
+    mk = M * k / d
+    rho = min(M, int(np.ceil(1.2 * mk + 5 * np.sqrt(mk) + 8)))
+    s = torch.arange(M, dtype=torch.int64, device=DEV) * d // M
+    bound = torch.sort(sample_key[s], descending=True).values[rho - 1]
+    return rho, int((key >= bound).sum()) < k
+
+
+def large_at_samples(d, k, gen):
+    """Large only at the sampled coordinates, at a few more of them than the bound's rank."""
+    x = values(d, gen)
+    rho, _ = short_of_k(x, x, d, k)
+    s = torch.arange(rho + 20, dtype=torch.int64, device=DEV) * d // min(d, 16_384)
+    x[s] = 10.0 + torch.randn(rho + 20, generator=gen, device=DEV)
+    return x, s
+
+
+@pytest.mark.parametrize("d,r,c,k", [
+    (50_001, 3, 1_000_003, 5_000), (50_001, 1, 1_000_003, 5_000), (50_001, 2, 1_000_003, 5_000),
+    (50_001, 16, 1_000_003, 5_000), (300_001, 8, 50_000, 3_000), (1_100_003, 5, 200_000, 11_000),
+    (600_011, 4, 1_300_007, 6_000), (1_048_577, 3, 20_000_003, 10_000)])
+def test_pruned_selection_short_of_k(monkeypatch, d, r, c, k):
+    monkeypatch.setenv("GS_SELECT_PATH", "pruned")
+    gen = torch.Generator(device=DEV).manual_seed(d + r)
+    hp = synth.hash_params(synth.BASE_SEED + 119, r)
+    ctx = gs.GsContext(d, 1, r, c, k, hp)
+    x, s = large_at_samples(d, k, gen)
+    m, other = sketch_of(x, hp, c), sketch_of(torch.randn(d, generator=gen, device=DEV), hp, c)
+    est, idx = torch.empty(d, dtype=torch.float32, device=DEV), torch.empty(k, dtype=torch.int32, device=DEV)
+    rnd = torch.empty(d, dtype=torch.int64, device=DEV).random_(0, 1 << 31, generator=gen)
+    rnd[s] += 1 << 31  # HEAVYMIX: the large draws at the samples too
+    rnd32 = (rnd - ((rnd >> 31) << 32)).int()
+    n_heavy, l2sq = torch.empty(1, dtype=torch.int64, device=DEV), torch.empty(1, dtype=torch.float64, device=DEV)
+    for table, short in ((m, True), (other, False), (m, True)):  # what a call leaves behind must not matter
+        ctx.unsketch_topk(table, k, idx, est)
+        key = est.view(torch.int32).long() & 0x7FFFFFFF
+        if short:
+            assert short_of_k(key, key, d, k)[1]
+        ctx.unsketch_topk(table, k, idx)
+        assert torch.equal(idx, ranked(key, k))
+        ctx.heavymix_topk(table, k, rnd32, idx, n_heavy=n_heavy, l2sq=l2sq)
+        heavy = est.double() ** 2 >= float(l2sq) / k
+        hkey = torch.where(heavy, key + (1 << 31), rnd >> 1)
+        if int(heavy.sum()) < k // 2:
+            assert short_of_k(hkey, rnd >> 1, d, k)[1]
+        assert torch.equal(idx, ranked(hkey, k)) and int(n_heavy) == int(heavy.sum())
+    ctx.close()
+
+
+@pytest.mark.parametrize("d,c,k", [(14_700_000, 1_470_000, 14_700), (25_600_000, 256_000, 25_600)])
+def test_short_selection_costs_about_a_full_estimate(monkeypatch, d, c, k):
+    # measured 1.2 and 1.4 times the call that estimates every coordinate directly
+    monkeypatch.delenv("GS_SELECT_PATH", raising=False)
+    monkeypatch.setenv("GS_ESTIMATE_PATH", "direct")
+    r, gen = 5, torch.Generator(device=DEV).manual_seed(d)
+    hp = synth.hash_params(synth.BASE_SEED + 121, r)
+    ctx = gs.GsContext(d, 1, r, c, k, hp)
+    m = sketch_of(large_at_samples(d, k, gen)[0], hp, c)
+    est, idx, full = torch.empty(d, device=DEV), *(torch.empty(k, dtype=torch.int32, device=DEV) for _ in range(2))
+    us = [best_us(lambda: ctx.unsketch_topk(m, k, full, est)), best_us(lambda: ctx.unsketch_topk(m, k, idx))]
+    print(f"[short] d={d} full {us[0]:.0f} us, short {us[1]:.0f} us", flush=True)
+    key = est.view(torch.int32).long() & 0x7FFFFFFF
+    assert short_of_k(key, key, d, k)[1] and torch.equal(idx, full)
+    assert us[1] < 2.0 * us[0]
+    ctx.close()
+
+
 # one emit range per CU up to 2^19 coordinates each (134M on 256 CUs), more ranges beyond; 1,024 of
 # them counted in LDS (2^29 coordinates)
 @pytest.mark.parametrize("path", ["pruned", "full"])

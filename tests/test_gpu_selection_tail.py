@@ -1,7 +1,8 @@
 """The selection's tail (digit passes and emit) on sketches made for its edges: keys many octaves
 above the sampled bound, ties from a few to all coordinates (the crowded bin that does not
-fit the LDS), one and two digit passes, one and many emit ranges, and the pruned pass falling
-short of k, all against the oracle's estimates and top-k bit for bit (needs an MI355X)."""
+fit the LDS), one and two digit passes, and one and many emit ranges, all against the oracle's
+estimates and top-k bit for bit (the pruned pass falling short of k: test_gpu_input_shapes.py; needs
+an MI355X)."""
 import numpy as np
 import pytest
 
