@@ -478,19 +478,32 @@ def test_unpacked_lists(monkeypatch, d, P, r, c, k):
     dv.close()
 
 
-@pytest.mark.parametrize("spin", ["0", "-1"])
-def test_emit_counts_earlier_words_itself(monkeypatch, spin):
-    # the emit's workgroups take their output offset from the counts their predecessors
-    # publish; with GS_EMIT_SPIN=0 a workgroup whose predecessors have not published yet, and
-    # with -1 every workgroup, counts the earlier bitmap words itself: the same indices
-    monkeypatch.setenv("GS_EMIT_SPIN", spin)
-    d, P, r, c, k = 4_200_000, 2, 3, 150_000, 9_000  # 33 emit workgroups
+@pytest.mark.parametrize("where", ["first", "middle", "last", "ends", "spread"])
+def test_emit_offsets_across_ranges(where):
+    # the emit's workgroups own a range of coordinates each and take their output offset from the counts of
+    # the ranges before: the selection within one or two of the ranges (the others without a selected
+    # coordinate), and in all of them
+    d, P, r, c, k = 4_200_003, 2, 3, 1_050_000, 2_000
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    per = max(4_096, -(--(-d // cus) // 64) * 64)  # coordinates of a range
+    ranges = -(-d // per)
+    at = {"first": [0], "middle": [ranges // 2], "last": [ranges - 1], "ends": [0, ranges - 1],
+          "spread": range(ranges)}[where]
     hp = synth.hash_params(synth.BASE_SEED + 45, r)
     rng = np.random.default_rng(45)
     dv = Dev(d, P, r, c, k, hp, 0.9)
-    g = rng.laplace(0, 1e-2, (P, d)).astype(np.float32)
+    g = rng.laplace(0, 1e-4, (P, d)).astype(np.float32)
+    places = np.concatenate([np.arange(q * per, min(d, (q + 1) * per)) for q in at])
+    big = rng.choice(places, k, replace=False)
+    g[:, big] += rng.choice([-1.0, 1.0], k).astype(np.float32) * rng.uniform(1.0, 2.0, k).astype(np.float32)
     z = np.zeros_like(g)
-    chain_check(dv, g, z, z.copy(), k, 0.9, label=f"emit spin {spin}")
+    chain_check(dv, g, z, z.copy(), k, 0.9, label=f"emit ranges {where}")
+    held = np.bincount(host(dv.idx) // per, minlength=ranges)
+    assert held.sum() == k
+    if where != "spread":
+        assert held[list(at)].sum() > 0.9 * k and (held == 0).sum() > ranges // 4
+    else:
+        assert (held > 0).mean() > 0.9
     dv.close()
 
 
