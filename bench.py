@@ -43,7 +43,7 @@ MI355X_CUS = 256  # compute units, when no device is visible to ask
 METRIC = "gradient coords/sec per full sketch+unsketch+top-k step; % of HBM peak"
 
 
-def stage_bytes(w, state: str = "vector") -> dict:
+def stage_bytes(w, state: str = "vector", layout: str = "interleaved") -> dict:
     """Algorithmic bytes each stage must move (not what an implementation happens to move)."""
     P, d, r, c, k = w.P, w.d, w.r, w.c, w.k
     if state == "sketch":
@@ -55,12 +55,15 @@ def stage_bytes(w, state: str = "vector") -> dict:
             "state_update": 8 * k,                # values and the correction of touched cells
         }
     # the fused step never writes the P per-worker tables: its tiles merge their own cells
+    gather = 12 * P * k + 4 * k              # read v, zero u and v at k coordinates; write k values
+    in_select = gathers_in_emit(w, layout)
     return {
         "accumulate": 20 * P * d,            # read g, u, v; write u, v
         "sketch": 4 * P * d + 4 * r * c,     # read v once, write the merged table
         "merge": 0,                          # no kernel: merged inside the sketch's tiles
-        "select": 4 * r * c + 4 * k,         # read the merged table, write k indices
-        "gather_reset": 12 * P * k + 4 * k,  # read v, zero u and v at k coordinates; write k values
+        # read the merged table, write k indices
+        "select": 4 * r * c + 4 * k + (gather if in_select else 0),
+        "gather_reset": 0 if in_select else gather,
     }
 
 
@@ -137,6 +140,19 @@ def num_cus() -> int:
     return MI355X_CUS
 
 
+def gather_lanes(w, layout: str) -> int:
+    """Lanes that share a selected coordinate in the gather: a power of two."""
+    lanes = state_stride(w.P) // 4 if layout == "interleaved" else w.P
+    return 1 << (lanes - 1).bit_length()
+
+
+def gathers_in_emit(w, layout: str) -> bool:
+    """Whether the selection's last kernel gathers and resets (the library's rule: the workgroup that owns
+    the most of the selection has at most 12 passes of its 1,024 threads, or the selection is over d/8)."""
+    own = min(2 ** 19, max(4096, -(-(-(-w.d // num_cus())) // 64) * 64))  # coordinates of an emit workgroup
+    return min(w.k, own) * gather_lanes(w, layout) <= 12 * 1024 or 8 * w.k > w.d
+
+
 def stage_kernels(w, layout: str = "interleaved", plan: dict = None) -> dict:
     """The kernels each stage of the fused step launches (names as rocprofv3 reports them).
     `plan` is the context's gs_describe; without it the library's size rule is assumed (list
@@ -148,10 +164,17 @@ def stage_kernels(w, layout: str = "interleaved", plan: dict = None) -> dict:
         acc = ["k_accumulate4"]
     else:
         acc = [f"k_vi_il<{w.P}, true>"]
-    tail = ["k_digit2", "k_emit"]  # the emit also gathers the exact values and resets
+    pruned = w.d * w.r > 2_000_000  # (the library's choice above 2,000,000 cells of d*r)
+    tail = ["k_digit2<false>", f"k_emit<{w.r}>"] if pruned else ["k_digit2<true>", "k_emit<0>"]
+    if gathers_in_emit(w, layout):
+        gather = []
+    elif layout == "worker_major" and w.P > 1 and w.k >= 32768:
+        gather = [f"k_gather_columns<{w.P if w.P <= 16 else 0}>"]
+    else:
+        gather = ["k_gather_reset"]
     # the full estimate's form: two coordinates per thread per pass up to 8 * 256 * (CUs)
     unsketch = f"k_unsketch<{w.r}, {2 if w.d <= 8 * 256 * num_cus() else 1}>"
-    if w.d * w.r > 2_000_000:  # pruned selection (the library's choice above 2,000,000 cells of d*r)
+    if pruned:
         row = -(-w.c // 128) * 128  # cells of a row of the heavy-cell map
         if (160 * 1024 - 256 - w.r * row // 8) // 4 >= 512:  # all rows fit the LDS beside the queue buffer
             lookups = [f"k_pruned<{w.r}, false, 0>"]
@@ -167,14 +190,16 @@ def stage_kernels(w, layout: str = "interleaved", plan: dict = None) -> dict:
     return {
         "accumulate": acc,
         # packed lists (the library's choice here); one worker in the worker-major layout: its
-        # plain state vector gathered directly (the fourth template argument)
+        # plain state vector gathered directly (the fourth template argument); the last argument: lists
+        # beyond 256 MB read past the caches where a lane takes an entry
         "sketch": [f"k_pull<{w.P}, {4 if w.P <= 4 else 6}, true, "
-                   f"{'true' if w.P == 1 and layout == 'worker_major' else 'false'}, {state_stride(w.P)}>"],
+                   f"{'true' if w.P == 1 and layout == 'worker_major' else 'false'}, {state_stride(w.P)}, "
+                   f"{'true' if w.P <= 4 and 4 * w.r * w.d > 256 << 20 else 'false'}>"],
         # the tiles merge their own cells; small sketches' tiles, split into list segments,
         # are summed here
         "merge": [f"k_merge_partials<{w.P}>"] if segmented else [],
         "select": select,
-        "gather_reset": [],  # in the selection's k_emit
+        "gather_reset": gather,
     }
 
 
@@ -352,7 +377,7 @@ def main():
     if args.state == "sketch":  # stages of the sketch-space step
         stage_ms = {"interleave": stage_ms["accumulate"], "sketch": stage_ms["sketch"], "merge": stage_ms["merge"],
                     "select": stage_ms["select"], "state_update": stage_ms["gather_reset"]}
-    sb = stage_bytes(w, args.state)
+    sb = stage_bytes(w, args.state, layout)
     kern = stage_kernels(w, layout, plan)
     stages = []
     for st, st_ms in stage_ms.items():

@@ -224,7 +224,9 @@ gs_status gs_apply_update(gs_ctx* ctx, void* stream, const int32_t* idx, const f
  * HIP event on `stream` before the first stage and after each stage, synchronizes the stream
  * and writes the stage durations in milliseconds to the HOST array stage_ms[GS_NUM_STAGES]:
  *   [0] accumulate   [1] sketch   [2] merge   [3] estimate + top-k selection
- *   [4] gather + reset
+ *   [4] gather + reset, where a kernel of its own does them. Where few of the selected coordinates
+ *       can fall to one workgroup the selection's last kernel gathers and resets: they are part of [3], and
+ *       [4] is the time between two events, as [2] is where the sketch's tiles merge their own cells.
  * Unlike gs_step this call blocks until the step has finished. */
 #define GS_NUM_STAGES 5
 gs_status gs_step_profiled(gs_ctx* ctx, void* stream, const float* g, float* u, float* v, int64_t k, float* merged,
@@ -235,7 +237,7 @@ gs_status gs_step_profiled(gs_ctx* ctx, void* stream, const float* g, float* u, 
  * calls of gs_step, gs_step_heavymix or gs_step_sketch_momentum records one event on its
  * stream before its first stage and one after each stage, without synchronizing (stages as
  * for gs_step_profiled; for gs_step_sketch_momentum [0] is the gradient interleave and [4]
- * the estimate correction of the sketch-space state). gs_timing_stop synchronizes, writes the
+ * the estimate correction of the sketch-space state, its values in [3] or [4] as the gather is). gs_timing_stop synchronizes, writes the
  * mean stage durations in milliseconds to the HOST array stage_ms[GS_NUM_STAGES] (may be
  * NULL) and the number of timed steps to *n_steps (may be NULL), and frees the events.
  * 1 <= max_steps <= 2^20; starting while active, or stopping while not, is

@@ -410,8 +410,18 @@ static hipError_t launch_sketch_phase(gs_ctx* x, hipStream_t s, const float* g, 
   return e;
 }
 
-static hipError_t launch_sketch_phase(gs_ctx* x, hipStream_t s, const float* g, float* u, float* v, float* merged) {
-  return launch_sketch_phase(x, s, g, u, v, merged, [x, s](int t) { gs::stage_mark(x, s, t); });
+// Selection and gather + reset of the fused step: select(ga) enqueues the selection, with the gather in its
+// last kernel where ga is not null; mark(t) is called after stages 3 and 4.
+template <class Select, class Mark>
+static hipError_t launch_select_phase(gs_ctx* x, hipStream_t s, float* u, float* v, int64_t k, const int32_t* idx,
+                                      float* values, Select select, Mark mark) {
+  const gs::GatherArgs ga = gs::gather_args(x, u, v, values);
+  const bool in_emit = gs::emit_gathers(x->d, x->num_cus, k, ga);
+  hipError_t e = select(in_emit ? &ga : nullptr);
+  mark(4);
+  if (e == hipSuccess && !in_emit) e = gs::launch_gather(x->num_cus, s, x->hs, nullptr, idx, k, ga);
+  mark(5);
+  return e;
 }
 
 extern "C" {
@@ -424,11 +434,12 @@ gs_status gs_step(gs_ctx* x, void* stream, const float* g, float* u, float* v, i
   if (k < 1 || k > x->k_max) return fail(x, GS_ERR_INVALID_ARG, "gs_step: k must satisfy 1 <= k <= k_max");
   if (unaligned_without_copy(x, v)) return fail(x, GS_ERR_INVALID_ARG, std::string("gs_step") + kUnalignedMsg);
   hipStream_t s = as_stream(stream);
-  hipError_t e = launch_sketch_phase(x, s, g, u, v, merged);
-  const gs::GatherArgs ga = gs::gather_args(x, u, v, values);
-  if (e == hipSuccess) e = gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx, &ga);
-  gs::stage_mark(x, s, 4);
-  gs::stage_mark(x, s, 5);
+  auto mark = [&](int t) { gs::stage_mark(x, s, t); };
+  hipError_t e = launch_sketch_phase(x, s, g, u, v, merged, mark);
+  if (e == hipSuccess)
+    e = launch_select_phase(x, s, u, v, k, idx, values, [&](const gs::GatherArgs* ga) {
+      return gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx, ga);
+    }, mark);
   return device_status(x, e, "gs_step");
 }
 
@@ -452,11 +463,12 @@ gs_status gs_step_heavymix(gs_ctx* x, void* stream, const float* g, float* u, fl
   if (unaligned_without_copy(x, v))
     return fail(x, GS_ERR_INVALID_ARG, std::string("gs_step_heavymix") + kUnalignedMsg);
   hipStream_t s = as_stream(stream);
-  hipError_t e = launch_sketch_phase(x, s, g, u, v, merged);
-  const gs::GatherArgs ga = gs::gather_args(x, u, v, values);
-  if (e == hipSuccess) e = gs::launch_heavymix_topk(x, s, merged, k, rnd, nullptr, idx, n_heavy, nullptr, &ga);
-  gs::stage_mark(x, s, 4);
-  gs::stage_mark(x, s, 5);
+  auto mark = [&](int t) { gs::stage_mark(x, s, t); };
+  hipError_t e = launch_sketch_phase(x, s, g, u, v, merged, mark);
+  if (e == hipSuccess)
+    e = launch_select_phase(x, s, u, v, k, idx, values, [&](const gs::GatherArgs* ga) {
+      return gs::launch_heavymix_topk(x, s, merged, k, rnd, nullptr, idx, n_heavy, nullptr, ga);
+    }, mark);
   return device_status(x, e, "gs_step_heavymix");
 }
 
@@ -576,10 +588,10 @@ gs_status gs_step_profiled(gs_ctx* x, void* stream, const float* g, float* u, fl
     if (erec == hipSuccess) erec = hipEventRecord(ev[t], s);
   };
   if (e == hipSuccess) e = launch_sketch_phase(x, s, g, u, v, merged, mark);
-  const gs::GatherArgs ga = gs::gather_args(x, u, v, values);
-  if (e == hipSuccess) e = gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx, &ga);
-  mark(4);
-  mark(5);
+  if (e == hipSuccess)
+    e = launch_select_phase(x, s, u, v, k, idx, values, [&](const gs::GatherArgs* ga) {
+      return gs::launch_unsketch_topk(x, s, merged, k, nullptr, idx, ga);
+    }, mark);
   if (e == hipSuccess) e = erec;
   if (e == hipSuccess) e = hipEventSynchronize(ev[5]);
   for (int t = 0; t < GS_NUM_STAGES && e == hipSuccess; ++t) e = hipEventElapsedTime(&stage_ms[t], ev[t], ev[t + 1]);

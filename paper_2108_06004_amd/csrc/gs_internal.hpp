@@ -223,18 +223,19 @@ hipError_t launch_sketch_acc(const gs_ctx* x, hipStream_t s, const float* v, Sta
 hipError_t launch_sketch(const gs_ctx* x, hipStream_t s, const float* v, StateView sv, float* tables);
 hipError_t launch_merge_acc(const gs_ctx* x, hipStream_t s, float* merged);
 hipError_t launch_merge(const gs_ctx* x, hipStream_t s, const float* tables, float* merged);
-// With ga (may be null) the selected coordinates are gathered too, in the selection's last
-// kernel or in one of its own.
+// With ga (may be null) the selected coordinates are gathered too, in the selection's last kernel.
 hipError_t launch_unsketch_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, float* est, int32_t* idx,
                                 const GatherArgs* ga);
 hipError_t launch_heavymix_topk(gs_ctx* x, hipStream_t s, const float* merged, int64_t k, const uint32_t* rnd,
                                 float* est, int32_t* idx, int64_t* n_heavy, double* l2sq, const GatherArgs* ga);
 // From the last digit pass's staged keys to the ascending index list (and the gather); `level` is
-// that pass (0 or 1), pruned and hm say what the candidates are.
+// that pass (0 or 1), pruned says what the candidates are; rnd are HEAVYMIX's draws, or null.
 hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
                        const float* merged, const uint32_t* rnd, int64_t k, int pruned, int level, int32_t* idx,
                        int64_t* n_heavy, double* l2sq, const GatherArgs* ga);
 hipError_t prepare_emit();
+// Whether that kernel is where to gather k of d coordinates; else launch_gather after it.
+bool emit_gathers(int64_t d, int num_cus, int64_t k, const GatherArgs& ga);
 // The gather alone, over idx[0, k).
 hipError_t launch_gather(int num_cus, hipStream_t s, const HashSet& hs, const float* merged, const int32_t* idx,
                          int64_t k, const GatherArgs& ga);

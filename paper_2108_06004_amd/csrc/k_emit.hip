@@ -490,6 +490,17 @@ __global__ void __launch_bounds__(kBlock) k_emit(EmitArgs a, HashSet hs, GatherA
 
 }  // namespace
 
+// The emit gathers what each workgroup has written, unless one could have so much of it (the selection
+// in one part of d, a layer's gradients) that it would work alone: more than 12 passes of its threads,
+// in a selection of at most d/8. With all large estimates within d/256, 66M x 16 takes 10.9 ms so, 10.1
+// with a gather of its own, 25.6M x 8 worker-major 1,968 and 1,662 us, 14.7M x 4 712 and 675; where they
+// are spread the kernel more costs 2 us (14.7M x 4 659 and 661; 1.2M x 6, 12 passes at most, 119
+// and 122). Beyond d/8 no workgroup has more than 8 times the mean (14.7M x 4, k = d/4: spread
+// 1,402 and 1,437 us, in one quarter of d 1,431 and 1,454).
+bool emit_gathers(int64_t d, int num_cus, int64_t k, const GatherArgs& ga) {
+  return std::min(k, emit_range(d, num_cus)) * ga.gl <= 12 * kBlock || 8 * k > d;
+}
+
 hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBufs& b, hipStream_t s,
                        const float* merged, const uint32_t* rnd, int64_t k, int pruned, int level, int32_t* idx,
                        int64_t* n_heavy, double* l2sq, const GatherArgs* ga) {
@@ -514,16 +525,8 @@ hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBu
   a.k = (uint32_t)k;
   a.level = level;
   const unsigned blocks = (unsigned)((d + a.range - 1) / a.range);
-  // The emit gathers what each workgroup has written, unless one could have so much of it (the selection
-  // in one part of d, a layer's gradients) that it would work alone: more than 12 passes of its threads,
-  // in a selection of at most d/8. With all large estimates within d/256, 66M x 16 takes 10.9 ms so, 10.1
-  // with a gather of its own, 25.6M x 8 worker-major 1,968 and 1,662 us, 14.7M x 4 712 and 675; where they
-  // are spread the kernel more costs 2 us (14.7M x 4 659 and 661; 1.2M x 6, 12 passes at most, 119
-  // and 122). Beyond d/8 no workgroup has more than 8 times the mean (14.7M x 4, k = d/4: spread
-  // 1,402 and 1,437 us, in one quarter of d 1,431 and 1,454).
-  const bool own = !ga || std::min(k, a.range) * ga->gl <= 12 * kBlock || 8 * k > d;
   const size_t lds = (size_t)(a.range / 32) * sizeof(uint32_t);
-  const GatherArgs g = ga && own ? *ga : GatherArgs{};
+  const GatherArgs g = ga ? *ga : GatherArgs{};
   switch (pruned ? hs.r : 0) {
 #define GS_EMIT(R) \
   case R: hipLaunchKernelGGL(k_emit<R>, dim3(blocks), dim3(kBlock), lds, s, a, hs, g); break;
@@ -531,9 +534,7 @@ hipError_t launch_emit(const HashSet& hs, int64_t d, int num_cus, const SelectBu
 #undef GS_EMIT
     default: return hipErrorInvalidValue;
   }
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || own) return e;
-  return launch_gather(num_cus, s, hs, merged, idx, k, *ga);
+  return hipGetLastError();
 }
 
 hipError_t prepare_emit() {

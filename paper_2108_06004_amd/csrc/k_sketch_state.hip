@@ -8,8 +8,8 @@
 //   Delta_i = estimate of E at i, for i in Top_k               (the step's values)
 //   E <- fl(E - D) on every cell D touches, D = S(Delta) summed per cell in fp64 and
 //        rounded once; U <- 0 on those cells when momentum is reset
-// The selection's last kernel writes the values and clears the touched cells' fp64 accumulators
-// and claim bits; two passes over the k*r (coordinate, row) pairs follow: add the signed values
+// The selection's last kernel (or one after it) writes the values and clears the touched cells' fp64
+// accumulators and claim bits; two passes over the k*r (coordinate, row) pairs follow: add the signed values
 // (fp64 atomics), and let the first pair to claim each cell apply it.
 #include "gs_internal.hpp"
 
@@ -79,16 +79,17 @@ hipError_t launch_sketch_state(gs_ctx* x, hipStream_t s, const float* merged, fl
   const int64_t rc = (int64_t)x->r * x->c;
   hipLaunchKernelGGL(k_sketch_mom, dim3(grid_for(rc, kBlock, 8 * x->num_cus)), dim3(kBlock), 0, s, merged, U, E, rc,
                      x->rho);
-  // fp64 cell accumulators and claim bits: context scratch free once the selection is made; its
-  // last kernel writes the values and clears those of the cells the selection touches
+  // fp64 cell accumulators and claim bits: context scratch free once the selection is made
   GatherArgs ga{};
   ga.op = kGatherSketch;
   ga.gl = 1;
   ga.values = values;
   ga.acc = x->use_pull ? x->partial : x->acc64;
   ga.claim = x->heavy;
-  const hipError_t e = launch_unsketch_topk(x, s, E, k, nullptr, idx, &ga);
+  const bool in_emit = emit_gathers(x->d, x->num_cus, k, ga);
+  hipError_t e = launch_unsketch_topk(x, s, E, k, nullptr, idx, in_emit ? &ga : nullptr);
   stage_mark(x, s, 4);
+  if (e == hipSuccess && !in_emit) e = launch_gather(x->num_cus, s, x->hs, E, idx, k, ga);
   if (e != hipSuccess) return e;
   const dim3 block(kBlock);
   const int64_t n_pairs = k * x->r;

@@ -118,6 +118,18 @@ def test_roofline_names_the_co_dominant_stage_furthest_below_peak():
     assert bench.roofline_of([], 1, 1.0) is None
 
 
+@pytest.mark.parametrize("layout", ["interleaved", "worker_major"])
+@pytest.mark.parametrize("name", list(synth.WORKLOADS))
+def test_gather_bytes_are_counted_where_the_gather_runs(name, layout):
+    # in the selection's last kernel (the two small workloads), or in a kernel of its own
+    w = synth.WORKLOADS[name]
+    sb, kern = bench.stage_bytes(w, "vector", layout), bench.stage_kernels(w, layout)
+    gather = 12 * w.P * w.k + 4 * w.k
+    assert bench.gathers_in_emit(w, layout) == (w.d <= 270_000)
+    assert bool(kern["gather_reset"]) == (sb["gather_reset"] == gather)
+    assert sb["select"] + sb["gather_reset"] == 4 * w.r * w.c + 4 * w.k + gather
+
+
 def test_step_bytes_leave_out_the_tables_the_fused_step_never_writes():
     w = synth.WORKLOADS["laplace53-d25.6M-P8"]
     assert bench.step_bytes(w) == 20 * w.P * w.d + 8 * w.r * w.c + 12 * w.P * w.k + 8 * w.k

@@ -229,6 +229,27 @@ def test_clustered_step():
     assert us[1] < 1.07 * us[0]
 
 
+def test_stage_times_show_a_gather_of_its_own():
+    # 64 workers' values of 100,000 coordinates, gathered by a kernel after the selection: its time is in the
+    # fifth stage (measured 249 us, and 5 us of a stage without a kernel)
+    d, P, r, c, k = 2_000_000, 64, 2, 1_000, 100_000
+    ctx = gs.GsContext(d, P, r, c, k, synth.hash_params(synth.BASE_SEED + 127, r))
+    assert ctx.describe()["segments"] == 1  # no merge kernel
+    g = torch.randn((P, d), device=DEV)
+    u, v = torch.zeros_like(g), torch.zeros_like(g)
+    merged = torch.empty((r, c), dtype=torch.float32, device=DEV)
+    idx, values = torch.empty(k, dtype=torch.int32, device=DEV), torch.empty(k, dtype=torch.float32, device=DEV)
+    for _ in range(2):
+        ctx.step(g, u, v, k, merged, idx, values)
+    ctx.timing_start(5)
+    for _ in range(5):
+        ctx.step(g, u, v, k, merged, idx, values)
+    stage, n = ctx.timing_stop()
+    print(f"[stages] {stage}", flush=True)
+    assert n == 5 and stage["gather_reset"] > 4 * stage["merge"]
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,k", [(500_000, 32_767), (500_000, 32_768), (524_288, 32_768), (524_289, 32_768),
                                  (40_001, 40_001)])
 @pytest.mark.parametrize("P", [2, 4, 5, 8, 9, 16, 17, 33, 64])
