@@ -117,13 +117,14 @@ typedef struct gs_ctx gs_ctx; /* opaque: a copy of the config plus device scratc
  * selects the atomic form for any shape, and GS_SKETCH_PATH=unpacked keeps the gather's
  * lists in their unpacked form (diagnostic overrides; results agree within the table
  * tolerance). A selection without an estimate vector prunes (estimates only coordinates
- * with enough heavy cells) when d*r exceeds 2,000,000 and k is a small part of d (up to a tenth
- * or a fifth, by the table's size) and estimates every coordinate
+ * with enough heavy cells) when d*r exceeds 2,000,000 and k is a small part of d (up to between a
+ * tenth and a third, by the table's size and the selection) and estimates every coordinate
  * otherwise; GS_SELECT_PATH=pruned or =full fixes that choice, and GS_ESTIMATE_PATH=tiles or
  * =direct how every coordinate is estimated (the selected set is the same either way).
  * Device scratch is about (16 + 4.1 r) d + 8 S P r c bytes (S list segments per tile, 1
  * unless the sketch is small), plus the 4 PP d bytes of the interleaved copy (PP = P rounded
- * up to 4) in a worker-major context with P > 1 or with GS_OPT_ROW_COPY, plus 2 r d bytes while the
+ * up to 4) in a worker-major context with P > 1 or with GS_OPT_ROW_COPY, plus r d / 8 bytes where r >= 4
+ * and r c outgrows 1.3 million cells (up to 2.6 million columns), plus 2 r d bytes while the
  * lists are built: with the interleaved state and no copy 1.0 GB at d = 25.6M, P = 8, r = 5,
  * c = 256,000 (1.8 GB worker-major) and 61 GB at d = 2^31 - 2, P = 2, r = 3 (95 GB
  * worker-major). The atomic form replaces the lists and the copy with 8 P r c bytes. */

@@ -17,10 +17,11 @@ struct StateView {
   __host__ __device__ int64_t at(int q, int64_t i) const { return (int64_t)q * qs + i * is; }
 };
 
-// Top-k selection works on 32-bit keys (the bits of |estimate|) in three radix digits.
-constexpr int kDigit1Shift = 20;  // digit 1: key bits 31..20 (12 bits; |est| keys leave bit 31 clear,
-constexpr int kDigit1Bins = 4096; // HEAVYMIX keys use it to rank the heavy set above the fill)
-constexpr int kDigitBins = 1024;  // digits 2 and 3: key bits 19..10 and 9..0
+// Top-k selection works on 32-bit keys: the bits of |estimate|, with bit 31 clear; HEAVYMIX's use bit 31
+// to rank the heavy set above the fill.
+constexpr int kDigit1Shift = 20;  // first digit of the sampled keys: bits 31..20
+constexpr int kDigit1Bins = 4096; // bins of the candidates' and the sampled keys' histograms (cand_bin)
+constexpr int kDigitBins = 1024;  // of the ten bits below a bin's
 
 // Passes of the emit's workgroups over a list too long for the LDS: 10 bits of a word of up to 63 each,
 // one that marks, and the end.
@@ -66,16 +67,16 @@ struct GatherArgs {
 constexpr int kGatherNone = 0, kGatherRows = 1, kGatherWorkers = 2, kGatherSketch = 3;
 
 // Buffers of the selection's tail: the context's scratch for gs_unsketch_topk and friends, or the
-// static scratch of gs_unsketch_topk_static. hist, hist2, hist_c, counts, ctl->n_stage and
-// ctl->emit_ticket are zero between calls.
+// static scratch of gs_unsketch_topk_static. hist, hist2, hist_c, counts, ctl->n_stage, ctl->emit_ticket
+// and ctl->settle (but its pass[]) are zero between calls.
 struct SelectBufs {
   uint32_t* cand_key;   // [d] candidate keys (dense: key of coordinate t at t)
   int32_t* cand_idx;    // [d] candidate coordinates (not used for dense candidates)
   uint32_t* keys;       // [d] staged keys of the k-th key's bin (every key, when the pruned pass fell short)
   int32_t* stage_idx;   // [d] their coordinates
   uint32_t* stage2;     // [2 kStage2Cap] keys, then coordinates, staged by a second digit pass
-  uint32_t* hist;       // [kDigit1Bins] digit-1 histogram of the dense keys
-  uint32_t* hist2;      // [kDigitBins] digit-2 histogram of the bin's keys
+  uint32_t* hist;       // [kDigit1Bins] histogram of the dense keys
+  uint32_t* hist2;      // [kDigitBins] of the next ten bits of the bin's keys
   uint32_t* hist_c;     // [kDigit1Bins] histogram of pruned candidates
   SelectCtl* ctl;
   uint32_t* bitmap;     // [ceil(d/32)] pruned candidates above the k-th key's bin
@@ -147,12 +148,12 @@ struct gs_ctx {
 
   // scratch (device)
   uint32_t* keys = nullptr;       // [d] survivor queue of the pruned pass, then the staged keys
-  uint32_t* hist = nullptr;       // [kDigit1Bins], zero between calls
-  uint32_t* hist2 = nullptr;      // [kDigitBins] digit-2 histogram of bucket b1, zero between calls
-  uint32_t* hist_s = nullptr;     // [kDigit1Bins] digit-1 histogram of the sampled keys, zero between calls
-  uint32_t* hist_c = nullptr;     // [kDigit1Bins] digit-1 histogram of the pruned candidates, zero between calls
+  uint32_t* hist = nullptr;       // [kDigit1Bins] of every coordinate's key, zero between calls
+  uint32_t* hist2 = nullptr;      // [kDigitBins] of the next ten bits in the k-th key's bin, zero between calls
+  uint32_t* hist_s = nullptr;     // [kDigit1Bins] of the sampled keys' first digit, zero between calls
+  uint32_t* hist_c = nullptr;     // [kDigit1Bins] of the pruned candidates, zero between calls
   gs::SelectCtl* ctl = nullptr;   // [1]
-  int32_t* stage_idx = nullptr;   // [d] coordinates of the keys staged in `keys` for the digit-3 pass
+  int32_t* stage_idx = nullptr;   // [d] coordinates of the keys staged in `keys`
   uint32_t* cand_key = nullptr;   // [cand_cap]
   int32_t* cand_idx = nullptr;    // [cand_cap]
   int64_t cand_cap = 0;

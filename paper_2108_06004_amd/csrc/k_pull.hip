@@ -1000,7 +1000,7 @@ hipError_t prepare_pull_kernels(const gs_ctx* x) {
     if (e != hipSuccess) return e;
   }
   {
-    const int lds = (int)(x->plan.W * sizeof(float));  // at most 81,896 bytes (one worker)
+    const int lds = (int)(x->plan.W * sizeof(float));  // at most 81,792 bytes (one worker)
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_push<true>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e == hipSuccess)
