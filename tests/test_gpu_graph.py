@@ -134,3 +134,41 @@ def test_graph_replays_of_the_static_selection():
         assert torch.equal(est, ref[t][0]) and torch.equal(idx, ref[t][1]), f"static selection replay {t}"
     del graph
     assert np.isfinite(noise.sum().item())
+
+
+def test_graph_replays_of_selections_settled_in_passes(monkeypatch):
+    # one captured selection replayed on sketches whose end differs: short of k candidates, ties of nearly all
+    # coordinates, and an ordinary one; each replay equals the eager call on the same sketch
+    from test_gpu_input_shapes import large_at_samples, sketch_of
+
+    monkeypatch.setenv("GS_SELECT_PATH", "pruned")
+    d, r, c, k = 1_100_003, 5, 200_000, 11_000
+    hp = synth.hash_params(synth.BASE_SEED + 57, r)
+    gen = torch.Generator(device=DEV).manual_seed(57)
+    ties = torch.zeros((r, c), dtype=torch.float32, device=DEV)
+    ties[:, ::1000] = 1.0
+    tables = [sketch_of(large_at_samples(d, k, gen)[0], hp, c), ties,
+              sketch_of(torch.randn(d, generator=gen, device=DEV), hp, c)]
+    ctx = gs.GsContext(d, 1, r, c, k, hp)
+    m, idx = torch.empty_like(ties), torch.empty(k, dtype=torch.int32, device=DEV)
+    ref = []
+    for t in range(STEPS):
+        m.copy_(tables[t])
+        ctx.unsketch_topk(m, k, idx)
+        torch.cuda.synchronize()
+        ref.append(idx.clone())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.unsketch_topk(m, k, idx)
+    torch.cuda.synchronize()
+    noise = torch.empty(1 << 20, dtype=torch.float32, device=DEV)
+    for t in (0, 1, 2, 1, 0, 0):
+        m.copy_(tables[t])
+        idx.zero_()
+        noise.normal_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(idx, ref[t]), f"replay on sketch {t}"
+    del graph
+    ctx.close()
