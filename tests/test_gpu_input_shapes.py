@@ -215,7 +215,7 @@ def test_clustered_step():
     # one, 1.10 where one workgroup gathers it
     d, P, r, c, k = 25_600_000, 8, 5, 256_000, 25_600
     hp = synth.hash_params(synth.BASE_SEED + 113, r)
-    us = []
+    steps = []
     for make in (spread, clustered):
         gen = torch.Generator(device=DEV).manual_seed(7)
         g = make(d, d // 256, gen).repeat(P, 1)
@@ -223,7 +223,12 @@ def test_clustered_step():
         u, v = torch.zeros((P, d), device=DEV), torch.zeros((P, d), device=DEV)
         merged = torch.empty((r, c), dtype=torch.float32, device=DEV)
         idx, values = torch.empty(k, dtype=torch.int32, device=DEV), torch.empty(k, dtype=torch.float32, device=DEV)
-        us.append(best_us(lambda: ctx.step(g, u, v, k, merged, idx, values)))
+        steps.append((ctx, (g, u, v, k, merged, idx, values)))
+    us = [float("inf")] * 2
+    for _ in range(5):  # in turn: the step's own time drifts by percents
+        for t, (ctx, args) in enumerate(steps):
+            us[t] = min(us[t], best_us(lambda: ctx.step(*args), reps=2))
+    for ctx, _ in steps:
         ctx.close()
     print(f"[clustered step] spread {us[0]:.0f} us, clustered {us[1]:.0f} us", flush=True)
     assert us[1] < 1.07 * us[0]
